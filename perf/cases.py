@@ -5,9 +5,10 @@ Kinds of case:
 
 * ``solve``  -- a capped eigensolve from a start block the caller holds (the inner solve of an
   outer loop, or a solve that is polled): ``set_x0``, ``solve``, ``get_x``, ``residuals``.
-* ``refine`` -- a mixed-precision solve to a float64 tolerance, and the spectral projector of
-  the basis it finds applied to a block of the caller's.
-* ``filter`` -- Chebyshev-filtered subspace iteration on a matrix-free stencil.
+* ``refine`` -- a mixed-precision solve to a float64 tolerance, and a vector of the caller's
+  projected onto the subspace it finds.
+* ``filter`` -- Chebyshev-filtered subspace iteration on a matrix-free stencil, and a vector
+  projected onto the filtered subspace.
 * ``batch``  -- many independent Schroedinger problems of uneven sizes in one persistent launch.
 * ``ortho``  -- Cholesky QR of a caller's block.
 * ``net`` / ``train`` -- the warm-start network: a forward pass, a training step.
@@ -239,6 +240,10 @@ def _net_inputs(case, g):
     return V.contiguous(), flat, Xs if Xs is None else Xs.contiguous()
 
 
+def _project(X, b):
+    return (X * (X * b).sum(0)).sum(1)
+
+
 def prepare(case, seed):
     g, kind = _gen(seed), case["kind"]
     if kind in ("solve", "refine", "filter"):
@@ -256,8 +261,8 @@ def prepare(case, seed):
         n = A.n if stencil else A[3]
         X0 = _block(n, case["p"], g)
         s = {"kind": kind, "X0": X0, "solver": gsi.Solver(A, X0, case["p"], **opts)}
-        if kind == "refine":
-            s["B"] = _block(n, 8, g)
+        if kind != "solve":
+            s["b"] = _block(n, 1, g)
         return s
     if kind == "batch":
         mats, ps, x0 = _batch(case, g)
@@ -278,20 +283,17 @@ def prepare(case, seed):
 
 def run(state):
     kind = state["kind"]
-    if kind in ("solve", "filter"):
+    if kind in ("solve", "refine", "filter"):
         s = state["solver"]
         s.set_x0(state["X0"])
         s.solve()
         X = s.get_x()
         ritz, res, _, _ = s.residuals()
-        return {"X": X, "ritz": ritz, "res": res}
-    if kind == "refine":
-        s = state["solver"]
-        s.set_x0(state["X0"])
-        s.solve()
-        ritz = s.residuals()[0]
-        X = s.get_x()
-        return {"ritz": ritz, "PB": X @ (X.t() @ state["B"])}
+        if kind == "solve":
+            return {"X": X, "ritz": ritz, "res": res}
+        # a converged solve's residuals are rounding, and the columns' signs are free
+        proj = _project(X, state["b"])
+        return {"ritz": ritz, "proj": proj} if kind == "refine" else {"ritz": ritz, "res": res, "proj": proj}
     if kind == "batch":
         s = state["solver"]
         s.solve()
@@ -523,13 +525,13 @@ def exact(case, seed):
             return {"X": X, "ritz": ritz, "res": res}
         if kind == "refine":
             X = _descend(op, X0, _norm_inf(A), 300, True, 1e-13)
-            return {"ritz": _ritz(op, X, sign)[0], "PB": X @ (X.t() @ _block(A[3], 8, g))}
+            return {"ritz": _ritz(op, X, sign)[0], "proj": _project(X, _block(A[3], 1, g))}
         X = _orth(X0)
         X = _ritz(op, X, sign)[2]
         for _ in range(case["iters"]):
             X = _ritz(op, _orth(_filtered(op, X, case["degree"], *_interval(case))), sign)[2]
         ritz, res, _ = _ritz(op, X, sign)
-        return {"X": None, "ritz": ritz, "res": res}  # the columns' signs are free
+        return {"ritz": ritz, "res": res, "proj": _project(X, _block(A[3], 1, g))}
     if kind == "batch":
         if case["count"] * case["iters"] > 1500:
             return None
