@@ -537,9 +537,8 @@ __device__ __noinline__ bool b_chol_inv(const double* G, double* Mout, int p, do
 // Out-of-line wrappers: the solver below calls every pass as a function, so each keeps its
 // own register allocation instead of the sum over one giant inlined body.
 template <int PP>
-__device__ __noinline__ int b_eig(double* small, int p, bool warm, double* lds, double* cs, int* uv, int* nrot,
-                                  int* anyr) {
-  return eig_dev<PP>(small, p, warm, lds, cs, uv, nrot, anyr);
+__device__ __noinline__ int b_eig(double* small, int p, bool warm, double* lds) {
+  return eig_dev<PP>(small, p, warm, to_lds(lds));
 }
 template <int PP>
 __device__ __noinline__ void b_linesearch(const double* PZr, const double* PYr, double* small, int p, double* lds,
@@ -551,12 +550,10 @@ __device__ __noinline__ void b_linesearch(const double* PZr, const double* PYr, 
 
 struct BatchShared {
   Terms terms;
-  double cs[2 * MAXP];
   double red[12];
   double xv[8];
   double smu, sbmax;
-  int uv[MAXP];
-  int nrot, anyr, sok, sevals, bad, restart_next, flag, want, job, rank;
+  int sok, sevals, bad, restart_next, flag, want, job, rank;
 };
 
 // Wall-clock ticks spent per pass (indices of the GSI_PASS_* enumeration).
@@ -870,7 +867,7 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
     for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) S[e] = 0.5 * (G2[e] + G2[(e % PP) * PP + e / PP]);
     pass_barrier();
     clk.mark(GSI_PASS_GRAM);
-    b_eig<PP>(small, p, v_valid, dl, sh.cs, sh.uv, &sh.nrot, &sh.anyr);
+    b_eig<PP>(small, p, v_valid, dl);
     v_valid = true;
     clk.mark(GSI_PASS_EIG);
     // SpMM of this member's rows (every row of P is final after the exchange above) and
@@ -935,33 +932,28 @@ __device__ __noinline__ void final_ritz(BatchProblem& pr, unsigned char* lds, Ba
   const int p = pr.p;
   double* dl = reinterpret_cast<double*>(lds + PP * PP * sizeof(double) + 64);
   double* C = small + S_C * PP * PP;
-  double* S = small + S_S * PP * PP;
+  constexpr int LD = DLD<PP>;
+  double* A = to_lds(dl);
+  double* lam = A + PP * LD;
+  int* ord = reinterpret_cast<int*>(lam + PP);
   pass_barrier();
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) S[e] = C[e];
-  pass_barrier();
-  b_eig<PP>(small, p, false, dl, sh.cs, sh.uv, &sh.nrot, &sh.anyr);
-  // eig_dev clamps negative eigenvalues at zero (it is written for P^T P): take the Ritz
-  // values as diag(V^T C V) with the eigenvectors it returned, sorted descending
-  double* V = small + S_V * PP * PP;
-  double* T1 = dl;
-  wg_mm<PP>(C, false, V, false, T1);
-  __syncthreads();
-  double* th = T1 + PP * PP;  // LDS scratch for the p Ritz values
-  for (int i = threadIdx.x; i < p; i += blockDim.x) {
-    double s = 0.0;
-    for (int q = 0; q < PP; ++q) s += V[q * PP + i] * T1[q * PP + i];
-    th[i] = s;
+  diag_order(p, ord, lam, [&](int i) { return C[i * PP + i]; });
+  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
+    const int i = e / PP, j = e % PP;
+    A[i * LD + j] = i < p && j < p ? C[ord[i] * PP + ord[j]] : 0.0;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < p; ++i) {
-      const double v = th[i];
-      int j = i - 1;
-      while (j >= 0 && th[j] < v) { th[j + 1] = th[j]; --j; }
-      th[j + 1] = v;
-    }
-    for (int i = 0; i < p; ++i) pr.ritz[i] = th[i];
+  // C is indefinite: its largest absolute row sum makes it positive semidefinite
+  double shift = 0.0;
+  for (int i = 0; i < p; ++i) {
+    double r = 0.0;
+    for (int j = threadIdx.x & 63; j < p; j += 64) r += fabs(A[i * LD + j]);
+    shift = fmax(shift, wave_sum(r));
   }
+  __syncthreads();
+  eig_lds<PP>(p, A, ord, shift, lam);
+  __syncthreads();
+  for (int i = threadIdx.x; i < p; i += blockDim.x) pr.ritz[rank_desc(lam, p, i)] = lam[i];
   __syncthreads();
 }
 
@@ -1136,7 +1128,7 @@ __global__ void k_batched_reset(BatchCtl* ctl) {
 }
 
 // dynamic LDS: product matrix (PP^2 doubles at most) + 64 bytes + 4 PP (PP+1) doubles
-// (Jacobi, line search, Gram reduction)
+// (eigendecomposition, line search, Gram reduction)
 constexpr int batched_lds() { return 32 * 32 * 8 + 64 + 4 * 32 * 33 * 8; }
 
 }  // namespace gsi

@@ -1,6 +1,7 @@
 // Single-workgroup float64 solves on the p x p projected problem: the stop test and
-// Polak-Ribiere coefficient, the eigendecomposition of P^T P (parallel cyclic Jacobi in
-// LDS, warm-started from the previous iteration's eigenvectors), the line-search diagonals,
+// Polak-Ribiere coefficient, the eigendecomposition of P^T P (one-sided Jacobi on its
+// Cholesky factor, warm-started from the previous iteration's eigenvectors), the line-search
+// diagonals,
 // the exact line search (bracket from the branch roots, Brent's method on phi'), the
 // retraction factor M, Cholesky QR and Rayleigh-Ritz.
 //
@@ -125,17 +126,13 @@ __global__ __launch_bounds__(WG) void k_after_dir(int PP, const double* __restri
 
 // Eigendecomposition of P^T P (see eig_dev), one workgroup.
 template <int PP>
-__global__ __launch_bounds__(WG) void k_eig(double* __restrict__ small, Scalars* __restrict__ sc) {
+__global__ __launch_bounds__(dense_threads(PP)) void k_eig(double* __restrict__ small, Scalars* __restrict__ sc) {
   if (sc->done || sc->null_step) return;
   // this single workgroup shares its CU with the SpMM running concurrently: raise its
   // waves' issue priority so the latency-bound rotation rounds are not starved
   __builtin_amdgcn_s_setprio(3);
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  __shared__ double cs[2 * MAXP];
-  __shared__ int uv[MAXP];
-  __shared__ int nrot, anyr;
-  const int sweeps = eig_dev<PP>(small, sc->p, sc->v_valid != 0, reinterpret_cast<double*>(lds_raw), cs, uv, &nrot,
-                                 &anyr);
+  const int sweeps = eig_dev<PP>(small, sc->p, sc->v_valid != 0, reinterpret_cast<double*>(lds_raw));
   if (threadIdx.x == 0) {
     sc->v_valid = 1;
     sc->sweeps = sweeps;
@@ -300,75 +297,67 @@ __global__ __launch_bounds__(WG) void k_transform_cw(double* __restrict__ small,
 }
 
 // Rayleigh-Ritz: eig of sym(red) (p x p): eigenvalues descending into vals[0..p),
-// eigenvectors as the columns of small[S_M] (stride PP, padding zero).
-__global__ __launch_bounds__(WG) void k_ritz(int PP, int p, const double* __restrict__ red, double* __restrict__ small,
-                                             double* __restrict__ vals) {
+// eigenvectors as the columns of small[S_M] (stride PP, padding zero). sym(red) is indefinite;
+// its largest absolute row sum bounds the spectrum and makes it a positive one.
+template <int PP>
+__global__ __launch_bounds__(dense_threads(PP)) void k_ritz(int p, const double* __restrict__ red,
+                                                            double* __restrict__ small, double* __restrict__ vals) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  // p up to 64 in LDS; above, in the work area of the small buffer
-  const bool wide = PP > PP_LDS_MAX;
-  double* A = wide ? small + small_work_offset(PP) + 4 * PP * (PP + 1) : reinterpret_cast<double*>(lds_raw);
-  double* V = A + (wide ? PP * (PP + 1) : MAXP * (MAXP + 1));
-  __shared__ double cs[2 * MAXP];  // at most 64 rotations per round (p <= 128)
-  __shared__ int uv[MAXP];
-  __shared__ int nrot, anyr;
-  __shared__ int order[TMAXP];
-  const int ld = p | 1;  // odd stride: no LDS bank conflicts in the column sweeps
-  for (int e = threadIdx.x; e < p * p; e += blockDim.x) {
-    const int i = e / p, j = e % p;
-    A[i * ld + j] = 0.5 * (red[i * PP + j] + red[j * PP + i]);
-    V[i * ld + j] = (i == j) ? 1.0 : 0.0;
+  constexpr int LD = DLD<PP>;
+  double* A = reinterpret_cast<double*>(lds_raw);
+  __shared__ double lam[PP], row[PP];
+  __shared__ int order[PP];
+  const int m = 16 * ((p + 15) >> 4);
+  diag_order(p, order, row, [&](int i) { return red[i * PP + i]; });
+  for (int i = threadIdx.x >> 6; i < m; i += blockDim.x >> 6)
+    for (int j = threadIdx.x & 63; j < m; j += 64)
+      A[i * LD + j] =
+          i < p && j < p ? 0.5 * (red[order[i] * PP + order[j]] + red[order[j] * PP + order[i]]) : 0.0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < p; i += blockDim.x) {
+    double s = 0.0;
+    for (int j = 0; j < p; ++j) s += fabs(A[i * LD + j]);
+    row[i] = s;
   }
   __syncthreads();
-  jacobi(p, ld, A, V, cs, uv, &nrot, &anyr);
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < p; ++i) order[i] = i;
-    for (int i = 1; i < p; ++i) {  // insertion sort, descending
-      const int o = order[i];
-      const double v = A[o * ld + o];
-      int j = i - 1;
-      while (j >= 0 && A[order[j] * ld + order[j]] < v) { order[j + 1] = order[j]; --j; }
-      order[j + 1] = o;
-    }
-    for (int i = 0; i < p; ++i) vals[i] = A[order[i] * ld + order[i]];
-  }
+  double shift = 0.0;
+  for (int i = 0; i < p; ++i) shift = fmax(shift, row[i]);
+  eig_lds<PP>(p, A, order, shift, lam);
   __syncthreads();
+  for (int i = threadIdx.x; i < p; i += blockDim.x) order[rank_desc(lam, p, i)] = i;
+  __syncthreads();
+  for (int i = threadIdx.x; i < p; i += blockDim.x) vals[i] = lam[order[i]];
   double* M = small + S_M * PP * PP;
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
-    const int i = e / PP, j = e % PP;
-    M[e] = (i < p && j < p) ? V[i * ld + order[j]] : 0.0;
-  }
+  for (int i = threadIdx.x >> 6; i < PP; i += blockDim.x >> 6)
+    for (int j = threadIdx.x & 63; j < PP; j += 64) M[i * PP + j] = i < p && j < p ? A[i * LD + order[j]] : 0.0;
 }
 
 // ---------------------------------------------------------------- launchers
 
-static constexpr int RITZ_LDS = 2 * MAXP * (MAXP + 1) * (int)sizeof(double);
+static constexpr int CHOL_LDS = 2 * MAXP * MAXP * (int)sizeof(double);
+constexpr int eig_bytes(int PP) { return eig_lds_doubles(PP) * (int)sizeof(double); }
+constexpr int ritz_bytes(int PP) { return PP * (PP + 2) * (int)sizeof(double); }
 
 template <int PP>
 static hipError_t init_pp() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_eig<PP>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 3 * PP * (PP + 1) * 8);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_linesearch<PP>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 4 * PP * PP * 8);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_transform_cw<PP>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 2 * PP * PP * 8);
+  auto lds = [](auto* f, int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  };
+  hipError_t e = lds(k_eig<PP>, eig_bytes(PP));
+  if (e == hipSuccess) e = lds(k_ritz<PP>, ritz_bytes(PP));
+  if (PP > PP_LDS_MAX) return e;  // the other p x p kernels use the work area there
+  if (e == hipSuccess) e = lds(k_linesearch<PP>, 4 * PP * PP * 8);
+  if (e == hipSuccess) e = lds(k_transform_cw<PP>, 2 * PP * PP * 8);
   return e;
 }
 
 hipError_t Small::init() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_ritz), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     RITZ_LDS);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_inv), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            RITZ_LDS);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_inv),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, CHOL_LDS);
   if (e == hipSuccess) e = init_pp<16>();
   if (e == hipSuccess) e = init_pp<32>();
   if (e == hipSuccess) e = init_pp<64>();
-  // p up to 128: the Jacobi's matrix in LDS (the other p x p kernels use the work area)
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_eig<128>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            128 * 129 * 8);
+  if (e == hipSuccess) e = init_pp<128>();
   return e;
 }
 void Small::after_grad(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, double* hist, int cond) {
@@ -379,10 +368,10 @@ void Small::after_dir(hipStream_t st, int PP, const double* red, double* small, 
 }
 void Small::eig(hipStream_t st, int PP, double* small, Scalars* sc) {
   switch (PP) {
-    case 16: k_eig<16><<<1, WG, 3 * 16 * 17 * 8, st>>>(small, sc); break;
-    case 32: k_eig<32><<<1, WG, 3 * 32 * 33 * 8, st>>>(small, sc); break;
-    case 64: k_eig<64><<<1, WG, 3 * 64 * 65 * 8, st>>>(small, sc); break;
-    case 128: k_eig<128><<<1, WG, 128 * 129 * 8, st>>>(small, sc); break;
+    case 16: k_eig<16><<<1, dense_threads(16), eig_bytes(16), st>>>(small, sc); break;
+    case 32: k_eig<32><<<1, dense_threads(32), eig_bytes(32), st>>>(small, sc); break;
+    case 64: k_eig<64><<<1, dense_threads(64), eig_bytes(64), st>>>(small, sc); break;
+    case 128: k_eig<128><<<1, dense_threads(128), eig_bytes(128), st>>>(small, sc); break;
   }
 }
 void Small::linesearch(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, double* hist,
@@ -402,7 +391,7 @@ void Small::after_refresh(hipStream_t st, int PP, const double* red, double* sma
   hipLaunchKernelGGL(k_after_refresh, dim3(1), dim3(WG), 0, st, PP, red, small, sc);
 }
 void Small::chol_inv(hipStream_t st, int PP, int p, const double* red, double* small, int* flag) {
-  hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(WG), PP > PP_LDS_MAX ? 0 : RITZ_LDS, st, PP, p, red, small, flag);
+  hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(WG), PP > PP_LDS_MAX ? 0 : CHOL_LDS, st, PP, p, red, small, flag);
 }
 void Small::transform_cw(hipStream_t st, int PP, double* small, int* flag) {
   switch (PP) {
@@ -413,7 +402,12 @@ void Small::transform_cw(hipStream_t st, int PP, double* small, int* flag) {
   }
 }
 void Small::ritz(hipStream_t st, int PP, int p, const double* red, double* small, double* out_vals) {
-  hipLaunchKernelGGL(k_ritz, dim3(1), dim3(WG), PP > PP_LDS_MAX ? 0 : RITZ_LDS, st, PP, p, red, small, out_vals);
+  switch (PP) {
+    case 16: k_ritz<16><<<1, dense_threads(16), ritz_bytes(16), st>>>(p, red, small, out_vals); break;
+    case 32: k_ritz<32><<<1, dense_threads(32), ritz_bytes(32), st>>>(p, red, small, out_vals); break;
+    case 64: k_ritz<64><<<1, dense_threads(64), ritz_bytes(64), st>>>(p, red, small, out_vals); break;
+    case 128: k_ritz<128><<<1, dense_threads(128), ritz_bytes(128), st>>>(p, red, small, out_vals); break;
+  }
 }
 
 }  // namespace gsi

@@ -1,19 +1,18 @@
 // Single-workgroup float64 building blocks for the p x p projected problem, shared by the
 // per-iteration kernels (gsi_small.hip) and the batched persistent solver (gsi_batched.hip):
-// f64 MFMA products of PP x PP matrices, parallel cyclic Jacobi, and Get_Mu with Brent's
-// method on phi'.
+// f64 MFMA products of PP x PP matrices, the eigendecomposition of P^T P, and Get_Mu with
+// Brent's method on phi'.
 #pragma once
 #include <math.h>
 
+#include "gsi_dense_dev.h"
 #include "gsi_device.h"
 #include "gsi_state.h"
 
 namespace gsi {
 
-constexpr double EPS = 2.220446049250313e-16;
 constexpr int MAXP = 64;    // block width of the batched solve and of the one-wave routines below
 constexpr int TMAXP = 128;  // block width of the single-problem float64 path (two terms per lane)
-constexpr int JCODE = 256;  // pair code u * JCODE + v of the Jacobi rotations (u, v < TMAXP)
 
 // Order LDS traffic among the lanes of one wavefront (used where only wave 0 runs).
 __device__ __forceinline__ void wave_sync() {
@@ -57,333 +56,6 @@ __device__ inline void col_dots(const double* V, const double* T, double* out, d
     for (int k = 0; k < PP; ++k) s += V[k * PP + i] * T[k * PP + i];
     out[i] = sign * s;
   }
-}
-
-// ---------------------------------------------------------------- Jacobi
-
-// Parallel cyclic Jacobi (round-robin pairs) on the leading p x p block of the symmetric
-// matrix A (LDS, stride ld). On return the diagonal of A holds the eigenvalues and V
-// (LDS, stride ld) has been multiplied by all rotations. A rotation is skipped when its
-// pivot is below eps * ||A||_F or eps * sqrt(|a_uu a_vv|); the sweeps stop when a whole
-// sweep skips every rotation. Returns the number of sweeps.
-__device__ inline int jacobi(int p, int ld, double* A, double* V, double* cs /* 2*MAXP */, int* uv /* MAXP */,
-                      int* nrot_s, int* any_s) {
-  const int m = p + (p & 1);
-  const int half = m / 2;
-  __shared__ double fro;
-  if (threadIdx.x < 64) {
-    double s = 0.0;
-    for (int e = threadIdx.x; e < p * p; e += 64) {
-      const double v = A[(e / p) * ld + e % p];
-      s += v * v;
-    }
-    s = wave_sum(s);
-    if (threadIdx.x == 0) fro = sqrt(s);
-  }
-  __syncthreads();
-  const double athr = EPS * fro;
-  int sweep = 0;
-  for (; sweep < 40; ++sweep) {
-    if (threadIdx.x == 0) *any_s = 0;
-    for (int round = 0; round < m - 1; ++round) {
-      if (threadIdx.x < 64) {  // wave 0: rotation parameters, compacted to the rotating pairs
-        const int i = threadIdx.x;
-        bool rot = false;
-        double c = 1.0, s = 0.0;
-        int code = 0;
-        if (i < half) {
-          auto player = [&](int pos) { return pos == 0 ? 0 : ((pos - 1 + round) % (m - 1)) + 1; };
-          int u = player(i), v = player(m - 1 - i);
-          if (u > v) { const int t = u; u = v; v = t; }
-          if (v < p) {
-            const double auu = A[u * ld + u], avv = A[v * ld + v], auv = A[u * ld + v];
-            if (fabs(auv) > athr && fabs(auv) > EPS * sqrt(fabs(auu * avv)) && fabs(auv) > 1e-300) {
-              const double tau = (avv - auu) / (2.0 * auv);
-              const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-              c = 1.0 / sqrt(1.0 + t * t);
-              s = t * c;
-              code = u * JCODE + v;
-              rot = true;
-            }
-          }
-        }
-        const uint64_t mask = __ballot(rot);
-        if (rot) {
-          const int idx = __popcll(mask & ((1ull << i) - 1ull));
-          cs[2 * idx] = c;
-          cs[2 * idx + 1] = s;
-          uv[idx] = code;
-        }
-        if (i == 0) {
-          *nrot_s = __popcll(mask);
-          if (mask) *any_s = 1;
-        }
-      }
-      __syncthreads();
-      const int nrot = *nrot_s;
-      if (nrot == 0) continue;  // uniform: every thread read the same value after the barrier
-      // rows: A <- J^T A. Lane k of every wave takes columns k, k + 64 (p <= 128), the waves
-      // take the rotations in turn: no integer division by the runtime p
-      const int w0 = threadIdx.x >> 6, nw = blockDim.x >> 6;
-      for (int k = threadIdx.x & 63; k < p; k += 64)
-        for (int i = w0; i < nrot; i += nw) {
-          const int u = uv[i] / JCODE, v = uv[i] % JCODE;
-          const double c = cs[2 * i], s = cs[2 * i + 1];
-          const double au = A[u * ld + k], av = A[v * ld + k];
-          A[u * ld + k] = c * au - s * av;
-          A[v * ld + k] = s * au + c * av;
-        }
-      __syncthreads();
-      // columns: A <- A J, V <- V J (row k)
-      for (int k = threadIdx.x & 63; k < p; k += 64)
-        for (int i = w0; i < nrot; i += nw) {
-          const int u = uv[i] / JCODE, v = uv[i] % JCODE;
-          const double c = cs[2 * i], s = cs[2 * i + 1];
-          const double au = A[k * ld + u], av = A[k * ld + v];
-          A[k * ld + u] = c * au - s * av;
-          A[k * ld + v] = s * au + c * av;
-          const double vu = V[k * ld + u], vv = V[k * ld + v];
-          V[k * ld + u] = c * vu - s * vv;
-          V[k * ld + v] = s * vu + c * vv;
-        }
-      __syncthreads();
-    }
-    __syncthreads();
-    if (*any_s == 0) break;
-    __syncthreads();
-  }
-  __syncthreads();
-  return sweep + 1;
-}
-
-// Reciprocal, reciprocal square root and square root in float64 from the hardware
-// approximations refined by two Newton steps each (the quadratic convergence takes the
-// approximation to the last bits); for positive normal arguments.
-__device__ __forceinline__ double rcp_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(r, e, r);
-  e = fma(-x, r, 1.0);
-  return fma(r, e, r);
-}
-__device__ __forceinline__ double rsq_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  double e = fma(-x * y, y, 1.0);
-  y = fma(0.5 * y, e, y);
-  e = fma(-x * y, y, 1.0);
-  return fma(0.5 * y, e, y);
-}
-
-// Parallel cyclic Jacobi, register-resident (used by the eigendecomposition of P^T P).
-//
-// The players 0..m-1 (m = p rounded up to even; an odd p gets one zero padding row) meet in
-// the round-robin order of the cyclic-by-rows parallel ordering: in round r, position 0
-// holds player 0 and position i >= 1 player ((i - 1 + r) mod (m - 1)) + 1, and positions
-// i and m-1-i form pair i. The matrix is held in "slot" order, slot 2i for position i and
-// slot 2i+1 for position m-1-i, so that every pair is a diagonal 2 x 2 block. Thread t < R h
-// (h = m / 2 pairs, R = 256 / h) owns pair J = t mod h: the 2 x 2 blocks (I, J) for
-// I = t / h + R q in registers, and the entries of V's columns u_J, v_J (the players of
-// pair J) in rows t / h + R q, V in LDS in player order. A round: every wave's lanes 0..h-1
-// read the diagonal blocks and form the pair rotations into the wave's own LDS table; each
-// thread rotates its blocks (two-sided) and its entries of V (one-sided, in place) and writes
-// its blocks to the other LDS buffer at the slots their rows and columns move to for the
-// next round (a fixed permutation: every player moves one position, position 1 wraps to
-// m-1, position 0 stays); one barrier; each thread reads its blocks back. After m - 1 rounds
-// the slots are back in their first order. A rotation is skipped when its pivot is not
-// above eps ||A||_F and eps sqrt(|a_pp a_qq|); the sweeps stop at the start of a sweep in
-// which no rotation would be made (the whole matrix is tested before the sweep, so no
-// confirming sweep is run). Returns the number of sweeps made.
-//
-// Input: A0 (player order, stride lda, LDS, p x p). Output: eigenvalues into d[0..p),
-// V (LDS, stride LV, PP rows) multiplied by all rotations. Abuf: 2 PP^2 doubles of LDS
-// (may overlap A0: A0 is read before the first write). Whole workgroup (256 threads).
-// FULL: m = PP (p >= PP - 1) and PP >= 32: the pair count and thread layout are compile-time
-// constants and the 256 threads own exactly the (PP/2)^2 blocks and the PP rows of V, so the
-// validity tests of the general case vanish.
-template <int PP, bool FULL>
-__device__ inline int jacobi_regs(int p, const double* A0, int lda, double* Abuf, double* V, int LV, double* d) {
-  constexpr int NBQ = PP * PP / 1024 > 0 ? PP * PP / 1024 : 1;  // blocks per thread
-  constexpr int NVQ = PP * PP / 512 > 0 ? PP * PP / 512 : 1;    // rows of V per thread
-  constexpr int H = PP / 2;
-  static_assert(!FULL || (H * H == WG * NBQ && PP * H == WG * NVQ), "FULL layout needs PP >= 32");
-  struct alignas(16) Rot { double c, s, t, app, aqq; int u, v; };
-  __shared__ Rot rtab[WG / 64][H];
-  __shared__ double fro_part[WG / 64];
-  const int m = FULL ? PP : p + (p & 1), h = FULL ? H : m / 2, R = WG / h;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const bool owner = FULL || tid < R * h;
-  const int J = owner ? tid % h : 0, I0 = owner ? tid / h : 0;
-  auto pos_of_slot = [&](int s) { return (s & 1) ? m - 1 - (s >> 1) : (s >> 1); };
-  auto slot_of_pos = [&](int q) { return q < h ? 2 * q : 2 * (m - 1 - q) + 1; };
-  // slot a row/column moves to for the next round
-  auto next_slot = [&](int s) {
-    const int q = pos_of_slot(s);
-    return slot_of_pos(q == 0 ? 0 : (q == 1 ? m - 1 : q - 1));
-  };
-  auto addr = [&](int i, int j) { return ((i >> 1) * h + (j >> 1)) * 4 + (i & 1) * 2 + (j & 1); };
-  double B[NBQ][4];
-  int bI[NBQ], dst[NBQ][4];
-  double fro2 = 0.0;
-#pragma unroll
-  for (int q = 0; q < NBQ; ++q) {
-    const int I = I0 + R * q;
-    bI[q] = (FULL || (owner && I < h)) ? I : -1;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      B[q][e] = 0.0;
-      dst[q][e] = 0;
-    }
-    if (bI[q] >= 0) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int si = 2 * I + (e >> 1), sj = 2 * J + (e & 1);
-        const int xi = pos_of_slot(si), xj = pos_of_slot(sj);  // round 0: player x sits at position x
-        const double v = (xi < p && xj < p) ? A0[xi * lda + xj] : 0.0;
-        B[q][e] = v;
-        fro2 += v * v;
-        dst[q][e] = addr(next_slot(si), next_slot(sj));
-      }
-    }
-  }
-  int vr[NVQ];
-#pragma unroll
-  for (int q = 0; q < NVQ; ++q) {
-    const int r = I0 + R * q;
-    vr[q] = (FULL || (owner && r < m)) ? r : -1;
-  }
-  fro2 = wave_sum(fro2);
-  if (lane == 0) fro_part[w] = fro2;
-  __syncthreads();  // also: every read of A0 is done before Abuf (which may overlap it) is written
-  double fsum = 0.0;
-  for (int k = 0; k < WG / 64; ++k) fsum += fro_part[k];
-  const double athr2 = EPS * EPS * fsum;  // (eps ||A||_F)^2
-  int cur = 0;
-#pragma unroll
-  for (int q = 0; q < NBQ; ++q)
-    if (FULL || bI[q] >= 0)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) Abuf[addr(2 * bI[q] + (e >> 1), 2 * J + (e & 1))] = B[q][e];
-  __syncthreads();
-  // pair k = lane of every wave (k < h): its players u (position k), v (position m-1-k)
-  int pu = lane, pv = m - 1 - lane;
-  Rot* tab = rtab[w];
-  int sweep = 0;
-  for (; sweep < 40; ++sweep) {
-    bool stop = false;
-    for (int round = 0; round < m - 1; ++round) {
-      const double* Ac = Abuf + cur * PP * PP;
-      double* An = Abuf + (cur ^ 1) * PP * PP;
-      if (lane < h) {
-        const double* blk = Ac + (lane * h + lane) * 4;
-        const double app = blk[0], apq = blk[1], aqq = blk[3];
-        const double apq2 = apq * apq;
-        double c = 1.0, s = 0.0, t = 0.0;
-        if (apq2 > athr2 && apq2 > EPS * EPS * fabs(app * aqq) && fabs(apq) > 1e-300) {
-          // t = tan of the angle that zeroes a_pq: sgn(tau) / (|tau| + sqrt(1 + tau^2)),
-          // tau = (a_qq - a_pp) / (2 a_pq); |tau| <= 1/eps here, so 1 + tau^2 cannot overflow
-          const double tau = (aqq - app) * rcp_nr(2.0 * apq);
-          const double q1 = 1.0 + tau * tau;
-          const double root = q1 * rsq_nr(q1);
-          const double ta = rcp_nr(fabs(tau) + root);
-          t = tau >= 0.0 ? ta : -ta;
-          c = rsq_nr(1.0 + t * t);
-          s = t * c;
-        }
-        Rot rr;
-        rr.c = c; rr.s = s; rr.t = t; rr.app = app; rr.aqq = aqq; rr.u = pu; rr.v = pv;
-        tab[lane] = rr;
-      }
-      wave_sync();
-      if (round == 0) {
-        // would this sweep rotate anything? (the whole matrix against the skip rule)
-        int big = 0;
-        const double dJ0 = tab[J].app, dJ1 = tab[J].aqq;
-#pragma unroll
-        for (int q = 0; q < NBQ; ++q) {
-          if (!FULL && bI[q] < 0) continue;
-          const double dI0 = tab[bI[q]].app, dI1 = tab[bI[q]].aqq;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int a = e >> 1, c = e & 1;
-            if (bI[q] == J && a == c) continue;
-            const double x2 = B[q][e] * B[q][e];
-            const double di = a ? dI1 : dI0, dj = c ? dJ1 : dJ0;
-            if (x2 > athr2 && x2 > EPS * EPS * fabs(di * dj) && fabs(B[q][e]) > 1e-300) big = 1;
-          }
-        }
-        if (!__syncthreads_or(big)) {
-          stop = true;
-          break;
-        }
-      }
-      if (owner) {
-        const Rot rJ = tab[J];
-        // blocks: B <- R_I^T B R_J; the diagonal block gets the rotated diagonal and an
-        // exact zero off the diagonal
-#pragma unroll
-        for (int q = 0; q < NBQ; ++q) {
-          if (!FULL && bI[q] < 0) continue;
-          const double cI = tab[bI[q]].c, sI = tab[bI[q]].s;
-          double* x = B[q];
-          const double r0 = cI * x[0] - sI * x[2], r1 = cI * x[1] - sI * x[3];
-          const double r2 = sI * x[0] + cI * x[2], r3 = sI * x[1] + cI * x[3];
-          double y0 = rJ.c * r0 - rJ.s * r1, y1 = rJ.s * r0 + rJ.c * r1;
-          double y2 = rJ.c * r2 - rJ.s * r3, y3 = rJ.s * r2 + rJ.c * r3;
-          const bool dg = bI[q] == J && rJ.s != 0.0;
-          const double off = x[1];
-          x[0] = dg ? x[0] - rJ.t * off : y0;
-          x[3] = dg ? x[3] + rJ.t * off : y3;
-          x[1] = dg ? 0.0 : y1;
-          x[2] = dg ? 0.0 : y2;
-        }
-        // V <- V R_J on the columns of pair J's players, in place
-        if (rJ.s != 0.0) {
-          double xu[NVQ], xv[NVQ];
-#pragma unroll
-          for (int q = 0; q < NVQ; ++q) {
-            xu[q] = 0.0;
-            xv[q] = 0.0;
-            if (FULL || vr[q] >= 0) {
-              xu[q] = V[vr[q] * LV + rJ.u];
-              xv[q] = V[vr[q] * LV + rJ.v];
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < NVQ; ++q)
-            if (FULL || vr[q] >= 0) {
-              V[vr[q] * LV + rJ.u] = rJ.c * xu[q] - rJ.s * xv[q];
-              V[vr[q] * LV + rJ.v] = rJ.s * xu[q] + rJ.c * xv[q];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NBQ; ++q)
-          if (FULL || bI[q] >= 0)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) An[dst[q][e]] = B[q][e];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < NBQ; ++q)
-        if (FULL || bI[q] >= 0) {
-          const double* blk = An + (bI[q] * h + J) * 4;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) B[q][e] = blk[e];
-        }
-      cur ^= 1;
-      // next round: every player except player 0 moves on (m - 1 wraps to 1)
-      if (lane != 0) pu = pu == m - 1 ? 1 : pu + 1;
-      pv = pv == m - 1 ? 1 : pv + 1;
-    }
-    if (stop) break;
-  }
-  // eigenvalue of player x: the diagonal entry at its slot (the slots are in their first order)
-  const double* Ac = Abuf + cur * PP * PP;
-  for (int x = tid; x < p; x += WG) {
-    const int sx = slot_of_pos(x);
-    d[x] = Ac[addr(sx, sx)];
-  }
-  __syncthreads();
-  return sweep;
 }
 
 // ---------------------------------------------------------------- line search (wave 0)
@@ -536,89 +208,83 @@ __device__ inline double get_mu(Terms& T, int p, int preal, int* evals) {
 // ---------------------------------------------------------------- eigendecomposition of P^T P
 
 // P^T P = V diag(b) V^T (Sec. 5.2) for S = small[S_S]: writes V (small[S_V]) and b
-// (small[S_VEC ...]); returns the Jacobi sweep count. Warm start (warm = true): the previous
-// V, made orthonormal again by one Newton-Schulz step V <- V (3 I - V^T V) / 2, turns S
-// into a nearly diagonal V^T S V when the directions change little from step to step.
-// lds: 3 PP (PP + 1) doubles: V with the odd stride PP + 1 (the in-place column updates of
-// the rotations are then free of bank conflicts) and the two block buffers of jacobi_regs,
-// which also hold the temporaries of the products (stride PP). Whole workgroup. The
-// arguments cs, uv, nrot, anyr are unused (kept for the callers' shared-memory layout).
+// (small[S_VEC ...]); returns the sweep count. Warm start (warm = true): the previous V, made
+// orthonormal again by one Newton-Schulz step V <- V (3 I - V^T V) / 2, turns S into a nearly
+// diagonal V^T S V when the directions change little from step to step.
+// lds: eig_lds_doubles(PP) doubles; above PP = 64 only the matrix that is decomposed fits
+// there, and V and the products' temporaries sit in the work area of the small buffer. Whole
+// workgroup of dense_threads(PP).
+constexpr int eig_lds_doubles(int PP) { return (PP > PP_LDS_MAX ? 1 : 3) * PP * (PP + 2); }
+
 template <int PP>
-__device__ inline int eig_dev(double* small, int p, bool warm, double* lds, double* cs, int* uv, int* nrot,
-                              int* anyr) {
-  if constexpr (PP > PP_LDS_MAX) {
-    // p up to 128: the parallel cyclic Jacobi (jacobi) with A = V^T S V in LDS (PP x (PP + 1),
-    // 132 KB) and the eigenvectors and the products' temporaries in the work area of the small
-    // buffer
-    constexpr int LD = PP + 1;
-    double* A = lds;
-    double* work = small + small_work_offset(PP);
-    double* Vw = work;                 // PP x LD
-    double* T0 = work + PP * LD;       // PP x PP
-    double* T1 = work + 2 * PP * LD;   // PP x PP
-    const double* S = small + S_S * PP * PP;
-    double* Vg = small + S_V * PP * PP;
-    if (warm) {
-      wg_mm<PP>(Vg, true, Vg, false, T0);  // T0 = V^T V
-      __syncthreads();
-      for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) T0[e] = 0.5 * (((e / PP) == (e % PP) ? 3.0 : 0.0) - T0[e]);
-      __syncthreads();
-      wg_mm<PP>(Vg, false, T0, false, T1);  // T1 = V (3I - V^T V) / 2
-    } else {
-      for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) T1[e] = (e / PP) == (e % PP) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    wg_mm<PP>(S, false, T1, false, T0);  // T0 = S V
-    __syncthreads();
-    wg_mm<PP>(T1, true, T0, false, Vw);  // V^T S V (Vw as a stride-PP temporary)
-    __syncthreads();
-    // symmetric to the last bit before the rotations (they read both triangles)
-    for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
-      const int i = e / PP, j = e % PP;
-      A[i * LD + j] = 0.5 * (Vw[i * PP + j] + Vw[j * PP + i]);
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) Vw[(e / PP) * LD + e % PP] = T1[e];
-    __syncthreads();
-    const int sweeps = jacobi(p, LD, A, Vw, cs, uv, nrot, anyr);
-    double* b = small + S_VEC * PP * PP;
-    for (int i = threadIdx.x; i < PP; i += blockDim.x) b[i] = i < p ? fmax(A[i * LD + i], 0.0) : 0.0;
-    for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) Vg[e] = Vw[(e / PP) * LD + e % PP];
-    __syncthreads();
-    return sweeps;
-  } else {
-  constexpr int LV = PP + 1;
-  double* Vv = lds;             // PP x LV
-  double* Ab = lds + PP * LV;   // 2 PP^2: jacobi_regs buffers
-  double* T0 = Ab;              // temporaries, stride PP
-  double* V1 = Ab + PP * PP;
+__device__ inline int eig_dev(double* small, int p, bool warm, double* lds) {
+  constexpr int LD = DLD<PP>;
+  constexpr bool wide = PP > PP_LDS_MAX;
+  __shared__ double key[PP];
+  __shared__ int ord[PP];
+  const int nb = (p + 15) >> 4, m = 16 * nb;
+  double* A = lds;
+  double* V1 = wide ? small + small_work_offset(PP) : lds + PP * LD;
+  double* T = V1 + PP * LD;
   const double* S = small + S_S * PP * PP;
   double* Vg = small + S_V * PP * PP;
+  double* b = small + S_VEC * PP * PP;
+  // the leading m x m block of f(i, j), 64 columns to a wave
+  auto fill = [&](double* dst, int ld, auto f) {
+    for (int i = threadIdx.x >> 6; i < m; i += blockDim.x >> 6)
+      for (int j = threadIdx.x & 63; j < m; j += 64) dst[i * ld + j] = f(i, j);
+  };
   if (warm) {
-    wg_mm<PP>(Vg, true, Vg, false, T0);  // T0 = V^T V
+    const double* V0 = Vg;
+    int ldv = PP;
+    if constexpr (!wide) {
+      fill(T, LD, [&](int i, int j) { return Vg[i * PP + j]; });
+      V0 = T;
+      ldv = LD;
+      __syncthreads();
+    }
+    mm_lds(nb, V0, ldv, true, V0, ldv, false, A, LD);
     __syncthreads();
-    for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) T0[e] = 0.5 * (((e / PP) == (e % PP) ? 3.0 : 0.0) - T0[e]);
+    fill(A, LD, [&](int i, int j) { return 0.5 * ((i == j ? 3.0 : 0.0) - A[i * LD + j]); });
     __syncthreads();
-    wg_mm<PP>(Vg, false, T0, false, V1);  // V1 = V (3I - V^T V) / 2
+    mm_lds(nb, V0, ldv, false, A, LD, false, V1, LD);
+    __syncthreads();
+    if constexpr (wide) {
+      mm_lds(nb, S, PP, false, V1, LD, false, T, LD);
+      __syncthreads();
+      mm_lds(nb, V1, LD, true, T, LD, false, A, LD);
+    } else {
+      fill(T, LD, [&](int i, int j) { return S[i * PP + j]; });
+      __syncthreads();
+      mm_lds(nb, T, LD, false, V1, LD, false, A, LD);
+      __syncthreads();
+      mm_lds(nb, V1, LD, true, A, LD, false, T, LD);
+    }
+    __syncthreads();
+    // symmetric to the last bit, sorted by the diagonal
+    if constexpr (wide) {
+      diag_order(p, ord, key, [&](int i) { return A[i * LD + i]; });
+      fill(T, LD, [&](int i, int j) { return 0.5 * (A[ord[i] * LD + ord[j]] + A[ord[j] * LD + ord[i]]); });
+      __syncthreads();
+      fill(A, LD, [&](int i, int j) { return T[i * LD + j]; });
+    } else {
+      diag_order(p, ord, key, [&](int i) { return T[i * LD + i]; });
+      fill(A, LD, [&](int i, int j) { return 0.5 * (T[ord[i] * LD + ord[j]] + T[ord[j] * LD + ord[i]]); });
+    }
   } else {
-    for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) V1[e] = (e / PP) == (e % PP) ? 1.0 : 0.0;
+    diag_order(p, ord, key, [&](int i) { return S[i * PP + i]; });
+    fill(A, LD, [&](int i, int j) { return S[ord[i] * PP + ord[j]]; });
   }
   __syncthreads();
-  wg_mm<PP>(S, false, V1, false, Vv);  // Vv (as a stride-PP temporary) = S V
+  const int sweeps = eig_lds<PP>(p, A, ord, 0.0, b);
   __syncthreads();
-  wg_mm<PP>(V1, true, Vv, false, T0);  // T0 = V^T S V
-  __syncthreads();
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) Vv[(e / PP) * LV + e % PP] = V1[e];
-  __syncthreads();
-  double* b = small + S_VEC * PP * PP;
-  // the compile-time layout needs every thread to own blocks: PP >= 32 (H^2 = 256 NBQ)
-  const int sweeps = (PP >= 32 && p >= PP - 1) ? jacobi_regs<PP, PP >= 32>(p, T0, PP, Ab, Vv, LV, b)
-                                               : jacobi_regs<PP, false>(p, T0, PP, Ab, Vv, LV, b);
+  if (warm)
+    mm_lds(nb, V1, LD, false, A, LD, false, Vg, PP);
+  else
+    fill(Vg, PP, [&](int i, int j) { return A[i * LD + j]; });
   for (int i = threadIdx.x; i < PP; i += blockDim.x) b[i] = i < p ? fmax(b[i], 0.0) : 0.0;
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) Vg[e] = Vv[(e / PP) * LV + e % PP];
   __syncthreads();
   return sweeps;
-  }
 }
 
 // ---------------------------------------------------------------- line search and retraction factor
