@@ -488,47 +488,26 @@ __device__ void b_reduce3(double& a, double& b, double& m, double* red /* 12 */)
 }
 
 // Cholesky of sym(G) (p x p block of a PP x PP matrix), M = L^{-T} into Mout (PP x PP,
-// padding zero). Returns false on a non-positive or tiny pivot. lds: 2 PP^2 doubles.
+// padding zero). Returns false on a non-positive or tiny pivot. lds: 2 PP (PP + 2) doubles.
 template <int PP>
 __device__ __noinline__ bool b_chol_inv(const double* G, double* Mout, int p, double* lds, int* bad) {
-  double* L = lds;
-  double* Li = lds + PP * PP;
-  for (int e = threadIdx.x; e < p * p; e += blockDim.x) {
-    const int i = e / p, j = e % p;
-    L[e] = 0.5 * (G[i * PP + j] + G[j * PP + i]);
+  constexpr int LD = DLD<PP>;
+  double* A = to_lds(lds);
+  double* Mb = A + PP * LD;
+  const int m = 16 * ((p + 15) >> 4);
+  double dmax = 0.0;
+  for (int i = 0; i < p; ++i) dmax = fmax(dmax, gld(G + i * PP + i));
+  for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
+    const int i = e / m, j = e % m;
+    A[i * LD + j] = i < p && j < p ? 0.5 * (gld(G + i * PP + j) + gld(G + j * PP + i)) : 0.0;
   }
   if (threadIdx.x == 0) *bad = 0;
   __syncthreads();
-  double dmax = 0.0;
-  for (int i = 0; i < p; ++i) dmax = fmax(dmax, L[i * p + i]);
-  for (int j = 0; j < p; ++j) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const double piv = L[j * p + j];
-      if (!(piv > 1e-13 * dmax) || !isfinite(piv)) *bad = 1;
-      L[j * p + j] = sqrt(fabs(piv) > 0.0 ? fabs(piv) : 1.0);
-    }
-    __syncthreads();
-    const double ljj = L[j * p + j];
-    for (int i = j + 1 + threadIdx.x; i < p; i += blockDim.x) L[i * p + j] /= ljj;
-    __syncthreads();
-    for (int e = threadIdx.x; e < (p - j - 1) * (p - j - 1); e += blockDim.x) {
-      const int i = j + 1 + e / (p - j - 1), k = j + 1 + e % (p - j - 1);
-      if (k <= i) L[i * p + k] -= L[i * p + j] * L[k * p + j];
-    }
-  }
-  __syncthreads();
-  for (int c = threadIdx.x; c < p; c += blockDim.x) {
-    for (int i = 0; i < p; ++i) {
-      double s = (i == c) ? 1.0 : 0.0;
-      for (int k = c; k < i; ++k) s -= L[i * p + k] * Li[k * p + c];
-      Li[i * p + c] = i < c ? 0.0 : s / L[i * p + i];
-    }
-  }
-  __syncthreads();
+  if (chol_lds<PP, false>(p, A, 1e-13 * dmax) && threadIdx.x == 0) *bad = 1;
+  inv_chol<PP>(p, A, Mb, LD);
   for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
     const int i = e / PP, j = e % PP;
-    Mout[e] = (i < p && j < p) ? Li[j * p + i] : 0.0;
+    gst(Mout + e, i < p && j < p ? Mb[i * LD + j] : 0.0);
   }
   __syncthreads();
   return *bad == 0;

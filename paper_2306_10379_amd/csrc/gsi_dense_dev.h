@@ -81,8 +81,9 @@ __device__ __forceinline__ double readlane_d(double v, int lane) {
 
 // Lower Cholesky factor in place of the leading p x p block of A (LDS, stride DLD<PP>, both
 // triangles given, rows and columns p .. 16 ceil(p/16) zero). What is left above the diagonal
-// is not part of it. A pivot not above `floor` (or NaN) is replaced by it (FIX), or reported:
-// returns true in wave 0 when there was one (the factor is then of no use).
+// is not part of it. A pivot not above `floor` (or NaN) is replaced by it (FIX), or reported, as
+// is one that is not finite: returns true in wave 0 when there was one (the factor is then of
+// no use).
 //
 // 16 columns at a time: wave 0 factors the panel with a row per lane (two at PP = 128), the
 // pivots and multipliers broadcast by v_readlane, with no barrier or LDS traffic inside the
@@ -115,7 +116,7 @@ __device__ __forceinline__ bool chol_lds(int p, double* A, double floor) {
             piv = fmax(piv, floor);
             a[h][j] = l == l0 + j ? piv : a[h][j];
           } else {
-            bad |= c0 + j < p && !(piv > floor);
+            bad |= c0 + j < p && !(piv > floor && piv < INFINITY);
           }
           // a zero matrix, and the padding columns of the last panel: zero factor
           const double rs = piv > 0.0 ? rsq_nr(piv) : 0.0;
@@ -160,6 +161,54 @@ __device__ __forceinline__ bool chol_lds(int p, double* A, double floor) {
     __syncthreads();
   }
   return bad;
+}
+
+// M = L^{-T} (upper triangular, all of its leading 16 ceil(p/16) square written, padding zero)
+// for the factor L that chol_lds left in A; M: stride ldm, LDS or global. Whole workgroup,
+// barriers inside; the caller puts one after.
+//
+// X = L^{-1} by block rows, M[j][i] = X[i][j]: 16 lanes invert each diagonal block, a column
+// each; block row i is then -X_ii sum_k L_ik X_kj on MFMA, whose inner sum leaves the matrix
+// unit in the layout that the product with X_ii takes it in.
+template <int PP>
+__device__ __forceinline__ void inv_chol(int p, const double* A, double* M, int ldm) {
+  constexpr int LD = DLD<PP>;
+  const int nb = (p + 15) >> 4, nw = blockDim.x >> 6, w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int g = l >> 4, c = l & 15;
+  if (const int kb = threadIdx.x >> 4; kb < nb) {
+    const int d = 16 * kb;
+    double x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      double s = i == c ? 1.0 : 0.0;
+#pragma unroll
+      for (int k = 0; k < i; ++k) s = fma(-A[(d + i) * LD + d + k], x[k], s);
+      x[i] = d + i < p ? s / A[(d + i) * LD + d + i] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) M[(d + c) * ldm + d + i] = x[i];
+  }
+  for (int t = w; t < nb * nb; t += nw) {  // zero below the diagonal
+    const int ib = t / nb, jb = t - ib * nb;
+    if (ib > jb)
+      for (int r = g; r < 16; r += 4) M[(16 * ib + r) * ldm + 16 * jb + c] = 0.0;
+  }
+  __syncthreads();
+  for (int i = 1; i < nb; ++i) {
+    for (int j = w; j < i; j += nw) {
+      d4 t = {0.0, 0.0, 0.0, 0.0};
+      for (int k = j; k < i; ++k)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          t = mfma(A[(16 * i + c) * LD + 16 * k + 4 * s + g], M[(16 * j + c) * ldm + 16 * k + 4 * s + g], t);
+      d4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) x = mfma(M[(16 * i + 4 * s + g) * ldm + 16 * i + c], t[s], x);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) M[(16 * j + c) * ldm + 16 * i + g + 4 * r] = -x[r];
+    }
+    __syncthreads();
+  }
 }
 
 // ---------------------------------------------------------------- eigensolver

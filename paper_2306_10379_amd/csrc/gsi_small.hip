@@ -211,57 +211,27 @@ __global__ __launch_bounds__(WG) void k_after_refresh(int PP, const double* __re
 
 // Cholesky G = L L^T of the leading p x p block of red, then M = L^{-T} (so X M has
 // orthonormal columns when G = X^T X). flag = 1 on a non-positive or tiny pivot.
-__global__ __launch_bounds__(WG) void k_chol_inv(int PP, int p, const double* __restrict__ red,
-                                                 double* __restrict__ small, int* __restrict__ flag) {
+template <int PP>
+__global__ __launch_bounds__(dense_threads(PP)) void k_chol_inv(int p, const double* __restrict__ red,
+                                                                double* __restrict__ small, int* __restrict__ flag) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  // p up to 64 in LDS; above, in the work area of the small buffer
-  const bool wide = PP > PP_LDS_MAX;
-  double* L = wide ? small + small_work_offset(PP) + 4 * PP * (PP + 1) : reinterpret_cast<double*>(lds_raw);
-  double* Li = L + (wide ? PP * PP : MAXP * MAXP);
-  __shared__ int bad;
-  __shared__ double dmax;
-  for (int e = threadIdx.x; e < p * p; e += blockDim.x) {
-    const int i = e / p, j = e % p;
-    L[e] = 0.5 * (red[i * PP + j] + red[j * PP + i]);
-  }
-  if (threadIdx.x == 0) {
-    bad = 0;
-    double m = 0.0;
-    for (int i = 0; i < p; ++i) m = fmax(m, red[i * PP + i]);
-    dmax = m;
-  }
+  constexpr int LD = DLD<PP>;
+  constexpr bool wide = PP > PP_LDS_MAX;  // L alone fits LDS then
+  double* A = reinterpret_cast<double*>(lds_raw);
+  double* Mb = wide ? small + small_work_offset(PP) + 4 * PP * (PP + 1) : A + PP * LD;
+  const int m = 16 * ((p + 15) >> 4), l = threadIdx.x & 63;
+  double dmax = 0.0;
+  for (int i = l; i < p; i += 64) dmax = fmax(dmax, red[i * PP + i]);
+  dmax = wave_max(dmax);
+  for (int i = threadIdx.x >> 6; i < m; i += blockDim.x >> 6)
+    for (int j = l; j < m; j += 64)
+      A[i * LD + j] = i < p && j < p ? 0.5 * (red[i * PP + j] + red[j * PP + i]) : 0.0;
   __syncthreads();
-  for (int j = 0; j < p; ++j) {
-    if (threadIdx.x == 0) {
-      const double piv = L[j * p + j];
-      if (!(piv > 1e-13 * dmax) || !isfinite(piv)) bad = 1;
-      L[j * p + j] = sqrt(fabs(piv) > 0.0 ? fabs(piv) : 1.0);
-    }
-    __syncthreads();
-    const double ljj = L[j * p + j];
-    for (int i = j + 1 + threadIdx.x; i < p; i += blockDim.x) L[i * p + j] /= ljj;
-    __syncthreads();
-    for (int e = threadIdx.x; e < (p - j - 1) * (p - j - 1); e += blockDim.x) {
-      const int i = j + 1 + e / (p - j - 1), k = j + 1 + e % (p - j - 1);
-      if (k <= i) L[i * p + k] -= L[i * p + j] * L[k * p + j];
-    }
-    __syncthreads();
-  }
-  // Li = L^{-1} (lower), one column per thread
-  for (int c = threadIdx.x; c < p; c += blockDim.x) {
-    for (int i = 0; i < p; ++i) {
-      double s = (i == c) ? 1.0 : 0.0;
-      for (int k = c; k < i; ++k) s -= L[i * p + k] * Li[k * p + c];
-      Li[i * p + c] = i < c ? 0.0 : s / L[i * p + i];
-    }
-  }
-  __syncthreads();
+  if (chol_lds<PP, false>(p, A, 1e-13 * dmax) && threadIdx.x == 0) *flag = 1;
+  inv_chol<PP>(p, A, Mb, LD);
   double* M = small + S_M * PP * PP;
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
-    const int i = e / PP, j = e % PP;
-    M[e] = (i < p && j < p) ? Li[j * p + i] : 0.0;  // M = L^{-T}
-  }
-  if (threadIdx.x == 0 && bad) *flag = 1;
+  for (int i = threadIdx.x >> 6; i < PP; i += blockDim.x >> 6)
+    for (int j = l; j < PP; j += 64) M[i * PP + j] = i < p && j < p ? Mb[i * LD + j] : 0.0;
 }
 
 // After a Cholesky QR pass X <- X M (M = R^{-1} in small[S_M]): C <- M^T C M, W <- M^T W.
@@ -334,9 +304,9 @@ __global__ __launch_bounds__(dense_threads(PP)) void k_ritz(int p, const double*
 
 // ---------------------------------------------------------------- launchers
 
-static constexpr int CHOL_LDS = 2 * MAXP * MAXP * (int)sizeof(double);
 constexpr int eig_bytes(int PP) { return eig_lds_doubles(PP) * (int)sizeof(double); }
 constexpr int ritz_bytes(int PP) { return PP * (PP + 2) * (int)sizeof(double); }
+constexpr int chol_bytes(int PP) { return (PP > PP_LDS_MAX ? 1 : 2) * PP * (PP + 2) * (int)sizeof(double); }
 
 template <int PP>
 static hipError_t init_pp() {
@@ -345,6 +315,7 @@ static hipError_t init_pp() {
   };
   hipError_t e = lds(k_eig<PP>, eig_bytes(PP));
   if (e == hipSuccess) e = lds(k_ritz<PP>, ritz_bytes(PP));
+  if (e == hipSuccess) e = lds(k_chol_inv<PP>, chol_bytes(PP));
   if (PP > PP_LDS_MAX) return e;  // the other p x p kernels use the work area there
   if (e == hipSuccess) e = lds(k_linesearch<PP>, 4 * PP * PP * 8);
   if (e == hipSuccess) e = lds(k_transform_cw<PP>, 2 * PP * PP * 8);
@@ -352,9 +323,7 @@ static hipError_t init_pp() {
 }
 
 hipError_t Small::init() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_chol_inv),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, CHOL_LDS);
-  if (e == hipSuccess) e = init_pp<16>();
+  hipError_t e = init_pp<16>();
   if (e == hipSuccess) e = init_pp<32>();
   if (e == hipSuccess) e = init_pp<64>();
   if (e == hipSuccess) e = init_pp<128>();
@@ -391,7 +360,12 @@ void Small::after_refresh(hipStream_t st, int PP, const double* red, double* sma
   hipLaunchKernelGGL(k_after_refresh, dim3(1), dim3(WG), 0, st, PP, red, small, sc);
 }
 void Small::chol_inv(hipStream_t st, int PP, int p, const double* red, double* small, int* flag) {
-  hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(WG), PP > PP_LDS_MAX ? 0 : CHOL_LDS, st, PP, p, red, small, flag);
+  switch (PP) {
+    case 16: k_chol_inv<16><<<1, dense_threads(16), chol_bytes(16), st>>>(p, red, small, flag); break;
+    case 32: k_chol_inv<32><<<1, dense_threads(32), chol_bytes(32), st>>>(p, red, small, flag); break;
+    case 64: k_chol_inv<64><<<1, dense_threads(64), chol_bytes(64), st>>>(p, red, small, flag); break;
+    case 128: k_chol_inv<128><<<1, dense_threads(128), chol_bytes(128), st>>>(p, red, small, flag); break;
+  }
 }
 void Small::transform_cw(hipStream_t st, int PP, double* small, int* flag) {
   switch (PP) {

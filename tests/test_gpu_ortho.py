@@ -65,3 +65,23 @@ def test_orthonormalize_repeats_bit_for_bit_and_reports_breakdown():
         gsi.orthonormalize(torch.zeros((100, 65), dtype=torch.float64, device="cuda"))
     with pytest.raises(gsi.GsiError):
         gsi.orthonormalize(torch.zeros((10, 11), dtype=torch.float64, device="cuda"))
+
+
+@pytest.mark.parametrize("p", [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64])
+@pytest.mark.parametrize("n", ["p", 127, 129, 40000, 262147])
+def test_orthonormalize_at_tile_edges(n, p):
+    """Column blocks of 16 and row tiles of 16 (U of them a wave), from fewer rows than one
+    workgroup takes to several groups of tiles per wave, columns scaled over three decades."""
+    gsi = _gsi()
+    n = max(p, n) if n != "p" else p
+    X = _block(n, p, 1000 + n + p, 1e2 if n == p else 1.0) * np.geomspace(1.0, 1e-3, p)
+    print(f"orthonormalize n={n} p={p}", flush=True)
+    Xd = torch.as_tensor(X, device="cuda").contiguous()
+    assert gsi.orthonormalize(Xd) == gsi.GSI_OK
+    Q = Xd.cpu().numpy()
+    assert np.max(np.abs(Q.T @ Q - np.eye(p))) <= 1e-13
+    # X = Q R with R upper triangular, positive diagonal: backward error of the two products
+    R = Q.T @ X
+    assert np.max(np.abs(np.tril(R, -1)) / np.linalg.norm(X, axis=0)) <= 1e-12
+    assert np.all(np.diag(R) > 0)
+    assert np.max(np.abs(X - Q @ R) / np.linalg.norm(X, axis=0)) <= 1e-12
