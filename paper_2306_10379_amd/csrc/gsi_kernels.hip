@@ -1494,6 +1494,86 @@ __global__ __launch_bounds__(WG) void k_gram(int64_t n, const T* __restrict__ A0
   }
 }
 
+// A^T B1 and (TWO) A^T B2 at PP = 16 and 32. Every wave forms all blocks of both Grams over its
+// own rows (16 of the tile's 64), so each row of A, B1 and B2 is read once per workgroup;
+// dealing the blocks to the waves, as k_gram does, read every operand in up to four waves and
+// left half of them idle with one Gram of two units (249 -> 42 us for X^T X at n = 884,640,
+// PP = 32, 0.23 GB: 5.4 TB/s). Lane (g, c) holds columns V c .. V c + V - 1 of row 4 s + g (one
+// 8- or 16-byte load): entry (V i + ib, V j + jb) of a Gram is entry (i, j) of its block
+// (ib, jb). U tiles' loads are in flight together. The waves' sums are added in wave order.
+// A == B1 (SAME): its rows are loaded once.
+template <typename T, int PP, bool TWO, bool SAME>
+__global__ __launch_bounds__(WG) void k_gram_rows(int64_t n, const T* __restrict__ A0, const T* __restrict__ A1,
+                                                  const T* __restrict__ B1, const T* __restrict__ B2,
+                                                  const Scalars* __restrict__ sc, int mode,
+                                                  double* __restrict__ partials) {
+  if (spmm_skip(sc, mode)) return;
+  constexpr int V = PP / 16, NG = TWO ? 2 : 1, U = PP == 16 ? 4 : 2;
+  typedef T TV __attribute__((ext_vector_type(V)));
+  const T* A = (mode == 1 && (sc->k & 1)) ? A1 : A0;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
+  typename Vec4<T>::type acc[NG][V][V];
+#pragma unroll
+  for (int q = 0; q < NG; ++q)
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+#pragma unroll
+      for (int j = 0; j < V; ++j) acc[q][i][j] = typename Vec4<T>::type{0, 0, 0, 0};
+  const int64_t ntiles = (n + TR - 1) / TR;
+  int64_t t0, t1;
+  tile_range(ntiles, t0, t1);
+  // rows past n of the last tile are the blocks' zero padding
+  auto row = [&](const T* B, int64_t t, int s) {
+    const T* q = B + (t * TR + 16 * w + 4 * s + g) * PP + V * c;
+    if constexpr (V == 1) return TV{gld(q)};
+    else return gld(reinterpret_cast<const TV*>(q));
+  };
+  auto form = [&](int64_t t, auto UU) {
+    constexpr int u = decltype(UU)::value;
+    TV a[u][4], b[u][4], y[u][4];
+#pragma unroll
+    for (int k = 0; k < u; ++k)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        a[k][s] = row(A, t + k, s);
+        if constexpr (!SAME) b[k][s] = row(B1, t + k, s);
+        if constexpr (TWO) y[k][s] = row(B2, t + k, s);
+      }
+#pragma unroll
+    for (int k = 0; k < u; ++k)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+#pragma unroll
+          for (int j = 0; j < V; ++j) {
+            acc[0][i][j] = mfma(a[k][s][i], SAME ? a[k][s][j] : b[k][s][j], acc[0][i][j]);
+            if constexpr (TWO) acc[1][i][j] = mfma(a[k][s][i], y[k][s][j], acc[1][i][j]);
+          }
+  };
+  int64_t t = t0;
+  for (; t + U <= t1; t += U) form(t, std::integral_constant<int, U>());
+  for (; t < t1; ++t) form(t, std::integral_constant<int, 1>());
+  __shared__ T sum[NG * PP * PP];
+  for (int k = 0; k < WG / 64; ++k) {
+    if (w == k)
+#pragma unroll
+      for (int q = 0; q < NG; ++q)
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+#pragma unroll
+          for (int j = 0; j < V; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              T* at = sum + q * PP * PP + (rowof<T>(g, r) * V + i) * PP + c * V + j;
+              *at = k ? *at + acc[q][i][j][r] : acc[q][i][j][r];
+            }
+    __syncthreads();
+  }
+  double* out = partials + (int64_t)blockIdx.x * NG * PP * PP;
+  for (int e = threadIdx.x; e < NG * PP * PP; e += WG) out[e] = (double)sum[e];
+}
+
 // A^T B1 and (TWO) A^T B2 at PP = 128 in float64, with the workgroups of the wide passes: the
 // A tiles double-buffered in LDS as in k_grad_wide, wave w holding column block w of B1 and B2
 // in the D layout and forming the blocks (ib, w) of both Grams. The B values of a row group
@@ -2026,7 +2106,16 @@ void Kernels<T, PP>::gram(hipStream_t st, int nb, int64_t n, const T* A0, const 
       k_gram_wide<T, PP, false><<<nb, WGW, 2 * WTILE * sizeof(double), st>>>(n, A0, A1, B1, B2, sc, mode, partials);
     return;
   }
-  k_gram<T, PP><<<nb, WG, 0, st>>>(n, A0, A1, B1, B2, sc, mode, partials);
+  if constexpr (PP <= 32) {
+    if (B2)
+      k_gram_rows<T, PP, true, false><<<nb, WG, 0, st>>>(n, A0, A1, B1, B2, sc, mode, partials);
+    else if (B1 == A0 && B1 == A1)
+      k_gram_rows<T, PP, false, true><<<nb, WG, 0, st>>>(n, A0, A1, B1, B2, sc, mode, partials);
+    else
+      k_gram_rows<T, PP, false, false><<<nb, WG, 0, st>>>(n, A0, A1, B1, B2, sc, mode, partials);
+  } else {
+    k_gram<T, PP><<<nb, WG, 0, st>>>(n, A0, A1, B1, B2, sc, mode, partials);
+  }
 }
 template <typename T, int PP>
 void Kernels<T, PP>::product(hipStream_t st, int nb, int64_t n, const T* IN, T* OUT, const double* M) {
