@@ -1203,13 +1203,21 @@ __global__ __launch_bounds__(WG) void k_spmm_stencil(int64_t n, int32_t nx, int3
 // SX x SY grid points in x and y, a chunk of SCC columns and a run of up to SZC planes, and
 // marches through its planes in z: the current plane of the tile with a one-point halo in x
 // and y sits in LDS (the x and y neighbours and the centre are read from there), the previous
-// plane's centres stay in registers, and the next plane's tile and halo are loaded into
-// registers while the current plane is computed, then written to LDS. Thread t owns the
+// plane's centres stay in registers, and the next plane's tile and halo, and this plane's
+// diagonal and V, are loaded into registers before the current plane is computed, the tile and
+// halo then written to LDS. 512 threads, half the points each of 256, leave registers for the V
+// and diagonal values; read where they are used, each of a thread's 8 points waited for its
+// own (filter step on 97 x 96 x 95, PP = 32, with the runs below: 402 -> 152 us, 0.68 GB at 4.5 TB/s). Thread t owns the
 // 16-byte piece q = t mod TPP of the chunk at the points t / TPP + PPS s of the tile (point
 // = y SX + x). The seven terms are those of k_spmm_stencil in the same order with the same
 // zero weights outside the grid, so both kernels return the same bits. Grid: (PP / SCC)
 // chunks fastest, then x tiles, y tiles, runs of planes.
-constexpr int SX = 32, SY = 8, SCC = 16, SZC = 32;
+//
+// Runs are as long as SZC planes where the grid gives MARCH_WGS workgroups (3 for each CU) that
+// way, and down to SZMIN planes otherwise: each run reads one plane more than it has on either
+// side, and too few workgroups leave CUs idle (97 x 96 x 95 at PP = 32 made 288 of them, 179 us
+// a product; runs of 12 planes make 768, 103 us).
+constexpr int SX = 32, SY = 8, SCC = 16, SZC = 32, SZMIN = 4, MARCH_WGS = 768, WGM = 512;
 constexpr int SHX = SX + 2, SHY = SY + 2, SNH = 2 * SX + 2 * SY;  // halo points: no corners
 
 // Halo point h of a tile -> its tile coordinates (-1 or SX / SY on the border).
@@ -1220,24 +1228,34 @@ __device__ __forceinline__ void march_halo_xy(int h, int& lx, int& ly) {
   else { lx = SX; ly = h - 2 * SX - SY; }
 }
 
-inline int64_t march_grid(int PP, const int32_t* dims) {
-  return (int64_t)(PP / SCC) * ((dims[0] + SX - 1) / SX) * ((dims[1] + SY - 1) / SY) * ((dims[2] + SZC - 1) / SZC);
+// Planes of a run, and the grid, for a block of PP columns.
+inline int march_run(int PP, const int32_t* dims) {
+  const int64_t per = (int64_t)(PP / SCC) * ((dims[0] + SX - 1) / SX) * ((dims[1] + SY - 1) / SY);
+  const int64_t longest = (dims[2] + SZC - 1) / SZC, most = (dims[2] + SZMIN - 1) / SZMIN;
+  int64_t runs = (MARCH_WGS + per - 1) / per;
+  runs = runs < longest ? longest : (runs > most ? most : runs);
+  return (int)((dims[2] + runs - 1) / runs);
+}
+inline int64_t march_grid(int PP, const int32_t* dims, int run) {
+  return (int64_t)(PP / SCC) * ((dims[0] + SX - 1) / SX) * ((dims[1] + SY - 1) / SY) * ((dims[2] + run - 1) / run);
 }
 
 template <typename T, int PP, bool AXPY>
-__global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32_t nz, const T* __restrict__ diag,
-                                                   T off, const T* __restrict__ W0, const T* __restrict__ W1,
-                                                   T* __restrict__ Z, const Scalars* __restrict__ sc, int mode,
-                                                   const T* __restrict__ V, double alpha, double beta, double gamma) {
+__global__ __launch_bounds__(WGM) void k_spmm_march(int32_t nx, int32_t ny, int32_t nz, int run,
+                                                    const T* __restrict__ diag, T off, const T* __restrict__ W0,
+                                                    const T* __restrict__ W1, T* __restrict__ Z,
+                                                    const Scalars* __restrict__ sc, int mode,
+                                                    const T* __restrict__ V, double alpha, double beta,
+                                                    double gamma) {
   if (!AXPY && spmm_skip(sc, mode)) return;
   const T* W = (!AXPY && mode == 1 && (sc->k & 1)) ? W1 : W0;
   typedef typename std::conditional<sizeof(T) == 8, d2, f4>::type V16;
   constexpr int E = 16 / (int)sizeof(T);         // elements per piece
   constexpr int TPP = SCC / E;                   // pieces of a point's chunk
-  constexpr int PPS = WG / TPP;                  // points per pass of the workgroup
+  constexpr int PPS = WGM / TPP;                 // points per pass of the workgroup
   constexpr int NS = SX * SY / PPS;              // points per thread
   constexpr int NCC = PP / SCC;
-  constexpr int HQ = (SNH * TPP + WG - 1) / WG;  // halo pieces per thread
+  constexpr int HQ = (SNH * TPP + WGM - 1) / WGM;  // halo pieces per thread
   static_assert(PP % SCC == 0 && (SX * SY) % PPS == 0, "tile shape");
   __shared__ V16 L[SHX * SHY * TPP];
   const int tx = (nx + SX - 1) / SX, ty = (ny + SY - 1) / SY;
@@ -1247,9 +1265,9 @@ __global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32
   const int bx = b % tx;
   b /= tx;
   const int by = b % ty;
-  const int z0 = (b / ty) * SZC;
+  const int z0 = (b / ty) * run;
   if (z0 >= nz) return;  // the whole workgroup, before any barrier
-  const int z1 = z0 + SZC < nz ? z0 + SZC : nz;
+  const int z1 = z0 + run < nz ? z0 + run : nz;
   const int x0 = bx * SX, y0 = by * SY, c0 = cc * SCC;
   const int q = threadIdx.x % TPP, p0 = threadIdx.x / TPP;
   const int64_t plane = (int64_t)nx * ny;
@@ -1267,7 +1285,7 @@ __global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32
   auto load_halo = [&](int z, V16* hl) {
 #pragma unroll
     for (int hh = 0; hh < HQ; ++hh) {
-      const int idx = threadIdx.x + WG * hh;
+      const int idx = threadIdx.x + WGM * hh;
       hl[hh] = zero;
       if (idx < SNH * TPP) {
         int lx, ly;
@@ -1285,7 +1303,7 @@ __global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32
     }
 #pragma unroll
     for (int hh = 0; hh < HQ; ++hh) {
-      const int idx = threadIdx.x + WG * hh;
+      const int idx = threadIdx.x + WGM * hh;
       if (idx < SNH * TPP) {
         int lx, ly;
         march_halo_xy(idx / TPP, lx, ly);
@@ -1293,7 +1311,8 @@ __global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32
       }
     }
   };
-  V16 prv[NS], nxt[NS], hal[HQ];
+  V16 prv[NS], nxt[NS], hal[HQ], vv[AXPY ? NS : 1];
+  T dgs[NS];
   if (z0 > 0) load_centres(z0 - 1, prv);
   else {
 #pragma unroll
@@ -1311,6 +1330,13 @@ __global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32
       for (int s = 0; s < NS; ++s) nxt[s] = zero;
     }
     if (z + 1 < z1) load_halo(z + 1, hal);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int pt = p0 + PPS * s, gx = x0 + pt % SX, gy = y0 + pt / SX;
+      const bool in = gx < nx && gy < ny;
+      dgs[s] = in ? gld(diag + ((int64_t)z * plane + (int64_t)gy * nx + gx)) : T(0);
+      if constexpr (AXPY) vv[s] = in && V ? gld(piece(V, gx, gy, z, q)) : zero;
+    }
     const T vzm = z > 0 ? off : T(0), vzp = z + 1 < nz ? off : T(0);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -1321,7 +1347,7 @@ __global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32
       const T vym = gy > 0 ? off : T(0), vxm = gx > 0 ? off : T(0);
       const T vxp = gx + 1 < nx ? off : T(0), vyp = gy + 1 < ny ? off : T(0);
       const int64_t row = (int64_t)z * plane + (int64_t)gy * nx + gx;
-      const T dg = diag[row];
+      const T dg = dgs[s];
       V16 acc;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -1340,7 +1366,7 @@ __global__ __launch_bounds__(WG) void k_spmm_march(int32_t nx, int32_t ny, int32
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           double zz = alpha * (double)acc[e] + beta * (double)wc[e];
-          if (V) zz += gamma * (double)gld(V + o + e);
+          if (V) zz += gamma * (double)vv[s][e];
           acc[e] = (T)zz;
         }
       }
@@ -2021,8 +2047,9 @@ template <typename T, int PP>
 void Kernels<T, PP>::spmm_stencil(hipStream_t st, int64_t n, const int32_t* dims, const T* diag, double off,
                                   const T* W0, const T* W1, T* Z, const Scalars* sc, int mode, int64_t plane_tiles) {
   if (dims[1] >= SY) {
-    k_spmm_march<T, PP, false><<<dim3((unsigned)march_grid(PP, dims)), dim3(WG), 0, st>>>(
-        dims[0], dims[1], dims[2], diag, (T)off, W0, W1, Z, sc, mode, nullptr, 1.0, 0.0, 0.0);
+    const int run = march_run(PP, dims);
+    k_spmm_march<T, PP, false><<<dim3((unsigned)march_grid(PP, dims, run)), dim3(WGM), 0, st>>>(
+        dims[0], dims[1], dims[2], run, diag, (T)off, W0, W1, Z, sc, mode, nullptr, 1.0, 0.0, 0.0);
     return;
   }
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
@@ -2034,8 +2061,9 @@ void Kernels<T, PP>::spmm_stencil_axpy(hipStream_t st, int64_t n, const int32_t*
                                        const T* W, const T* V, T* Z, double alpha, double beta, double gamma,
                                        int64_t plane_tiles) {
   if (dims[1] >= SY) {
-    k_spmm_march<T, PP, true><<<dim3((unsigned)march_grid(PP, dims)), dim3(WG), 0, st>>>(
-        dims[0], dims[1], dims[2], diag, (T)off, W, W, Z, nullptr, 0, V, alpha, beta, gamma);
+    const int run = march_run(PP, dims);
+    k_spmm_march<T, PP, true><<<dim3((unsigned)march_grid(PP, dims, run)), dim3(WGM), 0, st>>>(
+        dims[0], dims[1], dims[2], run, diag, (T)off, W, W, Z, nullptr, 0, V, alpha, beta, gamma);
     return;
   }
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
