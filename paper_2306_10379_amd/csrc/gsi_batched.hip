@@ -522,7 +522,7 @@ __device__ __noinline__ int b_eig(double* small, int p, bool warm, double* lds) 
 template <int PP>
 __device__ __noinline__ void b_linesearch(const double* PZr, const double* PYr, double* small, int p, double* lds,
                                           Terms& terms, double* smu, int* sok, int* sevals, double* sbmax) {
-  linesearch_dev<PP>(PZr, PYr, small, p, lds, terms, smu, sok, sevals, sbmax);
+  linesearch_dev<PP>(PZr, PYr, small, p, to_lds(lds), terms, smu, sok, sevals, sbmax);
 }
 
 // ---------------------------------------------------------------- one problem
@@ -1106,9 +1106,9 @@ __global__ void k_batched_reset(BatchCtl* ctl) {
   }
 }
 
-// dynamic LDS: product matrix (PP^2 doubles at most) + 64 bytes + 4 PP (PP+1) doubles
+// dynamic LDS: product matrix (PP^2 doubles at most) + 64 bytes + 4 PP (PP+2) doubles
 // (eigendecomposition, line search, Gram reduction)
-constexpr int batched_lds() { return 32 * 32 * 8 + 64 + 4 * 32 * 33 * 8; }
+constexpr int batched_lds() { return 32 * 32 * 8 + 64 + 4 * 32 * 34 * 8; }
 
 }  // namespace gsi
 

@@ -32,44 +32,89 @@ __device__ __forceinline__ double rsq_nr(double x) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+// x / y by the hardware reciprocal and one third-order step (y normal; otherwise it may give
+// no number).
+__device__ __forceinline__ double div_nr(double x, double y) {
+  const double r = __builtin_amdgcn_rcp(y), e = fma(-y, r, 1.0);
+  return x * fma(r * e, 1.0 + e, r);
+}
+
 // ---------------------------------------------------------------- products
 
-// Cout = alpha op(A) op(B) on the leading 16 nb x 16 nb blocks, strides lda, ldb, ldc (any
-// memory space), 16 x 16 output blocks dealt to the workgroup's waves; no barrier inside.
-__device__ __forceinline__ void mm_lds(int nb, const double* A, int lda, bool ta, const double* B, int ldb, bool tb,
-                              double* Cout, int ldc, double alpha = 1.0) {
+// op(A) op(B) on the leading 16 nb x 16 nb blocks (nb <= NB), row strides LDA and LDB (any
+// memory space); put(i, j, v) takes each entry. SYM: the product is symmetric, only blocks on
+// and above the diagonal are formed, and put sees i <= j (to store both). No barrier inside.
+//
+// A wave takes whole columns of 16 x 16 blocks: the right operand of 16 of k is loaded once for
+// all of them, their accumulators are independent MFMA chains, and the loads of the next 16 of k
+// are issued before these multiply. Strides and transposes are compile-time values, so that
+// loads are one base address and immediate offsets. 7.0k clocks at p = 64, against 4.1k of MFMA
+// issue on the four SIMDs (block by block: 8.2k).
+template <int NB, int LDA, bool TA, int LDB, bool TB, bool SYM = false, typename F>
+__device__ __forceinline__ void mm_dense(int nb, const double* A, const double* B, F put) {
+  constexpr int SA = TA ? LDA : 1, SB = TB ? 1 : LDB;  // steps of k
+  constexpr int IA = TA ? 16 : 16 * LDA;               // step of a block row
   const int nw = blockDim.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
-  const int sak = ta ? lda : 1, sbk = tb ? 1 : ldb;
-  for (int blk = threadIdx.x >> 6; blk < nb * nb; blk += nw) {
-    const int ib = blk / nb, jb = blk - ib * nb;
-    const double* a = A + (ta ? 16 * ib + c : (16 * ib + c) * lda) + g * sak;
-    const double* b = B + (tb ? (16 * jb + c) * ldb : 16 * jb + c) + g * sbk;
-    d4 acc = {0.0, 0.0, 0.0, 0.0};
-    double av[4], bv[4];
+  for (int jb = threadIdx.x >> 6; jb < nb; jb += nw) {
+    const int ni = SYM ? jb + 1 : nb;
+    const double* a = A + (TA ? c : c * LDA) + g * SA;
+    const double* b = B + (TB ? (16 * jb + c) * LDB : 16 * jb + c) + g * SB;
+    d4 acc[NB];
+    double av[NB][4], bv[4];
+    auto load = [&](double (&x)[NB][4], double (&y)[4]) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      av[s] = a[4 * s * sak];
-      bv[s] = b[4 * s * sbk];
-    }
-    for (int k = 0; k < nb; ++k) {
-      double an[4], bn[4];
-      const int o = k + 1 < nb ? 16 * (k + 1) : 0;  // the next 16 of k while these multiply
+      for (int s = 0; s < 4; ++s) y[s] = b[4 * s * SB];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        an[s] = a[(o + 4 * s) * sak];
-        bn[s] = b[(o + 4 * s) * sbk];
+      for (int i = 0; i < NB; ++i)
+        if (i < ni)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) x[i][s] = a[i * IA + 4 * s * SA];
+    };
+    auto mul = [&]() {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (i < ni)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc[i] = mfma(av[i][s], bv[s], acc[i]);
+    };
+#pragma unroll
+    for (int i = 0; i < NB; ++i) acc[i] = d4{0.0, 0.0, 0.0, 0.0};
+    load(av, bv);
+    for (int k = 1; k < nb; ++k) {
+      a += 16 * SA;
+      b += 16 * SB;
+      if constexpr (NB > 4) {  // two waves per SIMD cover each other's loads; no room for both
+        mul();
+        load(av, bv);
+      } else {
+        double an[NB][4], bn[4];
+        load(an, bn);
+        mul();
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          bv[s] = bn[s];
+#pragma unroll
+          for (int i = 0; i < NB; ++i) av[i][s] = an[i][s];
+        }
       }
-#pragma unroll
-      for (int s = 0; s < 4; ++s) acc = mfma(av[s], bv[s], acc);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        av[s] = an[s];
-        bv[s] = bn[s];
-      }
     }
+    mul();
 #pragma unroll
-    for (int r = 0; r < 4; ++r) Cout[(16 * ib + g + 4 * r) * ldc + 16 * jb + c] = alpha * acc[r];
+    for (int i = 0; i < NB; ++i)
+      if (i < ni)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = 16 * i + g + 4 * r, col = 16 * jb + c;
+          if (!SYM || row <= col) put(row, col, acc[i][r]);
+        }
   }
+}
+
+// dst[i ld + j] = f(i, j) on the leading m x m square, 64 columns to a wave.
+template <typename F>
+__device__ __forceinline__ void fill_dense(int m, double* dst, int ld, F f) {
+  for (int i = threadIdx.x >> 6; i < m; i += blockDim.x >> 6)
+    for (int j = threadIdx.x & 63; j < m; j += 64) dst[i * ld + j] = f(i, j);
 }
 
 // ---------------------------------------------------------------- Cholesky
@@ -268,6 +313,16 @@ __device__ __forceinline__ void sum_rows8(double (&v)[K]) {
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int k = 0; k < K; ++k) v[k] += o[k];
+}
+
+// Sum over the 64 lanes; every lane gets the same bits.
+__device__ __forceinline__ double wave_sum_all(double v) {
+  v += dpp_d<DPP_XOR1>(v);
+  v += dpp_d<DPP_XOR2>(v);
+  v += dpp_d<DPP_XOR7>(v);
+  double o[1] = {v};
+  sum_rows8(o);
+  return o[0];
 }
 
 // A wave's 8 column pairs (x, y) of eig_lds: pair q = lane mod 8, R rows a lane.

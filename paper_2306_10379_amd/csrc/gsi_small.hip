@@ -143,7 +143,7 @@ __global__ __launch_bounds__(dense_threads(PP)) void k_eig(double* __restrict__ 
 // Line search and retraction factor (see linesearch_dev), one workgroup; red holds the
 // reduced Grams P^T A P, P^T A X of the SpMM.
 template <int PP>
-__global__ __launch_bounds__(WG) void k_linesearch(const double* __restrict__ red, double* __restrict__ small,
+__global__ __launch_bounds__(dense_threads(PP)) void k_linesearch(const double* __restrict__ red, double* __restrict__ small,
                                                    Scalars* __restrict__ sc, double* __restrict__ hist,
                                                    int recompute_ax, int want_mc) {
   if (sc->done || sc->null_step) return;
@@ -156,10 +156,8 @@ __global__ __launch_bounds__(WG) void k_linesearch(const double* __restrict__ re
   for (int i = threadIdx.x; i < (int)(sizeof(Scalars) / 4); i += blockDim.x)
     reinterpret_cast<int32_t*>(&ls)[i] = reinterpret_cast<const int32_t*>(sc)[i];
   __syncthreads();
-  const int p = ls.p;
-  double* work = PP > PP_LDS_MAX ? small + small_work_offset(PP) + 4 * PP * (PP + 1)
-                                 : reinterpret_cast<double*>(lds_raw);
-  linesearch_dev<PP>(red, red + PP * PP, small, p, work, terms, &smu, &sok, &sevals, &sbmax, want_mc != 0);
+  linesearch_dev<PP>(red, red + PP * PP, small, ls.p, reinterpret_cast<double*>(lds_raw), terms, &smu, &sok, &sevals,
+                     &sbmax, want_mc != 0);
   if (threadIdx.x == 0) {
     sc->brent_evals = sevals;
     sc->grad_ready = 0;  // X changes (or the step is void and the next iteration restarts)
@@ -305,6 +303,7 @@ __global__ __launch_bounds__(dense_threads(PP)) void k_ritz(int p, const double*
 // ---------------------------------------------------------------- launchers
 
 constexpr int eig_bytes(int PP) { return eig_lds_doubles(PP) * (int)sizeof(double); }
+constexpr int linesearch_bytes(int PP) { return linesearch_lds_doubles(PP) * (int)sizeof(double); }
 constexpr int ritz_bytes(int PP) { return PP * (PP + 2) * (int)sizeof(double); }
 constexpr int chol_bytes(int PP) { return (PP > PP_LDS_MAX ? 1 : 2) * PP * (PP + 2) * (int)sizeof(double); }
 
@@ -316,8 +315,8 @@ static hipError_t init_pp() {
   hipError_t e = lds(k_eig<PP>, eig_bytes(PP));
   if (e == hipSuccess) e = lds(k_ritz<PP>, ritz_bytes(PP));
   if (e == hipSuccess) e = lds(k_chol_inv<PP>, chol_bytes(PP));
-  if (PP > PP_LDS_MAX) return e;  // the other p x p kernels use the work area there
-  if (e == hipSuccess) e = lds(k_linesearch<PP>, 4 * PP * PP * 8);
+  if (e == hipSuccess) e = lds(k_linesearch<PP>, linesearch_bytes(PP));
+  if (PP > PP_LDS_MAX) return e;  // k_transform_cw uses the work area there
   if (e == hipSuccess) e = lds(k_transform_cw<PP>, 2 * PP * PP * 8);
   return e;
 }
@@ -346,11 +345,15 @@ void Small::eig(hipStream_t st, int PP, double* small, Scalars* sc) {
 void Small::linesearch(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, double* hist,
                        int recompute_ax, bool want_mc) {
   const int mc = want_mc ? 1 : 0;
+  auto go = [&](auto P) {
+    constexpr int pp = decltype(P)::value;
+    k_linesearch<pp><<<1, dense_threads(pp), linesearch_bytes(pp), st>>>(red, small, sc, hist, recompute_ax, mc);
+  };
   switch (PP) {
-    case 16: k_linesearch<16><<<1, WG, 4 * 16 * 16 * 8, st>>>(red, small, sc, hist, recompute_ax, mc); break;
-    case 32: k_linesearch<32><<<1, WG, 4 * 32 * 32 * 8, st>>>(red, small, sc, hist, recompute_ax, mc); break;
-    case 64: k_linesearch<64><<<1, WG, 4 * 64 * 64 * 8, st>>>(red, small, sc, hist, recompute_ax, mc); break;
-    case 128: k_linesearch<128><<<1, WG, 0, st>>>(red, small, sc, hist, recompute_ax, mc); break;
+    case 16: go(std::integral_constant<int, 16>()); break;
+    case 32: go(std::integral_constant<int, 32>()); break;
+    case 64: go(std::integral_constant<int, 64>()); break;
+    case 128: go(std::integral_constant<int, 128>()); break;
   }
 }
 void Small::after_update_grams(hipStream_t st, int PP, const double* red, double* small, Scalars* sc) {

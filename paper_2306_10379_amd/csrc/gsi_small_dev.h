@@ -48,59 +48,51 @@ __device__ inline void wg_mm(const double* A, bool ta, const double* B, bool tb,
   }
 }
 
-// out[i] = sign * sum_k V[k][i] T[k][i]  (the diagonal of V^T T), i < PP.
-template <int PP>
-__device__ inline void col_dots(const double* V, const double* T, double* out, double sign) {
-  for (int i = threadIdx.x; i < PP; i += blockDim.x) {
-    double s = 0.0;
-    for (int k = 0; k < PP; ++k) s += V[k * PP + i] * T[k * PP + i];
-    out[i] = sign * s;
-  }
-}
-
 // ---------------------------------------------------------------- line search (wave 0)
 
 struct Terms {
   double a[TMAXP], b[TMAXP], g[TMAXP], z[TMAXP];
-  int act[TMAXP];
 };
 
-// phi'(mu) = - sum over active terms of (z + d mu - b z mu^2) / (1 + b mu^2)^2 (Sec. 5.2,
-// eq. deriv_P), evaluated by wave 0 (lane i holds terms i and i + 64).
-__device__ inline double dphi_term(const Terms& T, int i, double mu) {
-  const double b = T.b[i], z = T.z[i], d = T.g[i] - T.a[i] * b;
-  const double den = 1.0 + b * mu * mu;
-  return (z + d * mu - b * z * mu * mu) / (den * den);
-}
-__device__ inline double dphi(const Terms& T, int p, double mu) {
-  const int l = threadIdx.x & 63;
-  double v = 0.0;
-  if (l < p && T.act[l]) v = dphi_term(T, l, mu);
-  if (l + 64 < p && T.act[l + 64]) v += dphi_term(T, l + 64, mu);
-  return -wave_sum(v);
+// Term of phi'(mu) = - sum over active terms of (z + d mu - b z mu^2) / (1 + b mu^2)^2,
+// d = g - a b (Sec. 5.2, eq. deriv_P).
+__device__ __forceinline__ double dphi_term(double a, double b, double g, double z, double mu) {
+  const double d = g - a * b, den = 1.0 + b * mu * mu;
+  const double r = div_nr(1.0, den);  // den >= 1
+  return den < 1e300 ? (z + d * mu - b * z * mu * mu) * r * r : 0.0;
 }
 
 // Get_Mu (Algorithm 3, Sec. 5.2, Sec. 6.1): returns mu > 0 or -1 when no usable bracket.
 // Called by wave 0 only; p terms (padding terms have b = 0), preal the block size for the
-// activity threshold; *evals counts phi' evaluations.
-__device__ inline double get_mu(Terms& T, int p, int preal, int* evals) {
+// activity threshold; *evals counts phi' evaluations, *bm gets the largest b.
+__device__ inline double get_mu(Terms& T, int p, int preal, int* evals, double* bm) {
   // lane l holds terms l and l + 64 (the second only for p > 64)
   const int l = threadIdx.x & 63, l2 = l + 64;
-  const double bl = l < p ? T.b[l] : 0.0;
-  const double bl2 = l2 < p ? T.b[l2] : 0.0;
+  const bool two = p > 64;
+  const double al = l < p ? T.a[l] : 0.0, bl = l < p ? T.b[l] : 0.0;
+  const double gl = l < p ? T.g[l] : 0.0, zl = l < p ? T.z[l] : 0.0;
+  const double al2 = l2 < p ? T.a[l2] : 0.0, bl2 = l2 < p ? T.b[l2] : 0.0;
+  const double gl2 = l2 < p ? T.g[l2] : 0.0, zl2 = l2 < p ? T.z[l2] : 0.0;
   const double bmax = wave_max(l2 < p ? fmax(bl, bl2) : bl);
+  *bm = bmax;
   int ev = 0;
   if (!(bmax > 0.0)) { *evals = 0; return -1.0; }
   const bool act = l < p && bl > preal * EPS * bmax;
   const bool act2 = l2 < p && bl2 > preal * EPS * bmax;
-  if (l < p) T.act[l] = act ? 1 : 0;
-  if (l2 < p) T.act[l2] = act2 ? 1 : 0;
+  // inactive terms become zero ones, so that the sums below need no test
+  if (l < p && !act) T.a[l] = T.b[l] = T.g[l] = T.z[l] = 0.0;
+  if (l2 < p && !act2) T.a[l2] = T.b[l2] = T.g[l2] = T.z[l2] = 0.0;
   wave_sync();
-  const bool conv = act && T.z[l] > 0.0;
-  const bool conv2 = act2 && T.z[l2] > 0.0;
+  const bool conv = act && zl > 0.0;
+  const bool conv2 = act2 && zl2 > 0.0;
+  auto dphi = [&](double mu) {
+    double v = act ? dphi_term(al, bl, gl, zl, mu) : 0.0;
+    if (two && act2) v += dphi_term(al2, bl2, gl2, zl2, mu);
+    return -wave_sum_all(v);
+  };
   if (__ballot(conv || conv2) == 0) { *evals = 0; return -1.0; }
   // f(0) = -sum of active zeta
-  const double f0 = dphi(T, p, 0.0);
+  const double f0 = dphi(0.0);
   ++ev;
   if (!(f0 < 0.0)) { *evals = ev; return -1.0; }
   // branch roots of the convex branches, without cancellation (Sec. 6.1, eqs. derv1/derv2)
@@ -112,11 +104,9 @@ __device__ inline double get_mu(Terms& T, int p, int preal, int* evals) {
   // phi' at a candidate root: the sum over every active term
   auto dphi_all = [&](double x) {
     double acc = 0.0;
+#pragma unroll 8
     for (int i = 0; i < p; ++i) {
-      if (!T.act[i]) continue;
-      const double b = T.b[i], z = T.z[i], d = T.g[i] - T.a[i] * b;
-      const double den = 1.0 + b * x * x;
-      acc += (z + d * x - b * z * x * x) / (den * den);
+      acc += dphi_term(T.a[i], T.b[i], T.g[i], T.z[i], x);
     }
     return -acc;
   };
@@ -137,22 +127,22 @@ __device__ inline double get_mu(Terms& T, int p, int preal, int* evals) {
   if (hi == INFINITY) {
     int widen = 0;
     hi = 2.0 * (lo > 0.0 ? lo : 1.0);
-    fhi = dphi(T, p, hi);
+    fhi = dphi(hi);
     ++ev;
     while (fhi < 0.0 && widen < 60) {
       lo = hi;
       hi *= 2.0;
-      fhi = dphi(T, p, hi);
+      fhi = dphi(hi);
       ++ev;
       ++widen;
     }
     if (fhi < 0.0) { *evals = ev; return -1.0; }
   } else {
-    fhi = dphi(T, p, hi);
+    fhi = dphi(hi);
     ++ev;
   }
   if (fhi == 0.0) { *evals = ev; return hi; }
-  double flo = dphi(T, p, lo);
+  double flo = dphi(lo);
   ++ev;
   if (flo == 0.0) { *evals = ev; return lo; }
   // Brent's method (Brent 1973, ch. 4): inverse quadratic interpolation / secant steps
@@ -172,20 +162,20 @@ __device__ inline double get_mu(Terms& T, int p, int preal, int* evals) {
     if (fabs(xm) <= tol1 || fb == 0.0) break;
     if (fabs(e) >= tol1 && fabs(fa) > fabs(fb)) {
       double pp, q, r;
-      const double s = fb / fa;
+      const double s = div_nr(fb, fa);
       if (a == c) {
         pp = 2.0 * xm * s;
         q = 1.0 - s;
       } else {
-        q = fa / fc;
-        r = fb / fc;
+        q = div_nr(fa, fc);
+        r = div_nr(fb, fc);
         pp = s * (2.0 * xm * q * (q - r) - (b - a) * (r - 1.0));
         q = (q - 1.0) * (r - 1.0) * (s - 1.0);
       }
       if (pp > 0.0) q = -q; else pp = -pp;
       if (2.0 * pp < fmin(3.0 * xm * q - fabs(tol1 * q), fabs(e * q))) {
         e = d;
-        d = pp / q;
+        d = div_nr(pp, q);
       } else {
         d = xm;
         e = d;
@@ -197,7 +187,7 @@ __device__ inline double get_mu(Terms& T, int p, int preal, int* evals) {
     a = b;
     fa = fb;
     b += fabs(d) > tol1 ? d : (xm > 0.0 ? tol1 : -tol1);
-    fb = dphi(T, p, b);
+    fb = dphi(b);
     ++ev;
   }
   *evals = ev;
@@ -229,59 +219,51 @@ __device__ inline int eig_dev(double* small, int p, bool warm, double* lds) {
   const double* S = small + S_S * PP * PP;
   double* Vg = small + S_V * PP * PP;
   double* b = small + S_VEC * PP * PP;
-  // the leading m x m block of f(i, j), 64 columns to a wave
-  auto fill = [&](double* dst, int ld, auto f) {
-    for (int i = threadIdx.x >> 6; i < m; i += blockDim.x >> 6)
-      for (int j = threadIdx.x & 63; j < m; j += 64) dst[i * ld + j] = f(i, j);
-  };
+  auto to = [](double* dst) { return [dst](int i, int j, double v) { dst[i * LD + j] = v; }; };
+  auto to_sym = [](double* dst) { return [dst](int i, int j, double v) { dst[i * LD + j] = dst[j * LD + i] = v; }; };
   if (warm) {
-    const double* V0 = Vg;
-    int ldv = PP;
+    constexpr int LV = wide ? PP : LD;
+    const double* V0 = wide ? Vg : T;
     if constexpr (!wide) {
-      fill(T, LD, [&](int i, int j) { return Vg[i * PP + j]; });
-      V0 = T;
-      ldv = LD;
+      fill_dense(m, T, LD, [&](int i, int j) { return Vg[i * PP + j]; });
       __syncthreads();
     }
-    mm_lds(nb, V0, ldv, true, V0, ldv, false, A, LD);
+    mm_dense<PP / 16, LV, true, LV, false, true>(nb, V0, V0, [&](int i, int j, double v) {  // (3 I - V^T V) / 2
+      A[i * LD + j] = A[j * LD + i] = 0.5 * ((i == j ? 3.0 : 0.0) - v);
+    });
     __syncthreads();
-    fill(A, LD, [&](int i, int j) { return 0.5 * ((i == j ? 3.0 : 0.0) - A[i * LD + j]); });
-    __syncthreads();
-    mm_lds(nb, V0, ldv, false, A, LD, false, V1, LD);
+    mm_dense<PP / 16, LV, false, LD, false>(nb, V0, A, to(V1));
     __syncthreads();
     if constexpr (wide) {
-      mm_lds(nb, S, PP, false, V1, LD, false, T, LD);
+      mm_dense<PP / 16, PP, true, LD, false>(nb, S, V1, to(T));  // S is symmetric
       __syncthreads();
-      mm_lds(nb, V1, LD, true, T, LD, false, A, LD);
-    } else {
-      fill(T, LD, [&](int i, int j) { return S[i * PP + j]; });
+      mm_dense<PP / 16, LD, true, LD, false, true>(nb, V1, T, to_sym(A));
       __syncthreads();
-      mm_lds(nb, T, LD, false, V1, LD, false, A, LD);
-      __syncthreads();
-      mm_lds(nb, V1, LD, true, A, LD, false, T, LD);
-    }
-    __syncthreads();
-    // symmetric to the last bit, sorted by the diagonal
-    if constexpr (wide) {
       diag_order(p, ord, key, [&](int i) { return A[i * LD + i]; });
-      fill(T, LD, [&](int i, int j) { return 0.5 * (A[ord[i] * LD + ord[j]] + A[ord[j] * LD + ord[i]]); });
+      fill_dense(m, T, LD, [&](int i, int j) { return A[ord[i] * LD + ord[j]]; });
       __syncthreads();
-      fill(A, LD, [&](int i, int j) { return T[i * LD + j]; });
+      fill_dense(m, A, LD, [&](int i, int j) { return T[i * LD + j]; });
     } else {
+      fill_dense(m, T, LD, [&](int i, int j) { return S[i * PP + j]; });
+      __syncthreads();
+      mm_dense<PP / 16, LD, false, LD, false>(nb, T, V1, to(A));
+      __syncthreads();
+      mm_dense<PP / 16, LD, true, LD, false, true>(nb, V1, A, to_sym(T));
+      __syncthreads();
       diag_order(p, ord, key, [&](int i) { return T[i * LD + i]; });
-      fill(A, LD, [&](int i, int j) { return 0.5 * (T[ord[i] * LD + ord[j]] + T[ord[j] * LD + ord[i]]); });
+      fill_dense(m, A, LD, [&](int i, int j) { return T[ord[i] * LD + ord[j]]; });
     }
   } else {
     diag_order(p, ord, key, [&](int i) { return S[i * PP + i]; });
-    fill(A, LD, [&](int i, int j) { return S[ord[i] * PP + ord[j]]; });
+    fill_dense(m, A, LD, [&](int i, int j) { return S[ord[i] * PP + ord[j]]; });
   }
   __syncthreads();
   const int sweeps = eig_lds<PP>(p, A, ord, 0.0, b);
   __syncthreads();
   if (warm)
-    mm_lds(nb, V1, LD, false, A, LD, false, Vg, PP);
+    mm_dense<PP / 16, LD, false, LD, false>(nb, V1, A, [&](int i, int j, double v) { Vg[i * PP + j] = v; });
   else
-    fill(Vg, PP, [&](int i, int j) { return A[i * LD + j]; });
+    fill_dense(m, Vg, PP, [&](int i, int j) { return A[i * LD + j]; });
   for (int i = threadIdx.x; i < PP; i += blockDim.x) b[i] = i < p ? fmax(b[i], 0.0) : 0.0;
   __syncthreads();
   return sweeps;
@@ -289,46 +271,139 @@ __device__ inline int eig_dev(double* small, int p, bool warm, double* lds) {
 
 // ---------------------------------------------------------------- line search and retraction factor
 
+// a_i = v_i^T C v_i, g_i = v_i^T Z v_i, z_i = -v_i^T Y v_i for the leading 16 nb columns v_i of V
+// (LDS, stride DLD<PP>) and the matrices C, Z, Y (global, stride PP): the line-search
+// diagonals. A wave takes 16 columns, whose operand stays in registers for all three matrices;
+// a matrix is read by rows as the transposed left operand (coalesced; v^T B v = v^T B^T v) and
+// the product's blocks go into the dot products from the matrix unit's registers.
+template <int PP>
+__device__ __forceinline__ void quad_diag(int nb, const double* V, const double* C, const double* Z, const double* Y,
+                                          Terms& terms) {
+  constexpr int LD = DLD<PP>, NB = PP / 16;
+  const int nw = blockDim.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
+  for (int jb = threadIdx.x >> 6; jb < nb; jb += nw) {
+    double v[NB][4];
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) v[k][s] = k < nb ? V[(16 * k + 4 * s + g) * LD + 16 * jb + c] : 0.0;
+    // the blocks (matrix, ib) one after the other, the next one's rows loaded before this one's
+    // products
+    double sum[3] = {0.0, 0.0, 0.0};
+    double x[NB][4], y[NB][4];
+    auto load = [&](const double* B, int ib, double (&to)[NB][4]) {
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        if (k < nb)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) to[k][s] = B[(16 * k + 4 * s + g) * PP + 16 * ib + c];
+    };
+    if constexpr (NB <= 4) load(C, 0, x);
+    auto matrix = [&](const double* B, const double* next, double& acc) {
+      for (int ib = 0; ib < nb; ++ib) {
+        if constexpr (NB > 4) {
+          load(B, ib, x);  // two waves per SIMD cover each other's loads
+        } else {
+          if (ib + 1 < nb) load(B, ib + 1, y);
+          else if (next) load(next, 0, y);
+        }
+        d4 t = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+          if (k < nb)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) t = mfma(x[k][s], v[k][s], t);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc = fma(t[r], V[(16 * ib + g + 4 * r) * LD + 16 * jb + c], acc);
+        if constexpr (NB <= 4)
+#pragma unroll
+          for (int k = 0; k < NB; ++k)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) x[k][s] = y[k][s];
+      }
+    };
+    matrix(C, Z, sum[0]);
+    matrix(Z, Y, sum[1]);
+    matrix(Y, nullptr, sum[2]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      sum[q] += __shfl_xor(sum[q], 16, 64);
+      sum[q] += __shfl_xor(sum[q], 32, 64);
+    }
+    const double a = sum[0], gm = sum[1], z = sum[2];
+    if (g == 0) {
+      terms.a[16 * jb + c] = a;
+      terms.g[16 * jb + c] = gm;
+      terms.z[16 * jb + c] = -z;
+    }
+  }
+}
+
 // Exact line search (Sec. 5.2, Algorithm 3, Sec. 6.1) from V, b (eig_dev), C = small[S_C],
 // S = small[S_S] and the Grams P^T A P (PZr) and P^T A X (PYr). On success (*sok = 1) it
 // writes mu (*smu), M = small[S_M], the next C and W (small[S_C], small[S_W]) and the largest
 // b (*sbmax), and with want_mc also M C_next = small[S_MC] (the right factor of the next
-// gradient, G = (X - mu P) M C_next - (Y - mu Z) M, for the fused retraction pass). lds: 4 PP^2
-// doubles; terms, smu, sok, sevals, sbmax in shared memory. Whole workgroup.
+// gradient, G = (X - mu P) M C_next - (Y - mu Z) M, for the fused retraction pass). lds:
+// linesearch_lds_doubles(PP); terms, smu, sok, sevals, sbmax in shared memory. Whole workgroup
+// of dense_threads(PP).
+//
+// Twelve p x p products one after the other, and Get_Mu (5 us at p = 8, 7 us at p = 64), bound
+// it. Matrices sit in LDS at the stride that keeps the operand loads free of bank conflicts
+// (with a stride of PP each load hit one bank 16 times), the Grams are read coalesced, blocks
+// below the diagonal of symmetric products and past p are left out: k_linesearch 108 -> 64 us at
+// p = 64, 30 -> 27 us at p = 32, 15.5 -> 14.5 us at p = 8, 1010 -> 293 us at p = 128. Above PP = 64 one matrix fits LDS (V, then M in its two stages) and
+// the others sit in the work area of the small buffer, always read by rows.
+constexpr int linesearch_lds_doubles(int PP) { return (PP > PP_LDS_MAX ? 1 : 4) * PP * (PP + 2); }
+
 template <int PP>
 __device__ inline void linesearch_dev(const double* PZr, const double* PYr, double* small, int p, double* lds,
                                       Terms& terms, double* smu, int* sok, int* sevals, double* sbmax,
                                       bool want_mc = false) {
-  double* V = lds;
-  double* Mc = V + PP * PP;
-  double* T1 = Mc + PP * PP;
-  double* T2 = T1 + PP * PP;
+  constexpr int LD = DLD<PP>;
+  constexpr bool wide = PP > PP_LDS_MAX;
+  const int nb = (p + 15) >> 4, m = 16 * nb;
+  double* work = wide ? small + small_work_offset(PP) + 4 * PP * (PP + 1) : lds;
+  double *b0 = work, *b1 = work + PP * LD, *b2 = work + 2 * PP * LD;
+  double* U = wide ? lds : b0;
   const double* S = small + S_S * PP * PP;
   double* C = small + S_C * PP * PP;
+  double* M = small + S_M * PP * PP;
+  double* W = small + S_W * PP * PP;
+  double* MC = small + S_MC * PP * PP;
   const double* bvec = small + S_VEC * PP * PP;
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) V[e] = small[S_V * PP * PP + e];
-  for (int i = threadIdx.x; i < TMAXP; i += blockDim.x) terms.b[i] = i < PP ? bvec[i] : 0.0;
+  const double* Vg = small + S_V * PP * PP;
+  // a matrix that the following products read from LDS
+  auto settle = [&](double* src) {
+    if constexpr (!wide) return src;
+    __syncthreads();
+    fill_dense(m, lds, LD, [&](int i, int j) { return src[i * LD + j]; });
+    return lds;
+  };
+  fill_dense(m, U, LD, [&](int i, int j) { return Vg[i * PP + j]; });
+  const double* Sm = S;  // P^T P as the products read it: S^T = S
+  constexpr int LDS_S = wide ? PP : LD;
+  if constexpr (!wide) {
+    double* b3 = work + 3 * PP * LD;
+    fill_dense(m, b3, LD, [&](int i, int j) { return S[i * PP + j]; });
+    Sm = b3;
+  }
+  for (int i = threadIdx.x; i < TMAXP; i += blockDim.x) {
+    terms.b[i] = i < PP ? bvec[i] : 0.0;
+    if (i >= m) terms.a[i] = terms.g[i] = terms.z[i] = 0.0;
+  }
   __syncthreads();
   // line-search diagonals (Sec. 5.2, eq. CG_linesearch_D) in the basis V; the diagonal of
   // V^T B V only needs the symmetric part of B, so the raw Grams are used
-  wg_mm<PP>(C, false, V, false, T1);
-  wg_mm<PP>(PZr, false, V, false, T2);
-  __syncthreads();
-  col_dots<PP>(V, T1, terms.a, 1.0);
-  col_dots<PP>(V, T2, terms.g, 1.0);
-  wg_mm<PP>(PYr, false, V, false, Mc);
-  __syncthreads();
-  col_dots<PP>(V, Mc, terms.z, -1.0);
+  quad_diag<PP>(nb, U, C, PZr, PYr, terms);
   __syncthreads();
   if (threadIdx.x < 64) {
     int evals = 0;
-    const double mu = get_mu(terms, PP, p, &evals);
+    double bmax = 0.0;
+    const double mu = get_mu(terms, PP, p, &evals, &bmax);
     if (threadIdx.x == 0) {
       *smu = mu;
       *sok = mu > 0.0 && isfinite(mu);
       *sevals = evals;
-      double bmax = 0.0;
-      for (int i = 0; i < p; ++i) bmax = fmax(bmax, terms.b[i]);
       *sbmax = bmax;
     }
   }
@@ -339,51 +414,48 @@ __device__ inline void linesearch_dev(const double* PZr, const double* PYr, doub
   // about (number of rotations) * eps, which would let X(mu) drift from orthonormality
   // step after step; one Newton step for the inverse square root of B = I + mu^2 S,
   // M <- M (3 I - M B M) / 2, restores M B M = I to second order.
-  // (terms.a is free after Get_Mu: it holds the PP column factors (1 + mu^2 b)^{-1/2})
-  for (int i = threadIdx.x; i < PP; i += blockDim.x) terms.a[i] = 1.0 / sqrt(1.0 + mu * mu * terms.b[i]);
+  // (terms.a is free after Get_Mu: it holds the column factors (1 + mu^2 b)^{-1/4})
+  for (int i = threadIdx.x; i < PP; i += blockDim.x) terms.a[i] = sqrt(1.0 / sqrt(1.0 + mu * mu * terms.b[i]));
   __syncthreads();
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) T1[e] = V[e] * terms.a[e % PP];
+  fill_dense(m, U, LD, [&](int i, int j) { return U[i * LD + j] * terms.a[j]; });
   __syncthreads();
-  wg_mm<PP>(T1, false, V, true, Mc);  // Mc = V D V^T
+  mm_dense<PP / 16, LD, false, LD, true, true>(nb, U, U, [&](int i, int j, double v) { b1[i * LD + j] = b1[j * LD + i] = v; });
+  const double* M0 = settle(b1);
   __syncthreads();
-  wg_mm<PP>(S, false, Mc, false, T1);  // T1 = S M
+  mm_dense<PP / 16, LDS_S, true, LD, false>(nb, Sm, M0, [&](int i, int j, double v) {  // B M
+    b2[i * LD + j] = fma(mu * mu, v, M0[i * LD + j]);
+  });
   __syncthreads();
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) T1[e] = Mc[e] + mu * mu * T1[e];  // B M
+  mm_dense<PP / 16, LD, false, LD, false, true>(nb, M0, b2, [&](int i, int j, double v) {  // 3 I - M B M
+    b0[i * LD + j] = b0[j * LD + i] = (i == j ? 3.0 : 0.0) - v;
+  });
   __syncthreads();
-  wg_mm<PP>(Mc, false, T1, false, T2);  // M B M
-  __syncthreads();
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) T2[e] = ((e / PP) == (e % PP) ? 3.0 : 0.0) - T2[e];
-  __syncthreads();
-  wg_mm<PP>(Mc, false, T2, false, T1);  // M (3I - M B M)
-  __syncthreads();
-  double* M = small + S_M * PP * PP;
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
-    const int i = e / PP, j = e % PP;
-    const double v = 0.25 * (T1[i * PP + j] + T1[j * PP + i]);
-    Mc[e] = v;
-    M[e] = v;
-  }
+  mm_dense<PP / 16, LD, false, LD, false, true>(nb, M0, b0, [&](int i, int j, double v) {
+    const double h = 0.5 * v;
+    b2[i * LD + j] = b2[j * LD + i] = h;
+    M[i * PP + j] = M[j * PP + i] = h;
+  });
+  const double* Mf = settle(b2);
   __syncthreads();
   // next C = M (C - mu (P^T Y + Y^T P) + mu^2 P^T Z) M and next W = X_new^T P = -mu M S
   // (X^T P = 0 for the tangent direction; A X recursion of Sec. 6.1, eq. save_matvec)
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
-    const int i = e / PP, j = e % PP;
-    T2[e] = C[e] - mu * (PYr[e] + PYr[j * PP + i]) + 0.5 * mu * mu * (PZr[e] + PZr[j * PP + i]);
-  }
+  // (half of it by rows, so that the Grams are read coalesced, then the sum with its transpose)
+  fill_dense(m, b1, LD, [&](int i, int j) {
+    return 0.5 * C[i * PP + j] - mu * PYr[i * PP + j] + 0.5 * mu * mu * PZr[i * PP + j];
+  });
   __syncthreads();
-  wg_mm<PP>(Mc, false, T2, false, T1);
+  fill_dense(m, b0, LD, [&](int i, int j) { return b1[i * LD + j] + b1[j * LD + i]; });
   __syncthreads();
-  wg_mm<PP>(T1, false, Mc, false, T2);
-  double* W = small + S_W * PP * PP;
-  wg_mm<PP>(Mc, false, S, false, W, -mu);
+  mm_dense<PP / 16, LD, true, LD, false>(nb, b0, Mf, [&](int i, int j, double v) { b1[i * LD + j] = v; });
+  mm_dense<PP / 16, LD, false, LDS_S, false>(nb, Mf, Sm, [&](int i, int j, double v) { W[i * PP + j] = -mu * v; });
   __syncthreads();
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
-    const int i = e / PP, j = e % PP;
-    C[e] = 0.5 * (T2[e] + T2[j * PP + i]);
-  }
+  mm_dense<PP / 16, LD, false, LD, false, true>(nb, Mf, b1, [&](int i, int j, double v) {
+    C[i * PP + j] = C[j * PP + i] = v;
+    b0[i * LD + j] = b0[j * LD + i] = v;
+  });
   __syncthreads();
   if (want_mc) {
-    wg_mm<PP>(Mc, false, C, false, small + S_MC * PP * PP);
+    mm_dense<PP / 16, LD, false, LD, false>(nb, Mf, b0, [&](int i, int j, double v) { MC[i * PP + j] = v; });
     __syncthreads();
   }
 }
