@@ -71,6 +71,10 @@ struct Dev {
   }
 };
 
+// Launch sequences of an iteration (launch_iteration): the full one; the short one; the full one
+// before a short one, which stops the launches after it when the short one could not follow.
+enum Sequence { SEQ_FULL, SEQ_LEAN, SEQ_FULL_LEAD, SEQUENCES };
+
 // Tall blocks, matrix values and per-solve state for one block precision.
 template <typename T>
 struct Engine {
@@ -85,8 +89,9 @@ struct Engine {
   float* P32 = nullptr;
   double* small = nullptr;
   Scalars* sc = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
+  // the captured iterations, by Sequence
+  hipGraph_t graph[SEQUENCES] = {};
+  hipGraphExec_t gexec[SEQUENCES] = {};
   bool explicit_grams = false;
   // the retraction pass also forms the next gradient (k_update_grad): the float64 engine of the
   // gradient-type methods with C and W carried by the recursion
@@ -112,9 +117,12 @@ struct Engine {
     return true;
   }
   void destroy_graph() {
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
-    gexec = nullptr; graph = nullptr;
+    for (int k = 0; k < SEQUENCES; ++k) {
+      if (gexec[k]) (void)hipGraphExecDestroy(gexec[k]);
+      if (graph[k]) (void)hipGraphDestroy(graph[k]);
+      gexec[k] = nullptr;
+      graph[k] = nullptr;
+    }
   }
 };
 
@@ -343,37 +351,63 @@ gsi_status init_state(gsi_ctx* h, Engine<T>& e, double tol, int max_iter, int hi
   return hip_check(h, hipGetLastError(), "init_state launch");
 }
 
+// The explicit A X, X^T A X of an iteration that asked for it (the kernels test the flag).
+template <typename T, int PP>
+void launch_refresh(gsi_ctx* h, Engine<T>& e, bool hold) {
+  const int64_t P2 = (int64_t)PP * PP;
+  {
+    PassTimer t(h, GSI_PASS_REFRESH);
+    spmm_op<T, PP>(h, e, e.X, e.X, e.Y, 2);
+    Kernels<T, PP>::gram(h->st, e.nb, e.n, e.X, e.X, e.Y, nullptr, e.sc, 2, h->partials);
+  }
+  reduce(h, e.nb, P2, P2, e.sc, 2);
+  PassTimer t(h, GSI_PASS_SMALL);
+  Small::after_refresh(h->st, PP, h->red, e.small, e.sc, hold);
+}
+
 // One iteration's launch sequence. Unfused: gradient pass and its bookkeeping, direction
 // pass, eigendecomposition of P^T P (second stream) beside the SpMM and its Gram pass, line
 // search, retraction, explicit A X when asked for. Fused (e.fused): the gradient pass at the
 // top runs only when the gradient is not current (the first iteration, after an explicit A X, a
 // void step or a host-side change of the state); the retraction pass forms the next gradient
 // and its partial sums, whose bookkeeping runs at the end of the iteration.
+//
+// SEQ_LEAN (fused only): the short sequence, without the kernels at the top and for the explicit A X
+// that return at once in almost every iteration: seven launches of 4 to 5 us each, gaps included
+// (a quarter of an iteration at n = 1024, p = 8). When one of them would have had work to do, the
+// bookkeeping at the end sets DONE_HOLD and run_until_done launches a full sequence.
 template <typename T>
-void launch_iteration(gsi_ctx* h, Engine<T>& e, double* hist) {
+void launch_iteration(gsi_ctx* h, Engine<T>& e, double* hist, Sequence seq = SEQ_FULL) {
+  const bool lean = seq == SEQ_LEAN;
   const int recompute = h->rax;
   const bool fused = e.fused;
   const int gcond = fused ? GRAD_PENDING : GRAD_ALWAYS;
+  // reduce the partials of a pass, or let the kernel that consumes them do it
+  auto reduced = [&](int nb, int64_t nv, int64_t max_from, int cond) {
+    if ((int64_t)nb * nv <= FOLD_MAX) return Partials{h->partials, nb};
+    reduce(h, nb, nv, max_from, e.sc, cond);
+    return Partials{};
+  };
   dispatch_pp<T>(e.PP, [&](auto PPc) {
     constexpr int PP = decltype(PPc)::value;
     const int64_t P2 = (int64_t)PP * PP;
-    {
-      PassTimer t(h, GSI_PASS_GRAD);
-      Kernels<T, PP>::grad(h->st, e.nb, e.n, e.X, e.Y, e.G0, e.G1, e.small, e.sc, h->partials, gcond);
-    }
-    reduce(h, e.nb, P2 + 3, P2 + 2, e.sc, fused ? GRAD_PENDING : 3);
-    {
+    if (!lean) {
+      {
+        PassTimer t(h, GSI_PASS_GRAD);
+        Kernels<T, PP>::grad(h->st, e.nb, e.n, e.X, e.Y, e.G0, e.G1, e.small, e.sc, h->partials, gcond);
+      }
+      const Partials f = reduced(e.nb, P2 + 3, P2 + 2, fused ? GRAD_PENDING : 3);
       PassTimer t(h, GSI_PASS_SMALL);
-      Small::after_grad(h->st, PP, h->red, e.small, e.sc, hist, gcond);
+      Small::after_grad(h->st, PP, h->red, e.small, e.sc, hist, gcond, f);
     }
     {
       PassTimer t(h, GSI_PASS_DIR);
       Kernels<T, PP>::dir(h->st, e.nb, e.n, e.X, e.G0, e.G1, e.P0, e.P1, e.small, e.sc, h->partials, e.P16, e.P32);
     }
-    reduce(h, e.nb, P2 + 1, P2 + 1, e.sc, 1);
     {
+      const Partials f = reduced(e.nb, P2 + 1, P2 + 1, 1);
       PassTimer t(h, GSI_PASS_SMALL);
-      Small::after_dir(h->st, PP, h->red, e.small, e.sc);
+      Small::after_dir(h->st, PP, h->red, e.small, e.sc, f);
     }
     // the eigendecomposition of P^T P needs only S: run it on the second stream while the
     // SpMM and its Gram pass run on the first
@@ -408,11 +442,11 @@ void launch_iteration(gsi_ctx* h, Engine<T>& e, double* hist) {
       PassTimer t(h, GSI_PASS_GRAM);
       Kernels<T, PP>::gram(h->st, h->nb_gram, e.n, e.P0, e.P1, e.Z, e.Y, e.sc, 1, h->partials);
     }
-    reduce(h, h->nb_gram, 2 * P2, 2 * P2, e.sc, 1);
+    const Partials gf = reduced(h->nb_gram, 2 * P2, 2 * P2, 1);
     if (!h->timing) (void)hipStreamWaitEvent(h->st, h->ev_join, 0);
     {
       PassTimer t(h, GSI_PASS_LINESEARCH);
-      Small::linesearch(h->st, PP, h->red, e.small, e.sc, hist, recompute, fused);
+      Small::linesearch(h->st, PP, h->red, e.small, e.sc, hist, recompute, fused, gf);
     }
     {
       PassTimer t(h, GSI_PASS_UPDATE);
@@ -427,42 +461,39 @@ void launch_iteration(gsi_ctx* h, Engine<T>& e, double* hist) {
       // the new gradient's bookkeeping, when the retraction formed it (the partials of the
       // explicit A X below go to other entries of the reduced vector: red is reused only
       // after this reduction has been consumed)
-      reduce(h, e.nb, P2 + 3, P2 + 2, e.sc, GRAD_AFTER_FUSED);
+      const Partials f = reduced(e.nb, P2 + 3, P2 + 2, GRAD_AFTER_FUSED);
       PassTimer t(h, GSI_PASS_SMALL);
-      Small::after_grad(h->st, PP, h->red, e.small, e.sc, hist, GRAD_AFTER_FUSED);
+      Small::after_grad(h->st, PP, h->red, e.small, e.sc, hist, lean ? GRAD_AFTER_LEAN : GRAD_AFTER_FUSED, f);
     }
+    if (lean) return;
     if (e.explicit_grams) {
       reduce(h, e.nb, 2 * P2, 2 * P2, e.sc, 1);
       PassTimer t(h, GSI_PASS_SMALL);
       Small::after_update_grams(h->st, PP, h->red, e.small, e.sc);
     }
-    {
-      PassTimer t(h, GSI_PASS_REFRESH);
-      spmm_op<T, PP>(h, e, e.X, e.X, e.Y, 2);
-      Kernels<T, PP>::gram(h->st, e.nb, e.n, e.X, e.X, e.Y, nullptr, e.sc, 2, h->partials);
-    }
-    reduce(h, e.nb, P2, P2, e.sc, 2);
-    {
-      PassTimer t(h, GSI_PASS_SMALL);
-      Small::after_refresh(h->st, PP, h->red, e.small, e.sc);
-    }
+    launch_refresh<T, PP>(h, e, seq == SEQ_FULL_LEAD);
   });
 }
 
+// count iterations, the first with the sequence `first`, the others with `rest`.
 template <typename T>
-gsi_status enqueue_iterations(gsi_ctx* h, Engine<T>& e, double* hist, int count) {
-  if (h->opt.use_graph && !h->timing) {
-    if (!e.gexec) {
-      GSI_TRY(hip_check(h, hipStreamBeginCapture(h->st, hipStreamCaptureModeThreadLocal), "begin capture"));
-      launch_iteration(h, e, hist);
-      hipError_t ce = hipStreamEndCapture(h->st, &e.graph);
-      GSI_TRY(hip_check(h, ce, "end capture"));
-      GSI_TRY(hip_check(h, hipGraphInstantiate(&e.gexec, e.graph, nullptr, nullptr, 0), "graph instantiate"));
+gsi_status enqueue_iterations(gsi_ctx* h, Engine<T>& e, double* hist, int count, Sequence first = SEQ_FULL,
+                              Sequence rest = SEQ_FULL) {
+  const bool graphs = h->opt.use_graph && !h->timing;
+  for (int i = 0; i < count; ++i) {
+    const Sequence q = i ? rest : first;
+    if (!graphs) {
+      launch_iteration(h, e, hist, q);
+      continue;
     }
-    for (int i = 0; i < count; ++i)
-      GSI_TRY(hip_check(h, hipGraphLaunch(e.gexec, h->st), "graph launch"));
-  } else {
-    for (int i = 0; i < count; ++i) launch_iteration(h, e, hist);
+    if (!e.gexec[q]) {
+      GSI_TRY(hip_check(h, hipStreamBeginCapture(h->st, hipStreamCaptureModeThreadLocal), "begin capture"));
+      launch_iteration(h, e, hist, q);
+      hipError_t ce = hipStreamEndCapture(h->st, &e.graph[q]);
+      GSI_TRY(hip_check(h, ce, "end capture"));
+      GSI_TRY(hip_check(h, hipGraphInstantiate(&e.gexec[q], e.graph[q], nullptr, nullptr, 0), "graph instantiate"));
+    }
+    GSI_TRY(hip_check(h, hipGraphLaunch(e.gexec[q], h->st), "graph launch"));
   }
   return hip_check(h, hipGetLastError(), "iteration launch");
 }
@@ -482,6 +513,11 @@ void reorthonormalize(gsi_ctx* h, Engine<T>& e) {
     Kernels<T, PP>::product(h->st, e.nb, e.n, e.X, e.X, e.small + S_M * PP * PP);
     Kernels<T, PP>::product(h->st, e.nb, e.n, e.Y, e.Y, e.small + S_M * PP * PP);
   });
+}
+
+gsi_status read_scalars(gsi_ctx* h, const Scalars* dsc, Scalars* out) {
+  GSI_TRY(hip_check(h, hipMemcpyAsync(out, dsc, sizeof(Scalars), hipMemcpyDeviceToHost, h->st), "scalars"));
+  return hip_check(h, hipStreamSynchronize(h->st), "scalars sync");
 }
 
 // Automatic choice between the A X recursion and RCG(+): one iteration to warm up, then
@@ -524,11 +560,31 @@ gsi_status run_until_done(gsi_ctx* h, Engine<T>& e, double* hist, Scalars* out, 
   if (h->rax_pending && !h->timing) GSI_TRY(choose_recompute(h, e, hist));
   // in timing mode poll every iteration so that no launch after convergence is timed
   const int every = h->timing ? 1 : (h->opt.check_every > 0 ? h->opt.check_every : 25);
+  // the short sequence after a full one from any state (per-pass timing and RCG(+), whose every
+  // iteration forms A X, keep to the full one)
+  const bool lean = e.fused && !h->rax && !h->timing;
+  bool full_first = true;
+  GSI_TRY(read_scalars(h, e.sc, out));
   for (;;) {
-    GSI_TRY(enqueue_iterations(h, e, hist, every));
+    // no more launches than the iteration cap leaves (and one for the stop test of an engine
+    // that makes it at the top of an iteration): those past it would return at once
+    const int left = h->opt.max_iter - out->k + (e.fused ? 0 : 1);
+    const int count = every < left ? every : (left > 1 ? left : 1);
+    GSI_TRY(lean ? enqueue_iterations(h, e, hist, count, full_first ? SEQ_FULL_LEAD : SEQ_LEAN, SEQ_LEAN)
+                 : enqueue_iterations(h, e, hist, count));
     GSI_TRY(hip_check(h, hipMemcpyAsync(out, e.sc, sizeof(Scalars), hipMemcpyDeviceToHost, h->st), "poll"));
     GSI_TRY(hip_check(h, hipStreamSynchronize(h->st), "iterate"));
     if (h->timing) collect_times(h);
+    full_first = false;
+    if (out->done == DONE_HOLD) {
+      // an explicit A X or the gradient's own pass is due
+      out->done = 0;
+      full_first = true;
+      GSI_TRY(hip_check(h, hipMemcpyAsync(&e.sc->done, &out->done, sizeof(int32_t), hipMemcpyHostToDevice, h->st),
+                        "resume"));
+      dispatch_pp<T>(e.PP, [&](auto PPc) { launch_refresh<T, decltype(PPc)::value>(h, e, false); });
+      continue;
+    }
     if (out->done == 4 && e.P32) {
       // the float32 copies of A and P set the attainable residual of this phase (their
       // rounding enters the A X recursion and the line-search Grams): continue with the
@@ -547,6 +603,7 @@ gsi_status run_until_done(gsi_ctx* h, Engine<T>& e, double* hist, Scalars* out, 
       out->stall_window = 0;
       out->restart_next = 1;
       out->grad_ready = 0;  // the gradient of the new A X is formed at the top of the next iteration
+      full_first = true;
       GSI_TRY(hip_check(h, hipMemcpyAsync(e.sc, out, sizeof(Scalars), hipMemcpyHostToDevice, h->st), "resume"));
       continue;
     }
@@ -563,17 +620,13 @@ gsi_status run_until_done(gsi_ctx* h, Engine<T>& e, double* hist, Scalars* out, 
       });
       out->done = 0;
       out->grad_ready = 0;
+      full_first = true;
       GSI_TRY(hip_check(h, hipMemcpyAsync(e.sc, out, sizeof(Scalars), hipMemcpyHostToDevice, h->st), "resume"));
       continue;
     }
     if (out->done) return GSI_OK;
     if (reorth) reorthonormalize(h, e);
   }
-}
-
-gsi_status read_scalars(gsi_ctx* h, const Scalars* dsc, Scalars* out) {
-  GSI_TRY(hip_check(h, hipMemcpyAsync(out, dsc, sizeof(Scalars), hipMemcpyDeviceToHost, h->st), "scalars"));
-  return hip_check(h, hipStreamSynchronize(h->st), "scalars sync");
 }
 
 // Switch a mixed-precision solve to the float64 phase: X64 <- X32, Cholesky QR in
@@ -751,9 +804,12 @@ gsi_status si_iterate(gsi_ctx* h, int count) {
 }
 
 gsi_status start(gsi_ctx* h, const double* X0) {
-  // pack X0 into the active engine, orthonormalize, form A X and reset the state
-  h->e64.destroy_graph();
-  h->e32.destroy_graph();
+  // pack X0 into the active engine, orthonormalize, form A X and reset the state. The captured
+  // iterations hold buffers and launch shapes only, none of a solve's state, so they are kept
+  // (capturing and instantiating them took 0.4 ms a solve) unless what they were captured with
+  // changes: the float32 SpMM of a mixed solve, or an automatic choice of the A X update.
+  if (h->e64.P32 || h->opt.recompute_ax < 0) h->e64.destroy_graph();
+  if (h->opt.recompute_ax < 0) h->e32.destroy_graph();
   h->e64.vals32 = nullptr;
   h->e64.P32 = nullptr;
   h->si_k = h->si_spmm = h->si_done = 0;
@@ -909,11 +965,18 @@ gsi_status create_impl(gsi_handle* out, const gsi_csr* A, const gsi_stencil* S, 
   // two workgroups per CU for the streaming passes (the register-limited residency of the
   // float64 passes at p = 64): more workgroups did not move the passes and only enlarge the
   // per-workgroup partial sums the reductions read (measured at n = 128^3, p = 64)
-  h->nb = (int)(ntiles < 2 * (int64_t)ncu ? ntiles : 2 * (int64_t)ncu);
+  // no more of them than give the same largest share of the tiles: 274 instead of 512 for the
+  // 547 tiles of the 35 x 40 x 25 grid, two tiles each either way and half the partial sums
+  auto spread = [&](int64_t most) {
+    const int64_t share = (ntiles + most - 1) / most;
+    return (int)((ntiles + share - 1) / share);
+  };
+  h->nb = spread(2 * (int64_t)ncu);
   // the iteration's P^T A P / P^T A X pass on four workgroups per CU: alone it ran 835 -> 730 us
   // (128^3, p = 64); inside the solve the pass itself stays near 0.70 ms but the retraction pass
   // after it runs 1.78 -> 1.72 ms (solve 12.47 -> 12.34 s, two builds on one GPU, two solves each)
-  h->nb_gram = (int)(ntiles < 4 * (int64_t)ncu ? ntiles : 4 * (int64_t)ncu);
+  // (below four tiles to a workgroup that way, its partial sums outweigh it: two per CU)
+  h->nb_gram = spread((ntiles >= 16 * (int64_t)ncu ? 4 : 2) * (int64_t)ncu);
   h->hist_cap = opt->max_iter + 2;
   Dev& d = h->dev;
   if (A) {
@@ -1207,7 +1270,6 @@ gsi_status gsi_residuals(gsi_handle h, double* ritz, double* col_res, double* rh
                     "colres"));
   GSI_TRY(hip_check(h, hipStreamSynchronize(h->st), "residuals"));
   // restart the iteration from the rotated basis
-  e.destroy_graph();
   {
     Scalars s;
     GSI_TRY(read_scalars(h, e.sc, &s));

@@ -15,8 +15,20 @@ enum class Pass { Grad, Dir, Update, UpdateGrams, UpdateGrad, Spmm, SpmmPlain, G
 // only when the gradient is not current (the solve's first iteration, after an explicit A X, a
 // void step or a host-side change of the state). AFTER_FUSED: at the end of an iteration of the
 // fused sequence, when its retraction pass formed the gradient (a step was taken and A X was
-// carried by the recursion).
-enum GradCond { GRAD_ALWAYS = 0, GRAD_PENDING = 4, GRAD_AFTER_FUSED = 5 };
+// carried by the recursion). AFTER_LEAN: AFTER_FUSED in the short sequence, which stops the
+// launches that follow it (DONE_HOLD) when the gradient was not formed.
+enum GradCond { GRAD_ALWAYS = 0, GRAD_PENDING = 4, GRAD_AFTER_FUSED = 5, GRAD_AFTER_LEAN = 6 };
+
+// Partial sums that a single-workgroup kernel reduces itself (nb > 0) instead of reading the
+// result of launch_reduce.
+struct Partials {
+  const double* p = nullptr;
+  int nb = 0;
+};
+// Most partial values (workgroups x values) for that: the workgroup reads them at some 50 GB/s,
+// a launch and its gap cost 5 us. 16 workgroups of 515 values (n = 1024, p = 8) take 1 us more
+// in the consumer; 35 x 40 x 25 at p = 16 has 512 workgroups, 1 MB.
+constexpr int64_t FOLD_MAX = 16384;
 
 template <typename T, int PP>
 int lds_bytes(Pass pass);
@@ -96,20 +108,21 @@ struct Small {
   static hipError_t init();
   // after the gradient pass: rho, history, stop test, Polak-Ribiere beta, K + beta W; marks the
   // gradient current (grad_ready). cond (GradCond): when it runs
-  static void after_grad(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, double* hist,
-                         int cond = 0);
+  static void after_grad(hipStream_t st, int PP, double* red, double* small, Scalars* sc, double* hist, int cond = 0,
+                         Partials fold = {});
   // after the direction pass: S = P^T P, descent test
-  static void after_dir(hipStream_t st, int PP, const double* red, double* small, Scalars* sc);
+  static void after_dir(hipStream_t st, int PP, double* red, double* small, Scalars* sc, Partials fold = {});
   // eigendecomposition of P^T P (warm-started); independent of the SpMM
   static void eig(hipStream_t st, int PP, double* small, Scalars* sc);
   // after the SpMM: line-search diagonals, Get_Mu, M, next C and W (and M C_next for the fused
   // retraction-gradient pass); marks the gradient stale (the step changes X, or is void)
-  static void linesearch(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, double* hist,
-                         int recompute_ax, bool want_mc = false);
+  static void linesearch(hipStream_t st, int PP, double* red, double* small, Scalars* sc, double* hist,
+                         int recompute_ax, bool want_mc = false, Partials fold = {});
   // after an update with Gram epilogue: C = sym(X^T Y), W = X^T P (explicit)
   static void after_update_grams(hipStream_t st, int PP, const double* red, double* small, Scalars* sc);
-  // after an explicit A X: C = sym(X^T Y) (runs only when sc->refresh)
-  static void after_refresh(hipStream_t st, int PP, const double* red, double* small, Scalars* sc);
+  // after an explicit A X: C = sym(X^T Y) (only when sc->refresh, which it clears); hold: stops the
+  // launches that follow (DONE_HOLD) unless the gradient is current
+  static void after_refresh(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, bool hold = false);
   // Cholesky factor of the reduced Gram (PP x PP): writes R^{-1} into small[S_M]; flag on failure
   static void chol_inv(hipStream_t st, int PP, int p, const double* red, double* small, int* flag);
   // after a Cholesky QR pass with R^{-1} in small[S_M]: C <- R^{-T} C R^{-1}, W <- R^{-T} W;

@@ -1812,42 +1812,50 @@ __global__ __launch_bounds__(WG) void k_colres(int64_t n, const T* __restrict__ 
 
 // ---------------------------------------------------------------- reduction
 // out[v] = sum_b partials[b * nv + v] for v < max_from, max over b otherwise. A workgroup
-// covers 64 consecutive values with 4 slices of the nb partials each (b = q, q+4, ...);
-// the slices are combined in a fixed order, so the result is deterministic.
+// covers RVALS consecutive values with RSLICES slices of the nb partials each (b = q, q +
+// RSLICES, ...); the slices are combined in a fixed order, so the result is deterministic. What
+// one CU can read bounds it: 64 values to a workgroup made 17 workgroups for nv = 1027 and took
+// 8.1 us at nb = 512 (4.2 MB), 16 values 4.8 us.
 // cond: 0 always; 1 skip when the solve is done or the step is null; 2 run only when an
 // explicit A X refresh was requested; 3 skip when the solve is done.
-__global__ __launch_bounds__(WG) void k_reduce(const double* __restrict__ partials, int nb, int64_t nv,
-                                               int64_t max_from, double* __restrict__ out,
-                                               const Scalars* __restrict__ sc, int cond) {
+constexpr int RVALS = 16, RSLICES = 64;
+__global__ __launch_bounds__(RVALS * RSLICES) void k_reduce(const double* __restrict__ partials, int nb, int64_t nv,
+                                                            int64_t max_from, double* __restrict__ out,
+                                                            const Scalars* __restrict__ sc, int cond) {
   if (cond == 1 && (sc->done || sc->null_step)) return;
   if (cond == 2 && (sc->done || sc->null_step || !sc->refresh)) return;
   if (cond == 3 && sc->done) return;
   if (cond == GRAD_PENDING && (sc->done || sc->grad_ready)) return;
   if (cond == GRAD_AFTER_FUSED && (sc->done || sc->null_step || sc->refresh || sc->grad_ready)) return;
-  __shared__ double part[4][64];
-  const int q = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int64_t v = (int64_t)blockIdx.x * 64 + l;
+  __shared__ double part[RSLICES][RVALS];
+  const int q = threadIdx.x / RVALS, l = threadIdx.x % RVALS;
+  const int64_t v = (int64_t)blockIdx.x * RVALS + l;
   const bool use_max = v >= max_from;
+  auto fold = [&](double x, double y) { return use_max ? fmax(x, y) : x + y; };
   double s = 0.0;
   if (v < nv) {
     int b = q;
-    for (; b + 28 < nb; b += 32) {
+    for (; b + 7 * RSLICES < nb; b += 8 * RSLICES) {
       double x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) x[u] = partials[(int64_t)(b + 4 * u) * nv + v];
+      for (int u = 0; u < 8; ++u) x[u] = partials[(int64_t)(b + RSLICES * u) * nv + v];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) s = use_max ? fmax(s, x[u]) : s + x[u];
+      for (int u = 0; u < 8; ++u) s = fold(s, x[u]);
     }
-    for (; b < nb; b += 4) {
-      const double x = partials[(int64_t)b * nv + v];
-      s = use_max ? fmax(s, x) : s + x;
-    }
+    for (; b < nb; b += RSLICES) s = fold(s, partials[(int64_t)b * nv + v]);
   }
   part[q][l] = s;
   __syncthreads();
+  if (q < 8) {
+#pragma unroll
+    for (int k = 1; k < RSLICES / 8; ++k) s = fold(s, part[q + 8 * k][l]);
+    part[q][l] = s;
+  }
+  __syncthreads();
   if (q == 0 && v < nv) {
-    out[v] = use_max ? fmax(fmax(part[0][l], part[1][l]), fmax(part[2][l], part[3][l]))
-                     : (part[0][l] + part[1][l]) + (part[2][l] + part[3][l]);
+#pragma unroll
+    for (int k = 1; k < 8; ++k) s = fold(s, part[k][l]);
+    out[v] = s;
   }
 }
 
@@ -2161,8 +2169,8 @@ hipError_t Kernels<T, PP>::init() {
 
 void launch_reduce(hipStream_t st, const double* partials, int nb, int64_t nv, int64_t max_from, double* out,
                    const Scalars* sc, int cond) {
-  const int blocks = (int)((nv + 63) / 64);
-  hipLaunchKernelGGL(k_reduce, dim3(blocks), dim3(WG), 0, st, partials, nb, nv, max_from, out, sc, cond);
+  const int blocks = (int)((nv + RVALS - 1) / RVALS);
+  hipLaunchKernelGGL(k_reduce, dim3(blocks), dim3(RVALS * RSLICES), 0, st, partials, nb, nv, max_from, out, sc, cond);
 }
 
 // small[slot] = sym(red) (PP x PP), the projected matrix after an explicit Gram.

@@ -17,11 +17,35 @@ namespace gsi {
 
 // ---------------------------------------------------------------- kernels
 
-__global__ __launch_bounds__(WG) void k_after_grad(int PP, const double* __restrict__ red, double* __restrict__ small,
-                                                   Scalars* __restrict__ sc, double* __restrict__ hist, int cond) {
+// The reduction of a pass's partial sums (see k_reduce) by the single workgroup that consumes
+// them, when there are few (FOLD_MAX): the reduction's launch is saved. Ends with a barrier.
+__device__ __forceinline__ void fold_partials(const double* __restrict__ partials, int nb, int nv, int max_from,
+                                              double* __restrict__ red) {
+  for (int v = threadIdx.x; v < nv; v += blockDim.x) {
+    const bool use_max = v >= max_from;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = 0; b < nb; ++b) {
+      const double x = partials[(int64_t)b * nv + v];
+      s = use_max ? fmax(s, x) : s + x;
+    }
+    red[v] = s;
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(WG) void k_after_grad(int PP, double* red, double* __restrict__ small,
+                                                   Scalars* __restrict__ sc, double* __restrict__ hist, int cond,
+                                                   Partials fold) {
   if (sc->done) return;
   if (cond == GRAD_PENDING && sc->grad_ready) return;
-  if (cond == GRAD_AFTER_FUSED && (sc->null_step || sc->refresh || sc->grad_ready)) return;
+  if (cond >= GRAD_AFTER_FUSED && (sc->null_step || sc->refresh || sc->grad_ready)) {
+    // the short sequence has no kernels for what comes next (the gradient's own pass, an
+    // explicit A X): its remaining launches return at once and the host runs the full one
+    if (cond == GRAD_AFTER_LEAN && threadIdx.x == 0) sc->done = DONE_HOLD;
+    return;
+  }
+  if (fold.nb) fold_partials(fold.p, fold.nb, PP * PP + 3, PP * PP + 2, red);
   __shared__ double sbeta, sphi;
   // the scalars and the trace of C are read by all threads at once (one round trip) and the
   // sequential decisions below work on the LDS copy: dependent global reads one after the
@@ -101,9 +125,10 @@ __global__ __launch_bounds__(WG) void k_after_grad(int PP, const double* __restr
   }
 }
 
-__global__ __launch_bounds__(WG) void k_after_dir(int PP, const double* __restrict__ red, double* __restrict__ small,
-                                                  Scalars* __restrict__ sc) {
+__global__ __launch_bounds__(WG) void k_after_dir(int PP, double* red, double* __restrict__ small,
+                                                  Scalars* __restrict__ sc, Partials fold) {
   if (sc->done) return;
+  if (fold.nb) fold_partials(fold.p, fold.nb, PP * PP + 1, PP * PP + 1, red);
   double* S = small + S_S * PP * PP;
   // lane j of each wave, rows dealt to the waves (no division by the runtime PP)
   for (int i = threadIdx.x >> 6; i < PP; i += blockDim.x >> 6)
@@ -143,9 +168,9 @@ __global__ __launch_bounds__(dense_threads(PP)) void k_eig(double* __restrict__ 
 // Line search and retraction factor (see linesearch_dev), one workgroup; red holds the
 // reduced Grams P^T A P, P^T A X of the SpMM.
 template <int PP>
-__global__ __launch_bounds__(dense_threads(PP)) void k_linesearch(const double* __restrict__ red, double* __restrict__ small,
-                                                   Scalars* __restrict__ sc, double* __restrict__ hist,
-                                                   int recompute_ax, int want_mc) {
+__global__ __launch_bounds__(dense_threads(PP)) void k_linesearch(double* red, double* __restrict__ small, Scalars* __restrict__ sc,
+                                                   double* __restrict__ hist, int recompute_ax, int want_mc,
+                                                   Partials fold) {
   if (sc->done || sc->null_step) return;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ Terms terms;
@@ -155,6 +180,7 @@ __global__ __launch_bounds__(dense_threads(PP)) void k_linesearch(const double* 
   __shared__ Scalars ls;
   for (int i = threadIdx.x; i < (int)(sizeof(Scalars) / 4); i += blockDim.x)
     reinterpret_cast<int32_t*>(&ls)[i] = reinterpret_cast<const int32_t*>(sc)[i];
+  if (fold.nb) fold_partials(fold.p, fold.nb, 2 * PP * PP, 2 * PP * PP, red);
   __syncthreads();
   linesearch_dev<PP>(red, red + PP * PP, small, ls.p, reinterpret_cast<double*>(lds_raw), terms, &smu, &sok, &sevals,
                      &sbmax, want_mc != 0);
@@ -197,13 +223,22 @@ __global__ __launch_bounds__(WG) void k_after_update_grams(int PP, const double*
   }
 }
 
+// hold: the next iteration is a short one, which needs the current gradient.
 __global__ __launch_bounds__(WG) void k_after_refresh(int PP, const double* __restrict__ red,
-                                                      double* __restrict__ small, Scalars* __restrict__ sc) {
-  if (sc->done || sc->null_step || !sc->refresh) return;
-  double* C = small + S_C * PP * PP;
-  for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
-    const int i = e / PP, j = e % PP;
-    C[e] = 0.5 * (red[i * PP + j] + red[j * PP + i]);
+                                                      double* __restrict__ small, Scalars* __restrict__ sc, int hold) {
+  if (sc->done) return;
+  const bool formed = !sc->null_step && sc->refresh;
+  __syncthreads();
+  if (formed) {
+    double* C = small + S_C * PP * PP;
+    for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
+      const int i = e / PP, j = e % PP;
+      C[e] = 0.5 * (red[i * PP + j] + red[j * PP + i]);
+    }
+  }
+  if (threadIdx.x == 0) {
+    if (formed) sc->refresh = 0;
+    if (hold && !sc->grad_ready) sc->done = DONE_HOLD;
   }
 }
 
@@ -328,11 +363,12 @@ hipError_t Small::init() {
   if (e == hipSuccess) e = init_pp<128>();
   return e;
 }
-void Small::after_grad(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, double* hist, int cond) {
-  hipLaunchKernelGGL(k_after_grad, dim3(1), dim3(WG), 0, st, PP, red, small, sc, hist, cond);
+void Small::after_grad(hipStream_t st, int PP, double* red, double* small, Scalars* sc, double* hist, int cond,
+                       Partials fold) {
+  hipLaunchKernelGGL(k_after_grad, dim3(1), dim3(WG), 0, st, PP, red, small, sc, hist, cond, fold);
 }
-void Small::after_dir(hipStream_t st, int PP, const double* red, double* small, Scalars* sc) {
-  hipLaunchKernelGGL(k_after_dir, dim3(1), dim3(WG), 0, st, PP, red, small, sc);
+void Small::after_dir(hipStream_t st, int PP, double* red, double* small, Scalars* sc, Partials fold) {
+  hipLaunchKernelGGL(k_after_dir, dim3(1), dim3(WG), 0, st, PP, red, small, sc, fold);
 }
 void Small::eig(hipStream_t st, int PP, double* small, Scalars* sc) {
   switch (PP) {
@@ -342,12 +378,12 @@ void Small::eig(hipStream_t st, int PP, double* small, Scalars* sc) {
     case 128: k_eig<128><<<1, dense_threads(128), eig_bytes(128), st>>>(small, sc); break;
   }
 }
-void Small::linesearch(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, double* hist,
-                       int recompute_ax, bool want_mc) {
+void Small::linesearch(hipStream_t st, int PP, double* red, double* small, Scalars* sc, double* hist,
+                       int recompute_ax, bool want_mc, Partials fold) {
   const int mc = want_mc ? 1 : 0;
   auto go = [&](auto P) {
     constexpr int pp = decltype(P)::value;
-    k_linesearch<pp><<<1, dense_threads(pp), linesearch_bytes(pp), st>>>(red, small, sc, hist, recompute_ax, mc);
+    k_linesearch<pp><<<1, dense_threads(pp), linesearch_bytes(pp), st>>>(red, small, sc, hist, recompute_ax, mc, fold);
   };
   switch (PP) {
     case 16: go(std::integral_constant<int, 16>()); break;
@@ -359,8 +395,8 @@ void Small::linesearch(hipStream_t st, int PP, const double* red, double* small,
 void Small::after_update_grams(hipStream_t st, int PP, const double* red, double* small, Scalars* sc) {
   hipLaunchKernelGGL(k_after_update_grams, dim3(1), dim3(WG), 0, st, PP, red, small, sc);
 }
-void Small::after_refresh(hipStream_t st, int PP, const double* red, double* small, Scalars* sc) {
-  hipLaunchKernelGGL(k_after_refresh, dim3(1), dim3(WG), 0, st, PP, red, small, sc);
+void Small::after_refresh(hipStream_t st, int PP, const double* red, double* small, Scalars* sc, bool hold) {
+  hipLaunchKernelGGL(k_after_refresh, dim3(1), dim3(WG), 0, st, PP, red, small, sc, hold ? 1 : 0);
 }
 void Small::chol_inv(hipStream_t st, int PP, int p, const double* red, double* small, int* flag) {
   switch (PP) {

@@ -8,6 +8,9 @@ namespace gsi {
 // History fields per recorded iterate.
 enum { H_RHO = 0, H_PHI, H_MU, H_BETA, H_GINF, H_FIELDS };
 
+// done: the launches of the short iteration sequence wait for a full one from the host
+constexpr int32_t DONE_HOLD = 6;
+
 // Scalars, flags and counters; one instance in device memory per solve.
 struct Scalars {
   double gg;        // <G, G>
@@ -21,7 +24,7 @@ struct Scalars {
   double tol;
   double sqrt_p;
   int32_t k;            // accepted iterations
-  int32_t done;         // 0 running, 1 converged, 2 max_iter, 3 breakdown
+  int32_t done;         // 0 running, 1 converged, 2 max_iter, 3 breakdown, 4 stagnation, DONE_HOLD
   int32_t restart_next; // next direction is the projected gradient
   int32_t null_step;    // current iteration takes no step
   int32_t restart;      // current direction is a restart
