@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "../../include/fno.h"
+#include "gsi_dense_dev.h"
 #include "gsi_device.h"
 
 namespace fno {
@@ -115,14 +116,18 @@ struct PQtSmall {
   int R, Cc;  // both <= 32
   int64_t K;  // multiple of 16
   int splits;
-  float* part;  // [batch][split][32 x 32]
+  float* part;  // [batch][split][PART]
 };
 
-// Partial P_b Q_b^T over the split's share of K: grid (splits, batch). Every wave takes every
-// fourth 16-wide step of the share and keeps all four 16 x 16 blocks; the waves' sums are
-// added in wave order in LDS.
+// Values of a partial: 32 x 32, then the 32 row sums of P.
+constexpr int PART = 1024 + 32;
+
+// Partial P_b Q_b^T, and the row sums of P_b, over the split's share of K: grid (splits, batch).
+// Every wave takes every fourth 16-wide step of the share and keeps all four 16 x 16 blocks; the
+// waves' sums are added in wave order in LDS. The row sums (a bias gradient beside its weight
+// gradient) ride on the rows already loaded: a product with ones, one more MFMA per 16 rows.
 __global__ __launch_bounds__(WG) void k_pqt_small(PQtSmall a) {
-  __shared__ float red[32 * 32];
+  __shared__ float red[PART];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
   const int s = blockIdx.x, b = blockIdx.y;
   const int64_t nk = a.K / 16;
@@ -135,13 +140,16 @@ __global__ __launch_bounds__(WG) void k_pqt_small(PQtSmall a) {
   const float* q0 = Q + (qok0 ? c : 0) * a.ldq + 4 * g;
   const float* q1 = Q + (qok1 ? 16 + c : 0) * a.ldq + 4 * g;
   const f4 z = {0.f, 0.f, 0.f, 0.f};
-  f4 acc[2][2] = {{z, z}, {z, z}};
+  f4 acc[2][2] = {{z, z}, {z, z}}, sum[2] = {z, z};
+#pragma unroll 2
   for (int64_t kk = k_lo + w; kk < k_hi; kk += 4) {
     const int64_t k0 = kk * 16;
     const f4 a0 = pok0 ? ld4(p0 + k0) : z, a1 = pok1 ? ld4(p1 + k0) : z;
     const f4 b0 = qok0 ? ld4(q0 + k0) : z, b1 = qok1 ? ld4(q1 + k0) : z;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+      sum[0] = mfma(a0[q], 1.f, sum[0]);
+      sum[1] = mfma(a1[q], 1.f, sum[1]);
       acc[0][0] = mfma(a0[q], b0[q], acc[0][0]);
       acc[0][1] = mfma(a0[q], b1[q], acc[0][1]);
       acc[1][0] = mfma(a1[q], b0[q], acc[1][0]);
@@ -159,24 +167,48 @@ __global__ __launch_bounds__(WG) void k_pqt_small(PQtSmall a) {
             const int e = (16 * rb + 4 * g + r) * 32 + 16 * cb + c;
             red[e] = (ww ? red[e] : 0.f) + acc[rb][cb][r];
           }
+      if (c == 0)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int e = 1024 + 16 * rb + 4 * g + r;
+            red[e] = (ww ? red[e] : 0.f) + sum[rb][r];
+          }
     }
     __syncthreads();
   }
-  float* out = a.part + ((int64_t)b * a.splits + s) * 1024;
-  for (int e = threadIdx.x; e < 1024; e += WG) gst(out + e, red[e]);
+  float* out = a.part + ((int64_t)b * a.splits + s) * PART;
+  for (int e = threadIdx.x; e < PART; e += WG) gst(out + e, red[e]);
 }
 
-// out[gr][r][c] (at gr so_g + r ldo + c) = alpha * sum of the group's partials in order.
+// out[gr][r][c] (at gr so_g + r ldo + c) = alpha * sum of the group's partials, and, with bias
+// given, bias[r] = alpha * the sum of the row sums. A workgroup takes 16 entries, 16 lanes each a
+// share of the partials (16 entries x 4 bytes of a partial are contiguous), and adds the shares
+// in a fixed order: one thread per entry, adding up to 512 partials one load after the other on
+// two CUs, took 64 us a gradient, 12 times a training step; now 5 us.
+constexpr int SUM_E = 16, SUM_S = 16;
 template <typename TO>
-__global__ void k_sum_parts(const float* part, int per_group, int groups, int R, int Cc, TO* out, int64_t so_g,
-                            int ldo, float alpha) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int gr = blockIdx.y;
-  if (e >= R * Cc || gr >= groups) return;
-  const int r = e / Cc, c = e % Cc;
+__global__ __launch_bounds__(SUM_E * SUM_S) void k_sum_parts(const float* part, int per_group, int R, int Cc, TO* out,
+                                                             int64_t so_g, int ldo, float alpha, TO* bias) {
+  __shared__ double red[SUM_S][SUM_E];
+  const int x = threadIdx.x % SUM_E, q = threadIdx.x / SUM_E, gr = blockIdx.y;
+  const int e = blockIdx.x * SUM_E + x;  // rows of 32: the matrix, then the row sums
+  const int r = e >> 5, c = e & 31;
+  const bool sums = e >= 1024;
+  const bool ok = sums ? bias && c < R : r < R && c < Cc;
   double acc = 0.0;
-  for (int j = 0; j < per_group; ++j) acc += (double)gld(part + ((int64_t)gr * per_group + j) * 1024 + r * 32 + c);
-  gst(out + gr * so_g + r * ldo + c, (TO)(alpha * acc));
+  if (ok) {
+    const float* p = part + (int64_t)gr * per_group * PART + e;
+#pragma unroll 4
+    for (int j = q; j < per_group; j += SUM_S) acc += (double)gld(p + (int64_t)j * PART);
+  }
+  red[q][x] = acc;
+  __syncthreads();
+  if (q || !ok) return;
+  for (int k = 1; k < SUM_S; ++k) acc += red[k][x];
+  if (sums) gst(bias + c, (TO)(alpha * acc));
+  else gst(out + gr * so_g + r * ldo + c, (TO)(alpha * acc));
 }
 
 // ---------------------------------------------------------------- pointwise kernels
@@ -297,87 +329,51 @@ __global__ void k_mix_wgrad(const float* dVh, const float* Uh, float* dR, int B,
 
 // ---------------------------------------------------------------- loss
 
-// One workgroup per sample: G = Y^T Y, Bm = X*^T Y (float64, rows of 32). Cholesky of G,
-// Gi = G^-1, M = Bm^T Bm, loss = p - Tr(Gi M), and the coefficients of the gradient
-// dLoss/dY = scale (Y Kc - X* Ec) with Kc = Gi M Gi, Ec = Bm Gi, scale = 2 / batch.
+// One workgroup per sample: G = Y^T Y, Bm = X*^T Y (float64, rows of 32). Cholesky of G = L L^T,
+// with Li = L^-1, F = Bm Li^T: loss = p - |F|_F^2, and the coefficients of the gradient
+// dLoss/dY = scale (Y Kc - X* Ec) with Ec = Bm G^-1 = F Li and Kc = Ec^T Ec, scale = 2 / batch. The
+// factorization and the products are the p x p routines of the eigensolver (float64 MFMA): a
+// serial Cholesky by one thread took 550 us.
 __global__ __launch_bounds__(WG) void k_loss_small(const double* G, const double* Bm, int p, double scale,
                                                    double* loss, float* Kc, float* Ec, int* bad) {
-  __shared__ double L[32 * 33], Li[32 * 33], Gi[32 * 33], Ms[32 * 33], T[32 * 33], Bs[32 * 33];
+  constexpr int PP = 32, NB = PP / 16, LD = gsi::DLD<PP>;
+  __shared__ double L[PP * LD], M[PP * LD], Bs[PP * LD], F[PP * LD], E[PP * LD];
+  __shared__ double part[WG / 64];
   __shared__ int sbad;
-  const int b = blockIdx.x, t = threadIdx.x;
+  const int b = blockIdx.x, t = threadIdx.x, nb = (p + 15) >> 4, m = 16 * nb;
   const double* Gb = G + (int64_t)b * 1024;
   const double* Bb = Bm + (int64_t)b * 1024;
-  for (int e = t; e < p * p; e += WG) {
-    const int i = e / p, j = e % p;
-    L[i * 33 + j] = 0.5 * (Gb[i * 32 + j] + Gb[j * 32 + i]);
-    Bs[i * 33 + j] = Bb[i * 32 + j];
-    Li[i * 33 + j] = 0.0;
-  }
-  if (t == 0) sbad = 0;
+  gsi::fill_dense(m, L, LD, [&](int i, int j) { return i < p && j < p ? 0.5 * (Gb[i * 32 + j] + Gb[j * 32 + i]) : 0.0; });
+  gsi::fill_dense(m, Bs, LD, [&](int i, int j) { return i < p && j < p ? Bb[i * 32 + j] : 0.0; });
   __syncthreads();
-  if (t == 0) {
-    // Cholesky (lower) and the inverse of L, serially: p <= 32
-    for (int j = 0; j < p && !sbad; ++j) {
-      double d = L[j * 33 + j];
-      for (int k = 0; k < j; ++k) d -= L[j * 33 + k] * L[j * 33 + k];
-      if (!(d > 0.0) || !isfinite(d)) { sbad = 1; break; }
-      const double ljj = sqrt(d);
-      L[j * 33 + j] = ljj;
-      for (int i = j + 1; i < p; ++i) {
-        double s = L[i * 33 + j];
-        for (int k = 0; k < j; ++k) s -= L[i * 33 + k] * L[j * 33 + k];
-        L[i * 33 + j] = s / ljj;
-      }
-    }
-    if (!sbad)
-      for (int cidx = 0; cidx < p; ++cidx)
-        for (int i = cidx; i < p; ++i) {
-          double s = (i == cidx) ? 1.0 : 0.0;
-          for (int k = cidx; k < i; ++k) s -= L[i * 33 + k] * Li[k * 33 + cidx];
-          Li[i * 33 + cidx] = s / L[i * 33 + i];
-        }
-  }
+  const bool low = gsi::chol_lds<PP, false>(p, L, 0.0);
+  if (t == 0) sbad = low;
   __syncthreads();
+  float* Kb = Kc + (int64_t)b * 1024;
+  float* Eb = Ec + (int64_t)b * 1024;
+  for (int e = t; e < 1024; e += WG) Kb[e] = Eb[e] = 0.f;
   if (sbad) {
     if (t == 0) { loss[b] = NAN; atomicExch(bad, 1); }
-    for (int e = t; e < 1024; e += WG) { Kc[(int64_t)b * 1024 + e] = 0.f; Ec[(int64_t)b * 1024 + e] = 0.f; }
     return;
   }
-  // Gi = Li^T Li ; M = Bm^T Bm
-  for (int e = t; e < p * p; e += WG) {
-    const int i = e / p, j = e % p;
-    double s = 0.0, m = 0.0;
-    for (int k = (i > j ? i : j); k < p; ++k) s += Li[k * 33 + i] * Li[k * 33 + j];
-    for (int k = 0; k < p; ++k) m += Bs[k * 33 + i] * Bs[k * 33 + j];
-    Gi[i * 33 + j] = s;
-    Ms[i * 33 + j] = m;
-  }
+  gsi::inv_chol<PP>(p, L, M, LD);  // M = Li^T
   __syncthreads();
-  // T = Gi M
-  for (int e = t; e < p * p; e += WG) {
-    const int i = e / p, j = e % p;
-    double s = 0.0;
-    for (int k = 0; k < p; ++k) s += Gi[i * 33 + k] * Ms[k * 33 + j];
-    T[i * 33 + j] = s;
-  }
+  gsi::mm_dense<NB, LD, false, LD, false>(nb, Bs, M, [&](int i, int j, double v) { F[i * LD + j] = v; });
   __syncthreads();
-  if (t == 0) {
-    double tr = 0.0;
-    for (int i = 0; i < p; ++i) tr += T[i * 33 + i];
-    loss[b] = (double)p - tr;
+  gsi::mm_dense<NB, LD, false, LD, true>(nb, F, M, [&](int i, int j, double v) {
+    E[i * LD + j] = v;
+    Eb[i * 32 + j] = (float)(scale * v);
+  });
+  double s = 0.0;
+  for (int e = t; e < m * m; e += WG) {
+    const double f = F[e / m * LD + e % m];
+    s = fma(f, f, s);
   }
-  // Kc = T Gi, Ec = Bm Gi (row index a' of the sum, column a of dY)
-  for (int e = t; e < 1024; e += WG) {
-    const int i = e / 32, j = e % 32;
-    double kv = 0.0, ev = 0.0;
-    if (i < p && j < p)
-      for (int k = 0; k < p; ++k) {
-        kv += T[i * 33 + k] * Gi[k * 33 + j];
-        ev += Bs[i * 33 + k] * Gi[k * 33 + j];
-      }
-    Kc[(int64_t)b * 1024 + e] = (float)(scale * kv);
-    Ec[(int64_t)b * 1024 + e] = (float)(scale * ev);
-  }
+  s = gsi::wave_sum(s);
+  if ((t & 63) == 0) part[t >> 6] = s;
+  __syncthreads();
+  if (t == 0) loss[b] = (double)p - (((part[0] + part[1]) + part[2]) + part[3]);
+  gsi::mm_dense<NB, LD, true, LD, false>(nb, E, E, [&](int i, int j, double v) { Kb[i * 32 + j] = (float)(scale * v); });
 }
 
 // dY[b][a][i] = sum_a' Kc[a'][a] Y[b][a'][i] - Ec[a'][a] X[b][a'][i]. Thread per (sample, node).
@@ -480,7 +476,7 @@ struct fno_net {
   float *params = nullptr, *grad = nullptr, *m1 = nullptr, *m2 = nullptr;
   uint16_t* wbf = nullptr;  // bfloat16 working copy of params (bf16_weights), else null
   int64_t step = 0;
-  float *S = nullptr, *St = nullptr, *ones = nullptr, *prior = nullptr;
+  float *S = nullptr, *St = nullptr, *prior = nullptr;
   float *In = nullptr, *Y = nullptr, *Xc = nullptr, *dY = nullptr, *dPre = nullptr, *dUa = nullptr, *dUb = nullptr;
   float *Wt = nullptr, *Vh = nullptr, *dUh = nullptr, *Zt = nullptr, *Vs = nullptr, *part = nullptr;
   std::vector<float*> act, pre, uh;
@@ -539,16 +535,17 @@ void inv_transform(fno_net* h, const float* Vh, int BO, float* Out, float beta) 
 }
 
 // out (groups of R x Cc, element (r, c) at gr so_g + r ldo + c) = alpha * sum over the
-// batch entries of each group of P_b Q_b^T, with P_b: R x n, Q_b: Cc x n.
+// batch entries of each group of P_b Q_b^T, with P_b: R x n, Q_b: Cc x n; bias (nullable, one
+// group): alpha * the row sums of P.
 template <typename TO>
 void gram_small(fno_net* h, const float* P, int64_t sPb, const float* Q, int64_t sQb, int R, int Cc, int B,
-                bool per_sample, TO* out, int64_t so_g, int ldo, float alpha) {
+                bool per_sample, TO* out, int64_t so_g, int ldo, float alpha, TO* bias = nullptr) {
   PQtSmall a{P, h->n, sPb, Q, h->n, sQb, R, Cc, h->n, h->splits, h->part};
   k_pqt_small<<<dim3((unsigned)h->splits, (unsigned)B), WG, 0, h->st>>>(a);
   const int groups = per_sample ? B : 1;
   const int per_group = per_sample ? h->splits : B * h->splits;
-  k_sum_parts<TO><<<dim3(blocks(R * Cc), (unsigned)groups), WG, 0, h->st>>>(h->part, per_group, groups, R, Cc, out,
-                                                                            so_g, ldo, alpha);
+  k_sum_parts<TO><<<dim3((bias ? PART : 32 * R) / SUM_E, (unsigned)groups), SUM_E * SUM_S, 0, h->st>>>(
+      h->part, per_group, R, Cc, out, so_g, ldo, alpha, bias);
 }
 
 void forward(fno_net* h, const float* V, int B) {
@@ -583,8 +580,8 @@ void backward(fno_net* h, int B) {
                                                  l < L ? h->dPre : nullptr, dU, O, w, n, B, l < L ? 1 : 0);
     const float* dP = l < L ? h->dPre : h->dY;
     // W and b gradients: sums over samples and nodes
-    gram_small<float>(h, dP, (int64_t)O * n, h->act[l], (int64_t)w * n, O, w, B, false, h->grad + h->oW[l], 0, w, 1.f);
-    gram_small<float>(h, dP, (int64_t)O * n, h->ones, 0, O, 1, B, false, h->grad + h->ob[l], 0, 1, 1.f);
+    gram_small<float>(h, dP, (int64_t)O * n, h->act[l], (int64_t)w * n, O, w, B, false, h->grad + h->oW[l], 0, w, 1.f,
+                      h->grad + h->ob[l]);
     // spectral part: dVh = S dPre S^T, dR, dUh, dU += S^T dUh S
     fwd_transform(h, dP, B * O, h->Vh);
     k_mix_wgrad<<<blocks((int64_t)O * w * m * m), WG, 0, h->st>>>(h->Vh, h->uh[l], h->grad + h->oR[l], B, O, w, m, MP);
@@ -593,8 +590,8 @@ void backward(fno_net* h, int B) {
     if (l < L) std::swap(cur, nxt);
   }
   // lift: cur holds dU_0
-  gram_small<float>(h, cur, (int64_t)w * n, h->In, 3 * n, w, 3, B, false, h->grad + h->oWl, 0, 3, 1.f);
-  gram_small<float>(h, cur, (int64_t)w * n, h->ones, 0, w, 1, B, false, h->grad + h->obl, 0, 1, 1.f);
+  gram_small<float>(h, cur, (int64_t)w * n, h->In, 3 * n, w, 3, B, false, h->grad + h->oWl, 0, 3, 1.f,
+                    h->grad + h->obl);
 }
 
 gsi_status hip_status(fno_net* h, hipError_t e, const char* what) {
@@ -650,7 +647,6 @@ gsi_status fno_create(fno_handle* out, const fno_config* cfg, uint64_t seed, voi
   h->m2 = nalloc<float>(h, h->count, e);
   h->S = nalloc<float>(h, (size_t)MP * N, e);
   h->St = nalloc<float>(h, (size_t)N * MP, e);
-  h->ones = nalloc<float>(h, n, e);
   h->prior = nalloc<float>(h, (size_t)p * n, e);
   h->In = nalloc<float>(h, B * 3 * n, e);
   for (int l = 0; l <= L; ++l) h->act.push_back(nalloc<float>(h, B * w * n, e));
@@ -667,7 +663,7 @@ gsi_status fno_create(fno_handle* out, const fno_config* cfg, uint64_t seed, voi
   h->Zt = nalloc<float>(h, B * mx * N * MP, e);
   h->Vh = nalloc<float>(h, B * mx * MP * MP, e);
   h->dUh = nalloc<float>(h, B * w * MP * MP, e);
-  h->part = nalloc<float>(h, (size_t)B * h->splits * 1024, e);
+  h->part = nalloc<float>(h, (size_t)B * h->splits * PART, e);
   h->G = nalloc<double>(h, B * 1024, e);
   h->Bm = nalloc<double>(h, B * 1024, e);
   h->lossd = nalloc<double>(h, B, e);
@@ -675,8 +671,8 @@ gsi_status fno_create(fno_handle* out, const fno_config* cfg, uint64_t seed, voi
   h->Ec = nalloc<float>(h, B * 1024, e);
   h->bad = nalloc<int>(h, 1, e);
   if (e != hipSuccess) { h->err = "out of device memory"; return GSI_ENOMEM; }
-  // host-side constants: sine matrices (zero beyond m), ones, seeded parameters
-  std::vector<float> S((size_t)MP * N, 0.f), St((size_t)N * MP, 0.f), ones(n, 1.f), prm(h->count, 0.f);
+  // host-side constants: sine matrices (zero beyond m), seeded parameters
+  std::vector<float> S((size_t)MP * N, 0.f), St((size_t)N * MP, 0.f), prm(h->count, 0.f);
   const double sc = sqrt(2.0 / (N + 1));
   for (int k = 0; k < m; ++k)
     for (int i = 0; i < N; ++i) {
@@ -714,7 +710,6 @@ gsi_status fno_create(fno_handle* out, const fno_config* cfg, uint64_t seed, voi
   }
   e = hipMemcpyAsync(h->S, S.data(), S.size() * 4, hipMemcpyHostToDevice, h->st);
   if (e == hipSuccess) e = hipMemcpyAsync(h->St, St.data(), St.size() * 4, hipMemcpyHostToDevice, h->st);
-  if (e == hipSuccess) e = hipMemcpyAsync(h->ones, ones.data(), ones.size() * 4, hipMemcpyHostToDevice, h->st);
   if (e == hipSuccess) e = hipMemcpyAsync(h->params, prm.data(), prm.size() * 4, hipMemcpyHostToDevice, h->st);
   if (e == hipSuccess) e = hipMemcpyAsync(h->prior, prior.data(), prior.size() * 4, hipMemcpyHostToDevice, h->st);
   if (e == hipSuccess) e = hipMemsetAsync(h->m1, 0, h->count * 4, h->st);
