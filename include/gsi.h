@@ -354,20 +354,23 @@ gsi_status gsi_batched_get_x(gsi_batch_handle h, int32_t i, double* X_out);
 /* Per-problem timeline of the last solve, read from the device wall clock, in microseconds
  * from the earliest start: start, switch to float64 (= start without a float32 phase) and
  * end; iters_low: iterations of the float32 phase; team: workgroups that worked on the
- * problem at the end (1 unless idle workgroups were recruited, see below). Host arrays of
+ * problem at the end (1 unless it had a team, see below). Host arrays of
  * count, each nullable. Syncs.
  *
- * Teams: once every problem has started, a running problem recruits idle workgroups by
- * the team policy of gsi_batched_set_tuning (by default every 32 iterations, up to 4 at a
- * time, up to 16 members with at least 16 row tiles of 64 rows each). The members split the tiles, add their partial
- * Grams and sums in member order and repeat the p x p work, so all hold the same state.
- * Float64 results of a problem that stayed with one workgroup repeat bit for bit; with a
- * team they depend on the team size, which depends on timing, and agree to rounding. */
+ * Teams: a problem that would outlast the others starts with a team of workgroups (sized at
+ * creation from all problems' n and p), and once every problem has started, a running problem
+ * recruits idle workgroups by the team policy of gsi_batched_set_tuning (by default every 32
+ * iterations, up to 4 at a time), up to 16 members with at least 16 row tiles of 64 rows each.
+ * The members split the tiles, add their partial Grams and sums in member order and repeat
+ * the p x p work, so all hold the same state. Float64 results of a problem that stayed with one
+ * workgroup repeat bit for bit; with a team they depend on the team size, which depends on
+ * timing, and agree to rounding. */
 gsi_status gsi_batched_timeline(gsi_batch_handle h, double* begin_us, double* switch_us, double* end_us,
                                 int32_t* iters_low, int32_t* team);
 /* Team policy of the following solves (defaults 16, 4, 32): a problem recruits idle
  * workgroups every check_every iterations, at most recruit_step at a time, up to one member
- * per tiles_per_member row tiles of 64 rows (and at most 16 members). tiles_per_member >= 4,
+ * per tiles_per_member row tiles of 64 rows (and at most 16 members); the limit on members
+ * holds for the team that a problem starts with, too. tiles_per_member >= 4,
  * 1 <= recruit_step <= 15, check_every >= 1, else GSI_EINVAL. The values are what
  * paper_2306_10379_amd/tuning.py measures and picks per batch shape. Syncs. */
 gsi_status gsi_batched_set_tuning(gsi_batch_handle h, int32_t tiles_per_member, int32_t recruit_step,

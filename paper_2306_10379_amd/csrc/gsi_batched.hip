@@ -1,8 +1,9 @@
 // Batched solve: many independent eigenproblems of different n and p in one persistent
 // launch. Every workgroup pulls problem indices from an atomic queue (largest problems
 // first) and runs the whole Riemannian CG iteration for one problem with workgroup barriers
-// (once the queue has drained, a running problem may recruit idle workgroups into a team
-// that splits its rows; see k_batched): gradient, direction, eigendecomposition of P^T P, SpMM, Grams, line search and
+// (a problem of more than an even share of the work starts with a team of workgroups that
+// splits its rows, see start_teams; once the queue has drained, a running problem may recruit
+// idle workgroups, see k_batched): gradient, direction, eigendecomposition of P^T P, SpMM, Grams, line search and
 // retraction (the same steps and readings as the single-problem path, see gsi_kernels.hip
 // and gsi_small.hip). The p x p state is float64. Blocks are float64, or float32 first and
 // float64 after: the float32 phase runs until rho <= switch_tol (or rho stops improving),
@@ -17,9 +18,11 @@
 // Passes read rows that other waves of the same workgroup wrote in the previous pass; an
 // agent-scope fence (L1 invalidation) plus a barrier separates passes.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <utility>
 #include <new>
 #include <string>
@@ -54,6 +57,7 @@ struct BatchProblem {
   double* ritz;             // p outputs (Ritz values of the operator solved)
   int32_t tmax, team;       // largest team allowed this solve / team size reached
   int32_t tcap, tiles;      // member storage allocated; row tiles
+  int32_t team0, pad0;      // workgroups that the problem starts with (at most tmax are taken)
   int32_t iters, iters_low, status, restarts, null_steps;
   int32_t shape;            // tile shape of the passes (see Shape); 0 = the defaults of Unroll
   double rho;
@@ -72,8 +76,8 @@ struct QEntry {
 };
 
 struct BatchCtl {
-  int32_t headA;  // queue of problems to start (stage 1)
-  int32_t count;
+  int32_t headA, nstart;  // queue of workgroup entries of the problems to start (stage 1)
+  int32_t count, pad0;
   int32_t headB, tailB;  // queue of team-member entries
   int32_t idle;          // workgroups waiting for work, minus entries reserved for them
   int32_t active;        // problems not finished
@@ -82,13 +86,18 @@ struct BatchCtl {
   int32_t tpm, grow_step, esc_every, pad2;  // team policy
   double tol, switch_tol;
   int64_t timeout_ticks;  // longest wait at a team barrier (wall-clock ticks)
-  const int32_t* order;   // stage-1 queue order (problem indices)
+  int64_t gather_ticks;   // longest wait of a first member for its start team
+  const QEntry* start;    // stage-1 queue: a problem's first member, then its start team's others
+  int32_t* arrive;        // per problem: start members arrived, GATHERED once the team is closed
+  int32_t* gathered;      // per problem: size of the start team, 0 until it is closed
   QEntry* qB;             // count x (TMAX - 1) entries
   int32_t* readyB;        // entry published flags
   int32_t* bars;          // per-problem team barrier counters
   int32_t* grow;          // per-problem number of workgroups recruited at the last check
   LoopState* ls;          // per-problem loop state at the last recruitment
 };
+
+constexpr int32_t GATHERED = 1 << 16;
 
 // State handed from the float32 phase to the float64 phase.
 struct Resume {
@@ -532,7 +541,7 @@ struct BatchShared {
   double red[12];
   double xv[8];
   double smu, sbmax;
-  int sok, sevals, bad, restart_next, flag, want, job, rank;
+  int sok, sevals, bad, restart_next, flag, want, job, rank, team;
 };
 
 // Wall-clock ticks spent per pass (indices of the GSI_PASS_* enumeration).
@@ -746,7 +755,7 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
       k_check = k;
       if (threadIdx.x == 0 && tm.rank == 0) {
         int want = 0;
-        if (ld_acq(&ctl->headA) >= ctl->count && !ld_acq(&ctl->abort)) {
+        if (ld_acq(&ctl->headA) >= ctl->nstart && !ld_acq(&ctl->abort)) {
           const int room = pr.tmax - tm.t < ctl->grow_step ? pr.tmax - tm.t : ctl->grow_step;
           int cur = ld_acq(&ctl->idle);
           while (cur > 0) {
@@ -943,11 +952,19 @@ __device__ void widen_tiles(const Team& tm, const void* src, void* dst) {
   b_widen<float>(e1 - e0, (const float*)src + e0, (double*)dst + e0);
 }
 
-// One workgroup's part in problem pr: the whole solve (rank 0, join == null) or, for a
-// workgroup recruited into a running problem, from the published loop state to the end.
+// Tiles [ta, tb) of the start block into the T block.
+template <typename T, int PP>
+__device__ void start_tiles(const Team& tm, const double* src, void* dst) {
+  const int64_t e0 = tm.ta * TR * PP, e1 = tm.tb * TR * PP;
+  b_narrow<T>(e1 - e0, src + e0, (T*)dst + e0);
+}
+
+// One workgroup's part in problem pr: the whole solve as member rank of a start team of `team`
+// (join == null) or, for a workgroup recruited into a running problem, from the published loop
+// state to the end.
 template <int PP>
 __device__ __noinline__ void solve_problem(BatchProblem& pr, BatchCtl* ctl, int idx, unsigned char* lds,
-                                           BatchShared& sh, int64_t* tk, int rank, const LoopState* join) {
+                                           BatchShared& sh, int64_t* tk, int rank, int team, const LoopState* join) {
   PassClock clk{wall_clock64(), tk};
   Resume rs{0, 0.0, 0};
   Team tm;
@@ -962,14 +979,13 @@ __device__ __noinline__ void solve_problem(BatchProblem& pr, BatchCtl* ctl, int 
     for (int e = threadIdx.x; e < S_COUNT * PP * PP; e += blockDim.x) gst(sr + e, gld(s0 + e));
     if (!team_sync(tm, ctl, ctl->bars + idx, sh)) return;
   } else {
-    tm.set(0, 1, pr.n);
-    if (threadIdx.x == 0) { pr.restarts = 0; pr.null_steps = 0; pr.iters_low = 0; pr.team = 1; }
+    tm.set(rank, team, pr.n);
+    if (threadIdx.x == 0) { pr.restarts = 0; pr.null_steps = 0; pr.iters_low = 0; pr.team = team; }
   }
-  const int64_t nel = (pr.n + TR - 1) / TR * TR * PP;
   int phase = join ? join->phase : (ctl->mixed ? 0 : 1);
   if (phase == 0) {
     if (!join) {
-      b_narrow<float>(nel, pr.X0, (float*)pr.blk[0][0]);
+      start_tiles<float, PP>(tm, pr.X0, pr.blk[0][0]);
       pass_barrier();
     }
     const int st = solve_phase<float, PP>(pr, ctl, idx, lds, sh, rs, fmax(ctl->switch_tol, ctl->tol),
@@ -986,7 +1002,7 @@ __device__ __noinline__ void solve_problem(BatchProblem& pr, BatchCtl* ctl, int 
     if (threadIdx.x == 0 && tm.rank == 0) { pr.iters_low = rs.k; pr.t_switch = wall_clock64(); }
     clk.mark(GSI_PASS_SMALL);
   } else if (!join) {
-    b_narrow<double>(nel, pr.X0, (double*)pr.blk[1][0]);
+    start_tiles<double, PP>(tm, pr.X0, pr.blk[1][0]);
     pass_barrier();
   }
   const int st = solve_phase<double, PP>(pr, ctl, idx, lds, sh, rs, ctl->tol, 0, clk, tm, join);
@@ -995,20 +1011,57 @@ __device__ __noinline__ void solve_problem(BatchProblem& pr, BatchCtl* ctl, int 
   clk.mark(GSI_PASS_SMALL);
 }
 
-// Persistent scheduler. A workgroup takes, in order of preference: a problem from the
-// stage-1 queue (alone); a member entry of a team being formed; otherwise it waits as an
-// idle workgroup (counted in ctl->idle, which problems reserve before posting entries, so
-// that every posted entry has a waiting workgroup to take it) until no problem is left.
+// Workgroups of problem pr's start team under the tiles-per-member limit in force.
+__device__ __forceinline__ int start_team(const BatchProblem& pr, int tpm) {
+  const int cap = max(1, min(pr.tiles / tpm, pr.tcap));
+  return min(pr.team0, cap);
+}
+
+// The first member of problem idx closes its start team: with all `want` members, or after
+// gather_ticks with those that have arrived (a device shared with other work may not hold all
+// workgroups of the launch at once; late members take the next entry). Returns the team size.
+// Thread 0.
+__device__ int gather_team(BatchCtl* ctl, int idx, int want) {
+  const int64_t t0 = wall_clock64();
+  while (ld_acq(ctl->arrive + idx) < want - 1 && wall_clock64() - t0 < ctl->gather_ticks) __builtin_amdgcn_s_sleep(1);
+  const int team = 1 + (atomicOr(ctl->arrive + idx, GATHERED) & (GATHERED - 1));
+  st_rel(ctl->gathered + idx, team);
+  return team;
+}
+
+// A workgroup arrives for the start team of problem idx: its rank and the team size in
+// `team`, or rank 0 if the team was closed without it. Thread 0.
+__device__ int join_start(BatchCtl* ctl, int idx, int& team) {
+  const int a = atomicAdd(ctl->arrive + idx, 1);
+  if (a & GATHERED) return 0;
+  // the first member took its entry before this one did and closes the team within gather_ticks
+  while ((team = ld_acq(ctl->gathered + idx)) == 0) __builtin_amdgcn_s_sleep(1);
+  return a + 1;
+}
+
+// Persistent scheduler. A workgroup takes, in order of preference: an entry of the stage-1
+// queue (a problem to start, alone or as a member of its start team); a member entry of a team
+// being formed; otherwise it waits as an idle workgroup (counted in ctl->idle, which problems
+// reserve before posting entries, so that every posted entry has a waiting workgroup to take it)
+// until no problem is left.
 __global__ __launch_bounds__(WG) void k_batched(BatchProblem* __restrict__ probs, BatchCtl* __restrict__ ctl) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ BatchShared sh;
   int counted = 0;  // thread 0: this workgroup is counted in ctl->idle
   for (;;) {
     if (threadIdx.x == 0) {
-      int job = -1, rank = 0;
-      if (ld_acq(&ctl->headA) < ctl->count) {
+      int job = -1, rank = 0, team = 0;
+      while (job < 0 && ld_acq(&ctl->headA) < ctl->nstart) {
         const int q = atomicAdd(&ctl->headA, 1);
-        if (q < ctl->count) job = ctl->order[q];
+        if (q >= ctl->nstart) break;
+        const QEntry en = ctl->start[q];
+        const int want = start_team(probs[en.prob], ctl->tpm);
+        if (en.rank == 0) {
+          job = en.prob;
+          team = want > 1 ? gather_team(ctl, en.prob, want) : 1;
+        } else if (en.rank < want && (rank = join_start(ctl, en.prob, team)) > 0) {
+          job = en.prob;
+        }
       }
       if (job >= 0 && counted) {
         atomicSub(&ctl->idle, 1);
@@ -1044,9 +1097,10 @@ __global__ __launch_bounds__(WG) void k_batched(BatchProblem* __restrict__ probs
       }
       sh.job = job;
       sh.rank = rank;
+      sh.team = team;
     }
     __syncthreads();
-    const int idx = sh.job, rank = sh.rank;
+    const int idx = sh.job, rank = sh.rank, team = sh.team;
     __syncthreads();
     if (idx < 0) return;
     BatchProblem pr = probs[idx];
@@ -1056,19 +1110,14 @@ __global__ __launch_bounds__(WG) void k_batched(BatchProblem* __restrict__ probs
     }
     int64_t tk[GSI_NPASS];
     for (int i = 0; i < GSI_NPASS; ++i) tk[i] = 0;
-    if (rank > 0) {
-      const LoopState st = ctl->ls[idx];
-      if (pr.PP == 16)
-        solve_problem<16>(pr, ctl, idx, lds_raw, sh, tk, rank, &st);
-      else
-        solve_problem<32>(pr, ctl, idx, lds_raw, sh, tk, rank, &st);
-      continue;
-    }
+    LoopState st;  // recruited into a running problem: team is 0
+    if (team == 0) st = ctl->ls[idx];
     const int64_t t_begin = wall_clock64();
     if (pr.PP == 16)
-      solve_problem<16>(pr, ctl, idx, lds_raw, sh, tk, 0, nullptr);
+      solve_problem<16>(pr, ctl, idx, lds_raw, sh, tk, rank, team, team ? nullptr : &st);
     else
-      solve_problem<32>(pr, ctl, idx, lds_raw, sh, tk, 0, nullptr);
+      solve_problem<32>(pr, ctl, idx, lds_raw, sh, tk, rank, team, team ? nullptr : &st);
+    if (rank > 0) continue;
     if (threadIdx.x == 0) {
       BatchProblem& o = probs[idx];
       o.iters = pr.iters;
@@ -1095,7 +1144,11 @@ __global__ void k_batched_reset(BatchCtl* ctl) {
   const int count = ctl->count;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count * (TMAX - 1); i += gridDim.x * blockDim.x)
     ctl->readyB[i] = 0;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) ctl->bars[i] = 0;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) {
+    ctl->bars[i] = 0;
+    ctl->arrive[i] = 0;
+    ctl->gathered[i] = 0;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     ctl->headA = 0;
     ctl->headB = 0;
@@ -1147,6 +1200,71 @@ gsi_status fetch(gsi_batch* b, std::vector<BatchProblem>& res) {
   hipError_t e = hipMemcpy(res.data(), b->dprobs, sizeof(BatchProblem) * b->count, hipMemcpyDeviceToHost);
   if (e != hipSuccess) { b->err = std::string("results: ") + hipGetErrorString(e); return GSI_EDEVICE; }
   return GSI_OK;
+}
+
+// Start teams. One workgroup streams a block at a rate of its own whatever the rest of the
+// device does, so the largest problems decide when a batch ends: of 256 problems of 1 to 25 thousand
+// rows the last ran 2.4 times as long as the mean workgroup. Estimated time of an iteration by t
+// workgroups, in units of a 64-row tile of 32 float64 columns (13.6 us; one of 16 columns takes 0.7
+// of it): the tiles over t, a fixed part for the p x p work and one for a team's barriers. For a T, every problem gets the
+// fewest members (at most one per TPM_DEF tiles) that bring it under T; the T is taken that ends
+// the batch first on `slots` workgroups. Sets team0; returns the members in all. Recruiting alone,
+// every 32 iterations, took 251 ms for those 256 problems and 60 iterations, 130 ms for 5 problems of
+// 3600 to 19600 rows and 83 ms for 17 of 1600 to 12100; with start teams 205, 25 and 25 ms.
+int start_teams(std::vector<BatchProblem>& probs, int slots, bool mixed) {
+  const double size = mixed ? 0.6 : 1.0;  // most iterations of a mixed solve are float32
+  auto cost = [&](const BatchProblem& q, int t) {
+    const bool wide = q.PP > 16;
+    return size * q.tiles * (wide ? 1.0 : 0.7) / t + (wide ? 16.0 : 5.0) + (t > 1 ? 5.0 : 0.0);
+  };
+  auto cap = [](const BatchProblem& q) { return std::max(1, std::min(q.tiles / TPM_DEF, q.tcap)); };
+  auto members = [&](const BatchProblem& q, double T) {
+    int t = 1;
+    while (t < cap(q) && cost(q, t) > T) ++t;
+    return t;
+  };
+  // end of the batch with the teams of T: teams from the start, the other problems largest first
+  // to the next free workgroup
+  std::vector<double> solo;
+  auto makespan = [&](double T) {
+    std::vector<double> free_at;  // heap, smallest first
+    double end = 0.0;
+    solo.clear();
+    for (const BatchProblem& q : probs) {
+      const int t = members(q, T);
+      const double c = cost(q, t);
+      end = std::max(end, c);
+      if (t > 1) free_at.insert(free_at.end(), t, c);
+      else solo.push_back(c);
+    }
+    if (free_at.size() > (size_t)slots) return (double)INFINITY;  // teams all start at once
+    free_at.resize(slots, 0.0);
+    std::make_heap(free_at.begin(), free_at.end(), std::greater<double>());
+    std::sort(solo.begin(), solo.end(), std::greater<double>());
+    for (double c : solo) {
+      std::pop_heap(free_at.begin(), free_at.end(), std::greater<double>());
+      free_at.back() += c;
+      end = std::max(end, free_at.back());
+      std::push_heap(free_at.begin(), free_at.end(), std::greater<double>());
+    }
+    return end;
+  };
+  double lo = 0.0, hi = 0.0;
+  for (const BatchProblem& q : probs) {
+    hi = std::max(hi, cost(q, 1));
+    lo = std::max(lo, cost(q, cap(q)));
+  }
+  double best = hi, end = makespan(hi);
+  for (int j = 1; lo < hi && j <= 24; ++j) {
+    const double T = hi * pow(lo / hi, j / 24.0), m = makespan(T);
+    if (m < 0.999 * end) { end = m; best = T; }
+  }
+  int64_t all = 0;
+  for (BatchProblem& q : probs) {
+    q.team0 = members(q, best);
+    all += q.team0;
+  }
+  return (int)std::min<int64_t>(all, slots);
 }
 
 double tick_us() {
@@ -1246,13 +1364,32 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
     pr.ritz = b->ritz + b->ritz_off[i];
     pr.status = -1;
   }
-  // queue: largest n * p first (longest-processing-time order)
+  const int lds = batched_lds();
+  const void* kern = reinterpret_cast<const void*>(k_batched);
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  int per_cu = 1;
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, WG, lds);
+  int dev = 0, ncu = 256;
+  hipDeviceProp_t prop;
+  (void)hipGetDevice(&dev);
+  if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0) ncu = prop.multiProcessorCount;
+  if (e != hipSuccess) { b->err = std::string("kernel attributes: ") + hipGetErrorString(e); return GSI_EDEVICE; }
+  const int slots = ncu * std::max(per_cu, 1);  // workgroups resident at once
+  const int members = start_teams(b->hprobs, slots, b->mixed != 0);
+  // queue: largest n * p first (longest-processing-time order), the start teams before all
   std::vector<int32_t> order(count);
   for (int i = 0; i < count; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
-    return b->hprobs[a].n * b->hprobs[a].p > b->hprobs[c].n * b->hprobs[c].p;
+    const BatchProblem &pa = b->hprobs[a], &pc = b->hprobs[c];
+    if ((pa.team0 > 1) != (pc.team0 > 1)) return pa.team0 > 1;
+    return pa.n * pa.p > pc.n * pc.p;
   });
-  int32_t* dorder = balloc<int32_t>(b, count, e);
+  std::vector<QEntry> start;
+  for (int i : order)
+    for (int r = 0; r < b->hprobs[i].team0; ++r) start.push_back(QEntry{i, r});
+  QEntry* dstart = balloc<QEntry>(b, start.size(), e);
+  int32_t* arrive = balloc<int32_t>(b, count, e);
+  int32_t* gathered = balloc<int32_t>(b, count, e);
   b->dprobs = balloc<BatchProblem>(b, count, e);
   b->dctl = balloc<BatchCtl>(b, 1, e);
   QEntry* qB = balloc<QEntry>(b, (size_t)count * (TMAX - 1), e);
@@ -1275,7 +1412,10 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
   ctl.tpm = TPM_DEF;
   ctl.grow_step = GROW_DEF;
   ctl.esc_every = ESC_DEF;
-  ctl.order = dorder;
+  ctl.nstart = (int32_t)start.size();
+  ctl.start = dstart;
+  ctl.arrive = arrive;
+  ctl.gathered = gathered;
   ctl.qB = qB;
   ctl.readyB = readyB;
   ctl.bars = bars;
@@ -1283,30 +1423,21 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
   ctl.ls = ls;
   {
     // a team barrier waits at most 30 s (members step together; a healthy wait is
-    // one pass of one iteration)
-    int dev = 0, khz = 0;
-    (void)hipGetDevice(&dev);
+    // one pass of one iteration); a first member waits 2 ms for its start team, whose entries
+    // follow its own in the queue (microseconds on a free device)
+    int khz = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0) khz = 100000;
     ctl.timeout_ticks = (int64_t)khz * 1000 * 30;
+    ctl.gather_ticks = (int64_t)khz * 2;
   }
-  e = hipMemcpyAsync(dorder, order.data(), sizeof(int32_t) * count, hipMemcpyHostToDevice, b->st);
+  e = hipMemcpyAsync(dstart, start.data(), sizeof(QEntry) * start.size(), hipMemcpyHostToDevice, b->st);
   if (e == hipSuccess) e = hipMemcpyAsync(b->dctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice, b->st);
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->dprobs, b->hprobs.data(), sizeof(BatchProblem) * count, hipMemcpyHostToDevice, b->st);
   if (e == hipSuccess) e = hipStreamSynchronize(b->st);
   if (e != hipSuccess) { b->err = std::string("upload: ") + hipGetErrorString(e); return GSI_EDEVICE; }
-  // persistent grid: enough workgroups to fill the device, never more than the problems
-  const int lds = batched_lds();
-  const void* kern = reinterpret_cast<const void*>(k_batched);
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-  int per_cu = 1;
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, WG, lds);
-  int dev = 0, ncu = 256;
-  hipDeviceProp_t prop;
-  (void)hipGetDevice(&dev);
-  if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0) ncu = prop.multiProcessorCount;
-  if (e != hipSuccess) { b->err = std::string("kernel attributes: ") + hipGetErrorString(e); return GSI_EDEVICE; }
-  b->grid = std::max(1, std::min(count, ncu * std::max(per_cu, 1)));
+  // persistent grid: enough workgroups to fill the device, never more than there is work for
+  b->grid = std::max(1, std::min(std::max(count, members), slots));
   return GSI_OK;
 }
 

@@ -1,0 +1,68 @@
+"""Start teams of the batched solve: a problem that would outlast the others starts with several
+workgroups. Sizes sit at the edges of the member limit (16 tiles of 64 rows a member;
+16 members at most) and on both sides of 16 columns, and the results match one workgroup's."""
+import threading
+
+import numpy as np
+import pytest
+
+from paper_2306_10379_amd import inputs as I
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def _solver(sides, ps, precision="fp64"):
+    from paper_2306_10379_amd import gsi
+    mats = [I.schrodinger_2d(N, I.random_wells(900 + N, count=(4, 6))) for N in sides]
+    X0s = [I.start_block(A.n, p, 901) for A, p in zip(mats, ps)]
+    return gsi.BatchedSolver(mats, X0s, ps, which=-1, precision=precision, tol=1e-10, max_iter=20000)
+
+
+def _solve(b):
+    _, iters, status = b.solve()
+    *_, team = b.timeline()
+    assert np.all(status == 1)
+    return [b.results(i)[0] for i in range(len(b.ps))], team
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("sides,ps", [
+    ([45], [5]),                 # 2025 rows, 32 tiles: two members
+    ([44], [5]),                 # 1936 rows, 31 tiles: one
+    ([130], [17]),               # 265 tiles: the most members
+    ([96, 12, 11], [20, 3, 4]),  # one problem that decides the end among small ones
+], ids=["two", "one", "most", "among"])
+def test_start_teams_match_one_workgroup(sides, ps, precision):
+    """Both solves end below rho = 1e-10, where Ritz values are exact to rho^2 ||A||^2 / gap, far
+    below the 1e-10 asked for here."""
+    with _solver(sides, ps, precision) as b:
+        print(f"teams {sides} {ps} {precision}", flush=True)
+        got, team = _solve(b)
+        tiles = [(N * N + 63) // 64 for N in sides]
+        assert all(t <= max(1, min(16, n // 16)) for t, n in zip(team, tiles)), team
+        assert team[0] == max(1, min(16, tiles[0] // 16)) and np.all(team[1:] == 1), team
+        b.set_tuning(1 << 20, 1, 1 << 20)
+        ref, team = _solve(b)
+        assert np.all(team == 1)
+        for x, y in zip(got, ref):
+            assert np.max(np.abs(x - y) / np.abs(y)) <= 1e-10
+
+
+def test_start_teams_of_two_solvers_at_once():
+    """Two launches share the device; each closes its teams with whoever arrives."""
+    with _solver([96, 90, 20], [12, 20, 4]) as a, _solver([80, 100], [18, 9]) as b:
+        ref = [_solve(s)[0] for s in (a, b)]
+        out = [None, None]
+
+        def run(k, s):
+            out[k] = _solve(s)[0]
+
+        for _ in range(3):
+            ts = [threading.Thread(target=run, args=(k, s)) for k, s in enumerate((a, b))]
+            [t.start() for t in ts]
+            [t.join() for t in ts]
+            for k in range(2):
+                for x, y in zip(out[k], ref[k]):
+                    assert np.max(np.abs(x - y) / np.abs(y)) <= 1e-10
