@@ -395,7 +395,8 @@ gsi_status gsi_batched_set_wait_limit(gsi_batch_handle h, double seconds);
 /* Per-problem time per pass of the last solve in microseconds: host array of count x
  * GSI_NPASS, entry [i * GSI_NPASS + GSI_PASS_*] (GSI_PASS_REFRESH also holds the Cholesky
  * QR of the start block and the first A X, GSI_PASS_SMALL the p x p work outside the
- * eigendecomposition and line search). Syncs. */
+ * eigendecomposition and line search; the Grams are part of the gradient, direction and SpMM
+ * passes and counted there, GSI_PASS_GRAM is 0). Syncs. */
 gsi_status gsi_batched_pass_times(gsi_batch_handle h, double* us);
 const char* gsi_batched_last_error(gsi_batch_handle h);
 void gsi_destroy_batched(gsi_batch_handle h);

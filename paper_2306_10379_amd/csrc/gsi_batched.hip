@@ -39,6 +39,7 @@ namespace gsi {
 constexpr int NBLK = 7;      // X, Y, G0, G1, P0, P1, Z
 constexpr int TMAX = 16;     // largest team of workgroups on one problem
 constexpr int TPM_MIN = 4;   // fewest 64-row tiles per team member that storage is sized for
+constexpr int ROWNZ = 7;     // nonzeros of a row that the matrix product takes (checked at creation)
 // default team policy (gsi_batched_set_tuning changes it): fewest tiles per member,
 // workgroups recruited at one check, iterations between checks
 constexpr int TPM_DEF = 16, GROW_DEF = 4, ESC_DEF = 32;
@@ -190,19 +191,87 @@ __device__ void b_load_matrix(T* __restrict__ s, const double* __restrict__ M) {
   for (int i = threadIdx.x; i < PP * PP; i += blockDim.x) s[i] = (T)gld(M + i);
 }
 
-// G = X C - Y over tiles [ta, tb); sums of G^2 and G_old G, max absolute row sum.
+// A Gram that rides on a streaming pass: blocks acc[ib][jb] of this wave over its rows of the
+// tiles, both operands in the RL layout of 16 rows (k step r contracts the rows of register r, so
+// what a product leaves in the matrix unit's output registers is an operand as it is).
+template <typename T, int PP>
+struct GramAcc {
+  static constexpr int V = PP / 16;
+  typename Vec4<T>::type acc[V][V];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int ib = 0; ib < V; ++ib)
+#pragma unroll
+      for (int jb = 0; jb < V; ++jb) acc[ib][jb] = typename Vec4<T>::type{0, 0, 0, 0};
+  }
+  // SYM: blocks below the diagonal are left out
+  template <bool SYM = false>
+  __device__ __forceinline__ void add(const T (&a)[V][4], const T (&b)[V][4]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int ib = 0; ib < V; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < V; ++jb)
+          if (!SYM || ib <= jb) acc[ib][jb] = mfma(a[ib][r], b[jb][r], acc[ib][jb]);
+  }
+  // Operands with V consecutive columns a lane: row r of the step, columns V c ..
+  __device__ __forceinline__ void add_runs(const T (&a)[4][V], const T (&b)[4][V]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int ib = 0; ib < V; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < V; ++jb) acc[ib][jb] = mfma(a[r][ib], b[r][jb], acc[ib][jb]);
+  }
+  // The waves' sums added in wave order in red (LDS, PP^2 doubles), then to out (PP x PP).
+  // Workgroup barriers inside; out is complete after the next one. RUNS: of add_runs.
+  template <bool SYM = false, bool RUNS = false>
+  __device__ __forceinline__ void flush(double* red, double* out) const {
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
+    for (int ww = 0; ww < 4; ++ww) {
+      if (w == ww) {
+#pragma unroll
+        for (int ib = 0; ib < V; ++ib)
+#pragma unroll
+          for (int jb = 0; jb < V; ++jb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              if (SYM && ib > jb) continue;
+              const int row = rowof<T>(g, r);
+              const int e = RUNS ? (row * V + ib) * PP + c * V + jb : (16 * ib + row) * PP + 16 * jb + c;
+              red[e] = (ww ? red[e] : 0.0) + (double)acc[ib][jb][r];
+            }
+      }
+      __syncthreads();
+    }
+    for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) {
+      const int i = e / PP, j = e % PP;
+      gst(out + e, red[SYM && i / 16 > j / 16 ? j * PP + i : e]);
+    }
+  }
+};
+
+// G = X C - Y over tiles [ta, tb), K = X^T G; sums of G^2 and G_old G, max absolute row sum. A
+// pass of its own for K read X and G once more from memory: the eight passes of an iteration moved
+// 22 blocks where these move 17, and with a workgroup on every CU the batch runs at the
+// memory's rate (5.1 TB/s): 217 -> 190 ms for 256 problems of 1 to 25 thousand rows.
 template <typename T, int PP, int U>
 __device__ __noinline__ void b_grad(int64_t n, int64_t ta, int64_t tb, const T* X, const T* Y, const T* Gold, T* G,
-                                    const T* sC, bool have_old, double* sums) {
+                                    const T* sC, bool have_old, double* sums, double* red, double* kout) {
   const int w = threadIdx.x >> 6;
   sC = to_lds(sC);
+  red = to_lds(red);
   double gg = 0.0, gdot = 0.0, ginf = 0.0;
+  GramAcc<T, PP> K;
+  K.zero();
   for (int64_t t = ta; t < tb; t += U) {
-    T a[U][PP / 4], y[U][PP / 16][4], go[U][PP / 16][4];
+    T a[U][PP / 4], y[U][PP / 16][4], go[U][PP / 16][4], x[U][PP / 16][4];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t row0 = (t + u) * TR + 16 * w, nv = t + u < tb ? n : 0;
       load_al<T, PP>(X, row0, nv, a[u]);
+      load_rl<T, PP>(X, row0, nv, x[u]);
       load_rl<T, PP>(Y, row0, nv, y[u]);
       if (have_old) load_rl<T, PP>(Gold, row0, nv, go[u]);
     }
@@ -218,6 +287,7 @@ __device__ __noinline__ void b_grad(int64_t n, int64_t ta, int64_t tb, const T* 
 #pragma unroll
         for (int r = 0; r < 4; ++r) g[cb][r] = acc[cb][r] - y[u][cb][r];
       store_rl<T, PP>(G, row0, nv, g);
+      K.add(x[u], g);
       double rs[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int cb = 0; cb < PP / 16; ++cb)
@@ -235,15 +305,19 @@ __device__ __noinline__ void b_grad(int64_t n, int64_t ta, int64_t tb, const T* 
   sums[0] = gg;
   sums[1] = gdot;
   sums[2] = ginf;
+  K.flush(red, kout);
 }
 
-// P = G + beta P_old - X KD over tiles [ta, tb); sum of G P.
+// P = G + beta P_old - X KD over tiles [ta, tb), S = P^T P; sum of G P.
 template <typename T, int PP, int U>
 __device__ __noinline__ void b_dir(int64_t n, int64_t ta, int64_t tb, const T* X, const T* G, const T* Pold, T* P,
-                                   const T* sK, T beta, bool use_old, double* sums) {
+                                   const T* sK, T beta, bool use_old, double* sums, double* red, double* sout) {
   const int w = threadIdx.x >> 6;
   sK = to_lds(sK);
+  red = to_lds(red);
   double gp = 0.0;
+  GramAcc<T, PP> S;
+  S.zero();
   for (int64_t t = ta; t < tb; t += U) {
     T a[U][PP / 4], g[U][PP / 16][4], po[U][PP / 16][4];
 #pragma unroll
@@ -268,9 +342,11 @@ __device__ __noinline__ void b_dir(int64_t n, int64_t ta, int64_t tb, const T* X
           gp += (double)g[u][cb][r] * (double)pn[cb][r];
         }
       store_rl<T, PP>(P, row0, nv, pn);
+      S.template add<true>(pn, pn);
     }
   }
   sums[0] = gp;
+  S.template flush<true>(red, sout);
 }
 
 // X <- (X - mu P) M, Y <- (Y - mu Z) M over tiles [ta, tb) (Y skipped when upd_y is false).
@@ -399,6 +475,118 @@ __device__ __noinline__ void b_spmm(int64_t r0, int64_t r1, const int32_t* rowpt
 #pragma unroll
     for (int e = 0; e < EPL; ++e) gst(zr + e, acc[e]);
   }
+}
+
+// Z = A P over the rows of tiles [ta, tb), and P^T Z and P^T Y over them. Lane (g, c) computes
+// columns V c .. V c + V - 1 (V = PP / 16) of the rows 4 r + g of its wave's 16, the layout in which
+// the Gram takes them, so Z feeds it from registers, and the rows of P come from the caches that
+// their gathers filled. The nonzeros of 16 rows lie side by side: a wave loads them coalesced, one
+// tile ahead, and reads them from LDS, so that a gather waits for no index load. They number at
+// most 16 ROWNZ: longer rows are refused at creation. CH nonzeros of two rows are gathered together.
+// A product by itself, with the index loads in its gathers' way, and the Gram after it took
+// 2.6 ms an iteration for 25600 rows of 32 columns by one workgroup, this 1.8.
+template <typename T, int PP, int CH>
+__device__ __noinline__ void b_spmm_gram(int64_t n, int64_t ta, int64_t tb, const int32_t* rowptr,
+                                         const int32_t* colind, const T* vals, const T* P, T* Z, const T* Y,
+                                         double* red, double* pz, double* py) {
+  constexpr int V = PP / 16, SC = 128;
+  static_assert(16 * ROWNZ <= SC, "nonzeros of a wave's rows");
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
+  red = to_lds(red);
+  T* bv = reinterpret_cast<T*>(reinterpret_cast<char*>(red) + w * SC * (sizeof(T) + sizeof(int32_t)));
+  int32_t* bc = reinterpret_cast<int32_t*>(bv + SC);
+  GramAcc<T, PP> GZ, GY;
+  GZ.zero();
+  GY.zero();
+  // row pointers of a wave's rows: lane i <= 16 that of row i
+  auto pointers = [&](int64_t t) {
+    const int64_t row = t * TR + 16 * w + min(l, 16);
+    return t < tb ? gld(rowptr + (row < n ? row : n)) : 0;
+  };
+  int32_t sc[SC / 64];
+  T sv[SC / 64];
+  auto stage = [&](int32_t rp) {
+    const int32_t js = __builtin_amdgcn_readlane(rp, 0), je = __builtin_amdgcn_readlane(rp, 16);
+#pragma unroll
+    for (int e = 0; e < SC / 64; ++e) {
+      const int32_t j = js + 64 * e + l;
+      sc[e] = j < je ? gld(colind + j) : 0;
+      sv[e] = j < je ? gld(vals + j) : T(0);
+    }
+  };
+  int32_t rp = pointers(ta), rp1 = pointers(ta + 1);
+  stage(rp);
+  for (int64_t t = ta; t < tb; ++t) {
+    const int64_t row0 = t * TR + 16 * w;
+    const int32_t js = __builtin_amdgcn_readlane(rp, 0), je = __builtin_amdgcn_readlane(rp, 16);
+    wave_sync();  // the last tile's reads
+#pragma unroll
+    for (int e = 0; e < SC / 64; ++e) {
+      bc[64 * e + l] = sc[e];
+      bv[64 * e + l] = sv[e];
+    }
+    wave_sync();
+    const int32_t rp2 = pointers(t + 2);
+    stage(rp1);
+    T pr[4][V], y[4][V], z[4][V];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {  // blocks span whole tiles
+      const int64_t at = (row0 + 4 * r + g) * PP + V * c;
+      load_run<T, V>(P + at, true, pr[r]);
+      load_run<T, V>(Y + at, true, y[r]);
+#pragma unroll
+      for (int e = 0; e < V; ++e) z[r][e] = T(0);
+    }
+    // nonzeros of the longest of the 16 rows: every row takes as many turns, past its end with a
+    // zero value at some nonzero of the 16 rows (no divergent loads)
+    int32_t most = __shfl(rp, (l & 15) + 1, 64) - __shfl(rp, l & 15, 64);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+    most = __builtin_amdgcn_readfirstlane(most);
+#pragma unroll
+    for (int r0 = 0; r0 < 4; r0 += 2) {
+      int32_t j0[2], j1[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        j0[h] = __shfl(rp, 4 * (r0 + h) + g, 64);
+        j1[h] = __shfl(rp, 4 * (r0 + h) + g + 1, 64);
+      }
+      for (int32_t jb = 0; jb < most; jb += CH) {
+        T src[2][CH][V];
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          if (jb + u < most)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              load_run<T, V>(P + (int64_t)bc[min(j0[h] + jb + u, je - 1) - js] * PP + V * c, true, src[h][u]);
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          if (jb + u < most)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const int32_t j = j0[h] + jb + u;
+              const T x = bv[min(j, je - 1) - js], v = j < j1[h] ? x : T(0);
+#pragma unroll
+              for (int e = 0; e < V; ++e) z[r0 + h][e] += v * src[h][u][e];
+            }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = row0 + 4 * r + g;
+      if (row < n)
+#pragma unroll
+        for (int e = 0; e < V; ++e) gst(Z + row * PP + V * c + e, z[r][e]);
+    }
+    GZ.add_runs(pr, z);
+    GY.add_runs(pr, y);
+    rp = rp1;
+    rp1 = rp2;
+  }
+  __syncthreads();  // red held the staged nonzeros
+  GZ.template flush<false, true>(red, pz);
+  __syncthreads();
+  GY.template flush<false, true>(red, py);
 }
 
 // out1 = A^T B1, out2 = A^T B2 (B2 may be null) over tiles [ta, tb): PP x PP float64.
@@ -640,6 +828,24 @@ __device__ void gram_part(const Team& tm, BatchProblem& pr, const T* A, const T*
   });
 }
 
+// Where this member's partial of a Gram (nth of an exchange) goes: dst for a lone workgroup.
+template <int PP>
+__device__ __forceinline__ double* gram_slot(const Team& tm, const BatchProblem& pr, int nth, double* dst) {
+  return tm.t == 1 ? dst : xslot<PP>(pr, tm.xc & 1, tm.rank) + nth * PP * PP;
+}
+
+// The team's sums of nmat Grams whose partials are in gram_slot, and of the scalars (a plain
+// barrier for a lone workgroup).
+template <int PP>
+__device__ __forceinline__ bool team_sums(Team& tm, BatchCtl* ctl, BatchProblem& pr, int32_t* bar, BatchShared& sh,
+                                          int nmat, double* d1, double* d2, double* v, int ns, int nx) {
+  if (tm.t == 1) {
+    pass_barrier();
+    return true;
+  }
+  return exchange<PP>(tm, ctl, pr, bar, sh, nmat, d1, d2, v, ns, nx);
+}
+
 // Gram plus scalars over the team (a plain barrier for a lone workgroup).
 template <typename T, int PP>
 __device__ bool team_gram(Team& tm, BatchCtl* ctl, BatchProblem& pr, int32_t* bar, BatchShared& sh, const T* A,
@@ -808,17 +1014,16 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
     b_load_matrix<T, PP>(sMat, C);
     __syncthreads();
     double sums[3];
-    with_124(shp.u, [&](auto U) { b_grad<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Y, Gb[par ^ 1], Gb[par], sMat, k > 0, sums); });
+    with_124(shp.u, [&](auto U) { b_grad<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Y, Gb[par ^ 1], Gb[par], sMat, k > 0, sums, dl, gram_slot<PP>(tm, pr, 0, K)); });
     double gg = sums[0], gdot = sums[1], ginf = sums[2];
     b_reduce3(gg, gdot, ginf, sh.red);
-    clk.mark(GSI_PASS_GRAD);
     v[0] = gg;
     v[1] = gdot;
     v[2] = ginf;
-    if (!team_gram<T, PP>(tm, ctl, pr, bar, sh, X, Gb[par], nullptr, K, nullptr, dl, v, 2, 1)) { stop = 5; break; }
+    if (!team_sums<PP>(tm, ctl, pr, bar, sh, 1, K, nullptr, v, 2, 1)) { stop = 5; break; }
     gg = v[0];
     gdot = v[1];
-    clk.mark(GSI_PASS_GRAM);
+    clk.mark(GSI_PASS_GRAD);
     rho = sqrt(gg) / (sqrt_p * pr.nA);
     if (k == k_first || rho <= 0.5 * rho_best) { rho_best = rho; k_best = k; }
     if (!isfinite(gg)) stop = 3;
@@ -835,15 +1040,11 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
     b_load_matrix<T, PP>(sMat, KD);
     __syncthreads();
     clk.mark(GSI_PASS_SMALL);
-    with_124(shp.u, [&](auto U) { b_dir<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Gb[par], Pb[par ^ 1], Pb[par], sMat, (T)beta, !restart, sums); });
+    with_124(shp.u, [&](auto U) { b_dir<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Gb[par], Pb[par ^ 1], Pb[par], sMat, (T)beta, !restart, sums, dl, gram_slot<PP>(tm, pr, 0, G2)); });
     double gp = sums[0], dz1 = 0.0, dz2 = 0.0;
     b_reduce3(gp, dz1, dz2, sh.red);
-    clk.mark(GSI_PASS_DIR);
     v[0] = gp;
-    if (!team_gram<T, PP>(tm, ctl, pr, bar, sh, Pb[par], Pb[par], nullptr, G2, nullptr, dl, v, 1, 0)) {
-      stop = 5;
-      break;
-    }
+    if (!team_sums<PP>(tm, ctl, pr, bar, sh, 1, G2, nullptr, v, 1, 0)) { stop = 5; break; }
     gp = v[0];
     if (!(gp > 0.0)) {
       if (restart) { stop = 3; break; }
@@ -854,17 +1055,18 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
     }
     for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) S[e] = 0.5 * (G2[e] + G2[(e % PP) * PP + e / PP]);
     pass_barrier();
-    clk.mark(GSI_PASS_GRAM);
+    clk.mark(GSI_PASS_DIR);
     b_eig<PP>(small, p, v_valid, dl);
     v_valid = true;
     clk.mark(GSI_PASS_EIG);
     // SpMM of this member's rows (every row of P is final after the exchange above) and
     // the line-search Grams
-    with_48_16(shp.ch, [&](auto C) { b_spmm<T, PP, decltype(C)::value>(tm.r0, tm.r1, pr.rowptr, pr.colind, vals, Pb[par], Z); });
-    pass_barrier();
+    with_48_16(shp.ch, [&](auto C) {
+      b_spmm_gram<T, PP, decltype(C)::value>(n, tm.ta, tm.tb, pr.rowptr, pr.colind, vals, Pb[par], Z, Y, dl,
+                                             gram_slot<PP>(tm, pr, 0, PZ), gram_slot<PP>(tm, pr, 1, PY));
+    });
+    if (!team_sums<PP>(tm, ctl, pr, bar, sh, 2, PZ, PY, v, 0, 0)) { stop = 5; break; }
     clk.mark(GSI_PASS_SPMM);
-    if (!team_gram<T, PP>(tm, ctl, pr, bar, sh, Pb[par], Z, Y, PZ, PY, dl, v, 0, 0)) { stop = 5; break; }
-    clk.mark(GSI_PASS_GRAM);
     b_linesearch<PP>(PZ, PY, small, p, dl, sh.terms, &sh.smu, &sh.sok, &sh.sevals, &sh.sbmax);
     clk.mark(GSI_PASS_LINESEARCH);
     if (!sh.sok) {
@@ -1351,6 +1553,7 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
     (void)hipMemcpyAsync(&fl, flags, sizeof(int), hipMemcpyDeviceToHost, b->st);
     e = hipStreamSynchronize(b->st);
     if (e != hipSuccess) { b->err = std::string("validate: ") + hipGetErrorString(e); return GSI_EDEVICE; }
+    // any flag refuses the matrix, that of a row of more than ROWNZ nonzeros too
     if (fl) { b->err = "problem " + std::to_string(i) + ": invalid CSR or non-finite values"; return GSI_EINVAL; }
     double nA = 0.0;
     for (double v : pm) nA = v > nA ? v : nA;

@@ -1,6 +1,7 @@
 """Start teams of the batched solve: a problem that would outlast the others starts with several
 workgroups. Sizes sit at the edges of the member limit (16 tiles of 64 rows a member;
-16 members at most) and on both sides of 16 columns, and the results match one workgroup's."""
+16 members at most) and on both sides of 16 columns; the results match those of one workgroup. And the
+row lengths that the matrix product meets."""
 import threading
 
 import numpy as np
@@ -66,3 +67,27 @@ def test_start_teams_of_two_solvers_at_once():
             for k in range(2):
                 for x, y in zip(out[k], ref[k]):
                     assert np.max(np.abs(x - y) / np.abs(y)) <= 1e-10
+
+
+@pytest.mark.parametrize("p", [5, 20])
+@pytest.mark.parametrize("n", [64, 77, 1100])
+def test_row_lengths_of_the_matrix_product(n, p):
+    """Rows of seven nonzeros (the most that a batch takes: 112 in a wave's 16 rows), of one, of
+    none and of lengths that differ within the 16, against dense eigenvalues."""
+    from paper_2306_10379_amd import gsi
+    a = np.zeros((n, n))
+    for i in range(33):  # band of seven, then short rows
+        for j in range(max(0, i - 3), min(33, i + 4)):
+            a[i, j] = 40.0 + 2.0 * i if i == j else 1.0 / (1 + abs(i - j))
+    a[np.arange(40, n), np.arange(40, n)] = np.linspace(1.0, 3.0, n - 40)  # rows 33 .. 39 are empty
+    for i in range(45, n - 1, 2):
+        a[i, i + 1] = a[i + 1, i] = 0.5
+    A = I.dense_to_csr(a)
+    lens = np.diff(A.rowptr)
+    assert lens.max() == 7 and lens.min() == 0
+    print(f"rows {n} {p} nnz {A.nnz}", flush=True)
+    with gsi.BatchedSolver([A], [I.start_block(n, p, 5)], [p], which=1, precision="fp64", tol=1e-11,
+                           max_iter=20000) as b:
+        ritz, _ = _solve(b)
+    w = np.linalg.eigvalsh(a)[::-1][:p]
+    assert np.max(np.abs(ritz[0] - w)) <= 1e-10 * np.max(np.abs(w))
