@@ -322,7 +322,7 @@ const char* gsi_last_error(gsi_handle h);
 /* ------------------------------------------------------------------------------------------
  * Batched solve: count independent problems (A[i], p[i], X0[i]) of different sizes solved by
  * one persistent kernel launch, captured in a HIP graph. Each workgroup takes problems from
- * an atomic queue (largest n*p first) and runs the whole iteration of one problem (Sec. 5,
+ * an atomic queue (longest estimated time first) and runs the whole iteration of one problem (Sec. 5,
  * Algorithm 4, with the same readings as gsi_solve) with workgroup barriers only. Options
  * shared by all problems: which, method, precision, recompute_ax, k_restart, max_iter, tol,
  * switch_tol, stall_window. GSI_FP64: float64 blocks throughout. GSI_MIXED_FP32: float32
@@ -395,8 +395,9 @@ gsi_status gsi_batched_set_wait_limit(gsi_batch_handle h, double seconds);
 /* Per-problem time per pass of the last solve in microseconds: host array of count x
  * GSI_NPASS, entry [i * GSI_NPASS + GSI_PASS_*] (GSI_PASS_REFRESH also holds the Cholesky
  * QR of the start block and the first A X, GSI_PASS_SMALL the p x p work outside the
- * eigendecomposition and line search; the Grams are part of the gradient, direction and SpMM
- * passes and counted there, GSI_PASS_GRAM is 0). Syncs. */
+ * eigendecomposition and line search; an iteration's Grams are part of its gradient, direction
+ * and SpMM passes and counted there, GSI_PASS_GRAM holds those of the start and of refreshes).
+ * Syncs. */
 gsi_status gsi_batched_pass_times(gsi_batch_handle h, double* us);
 const char* gsi_batched_last_error(gsi_batch_handle h);
 void gsi_destroy_batched(gsi_batch_handle h);

@@ -1,5 +1,5 @@
 // Batched solve: many independent eigenproblems of different n and p in one persistent
-// launch. Every workgroup pulls problem indices from an atomic queue (largest problems
+// launch. Every workgroup pulls problem indices from an atomic queue (longest problems
 // first) and runs the whole Riemannian CG iteration for one problem with workgroup barriers
 // (a problem of more than an even share of the work starts with a team of workgroups that
 // splits its rows, see start_teams; once the queue has drained, a running problem may recruit
@@ -915,6 +915,7 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
     bool ok = true;
     for (int pass = 0; pass < 2 && ok; ++pass) {
       if (!team_gram<T, PP>(tm, ctl, pr, bar, sh, X, X, nullptr, G2, nullptr, dl, v, 0, 0)) { stop = 5; break; }
+      clk.mark(GSI_PASS_GRAM);
       ok = b_chol_inv<PP>(G2, M, p, dl, &sh.bad);
       b_load_matrix<T, PP>(sMat, M);
       __syncthreads();
@@ -933,6 +934,7 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
     // Y = A X, C = sym(X^T Y); with a carried direction also W = X^T P_old
     with_48_16(shp.ch, [&](auto C) { b_spmm<T, PP, decltype(C)::value>(tm.r0, tm.r1, pr.rowptr, pr.colind, vals, X, Y); });
     pass_barrier();
+    clk.mark(GSI_PASS_REFRESH);
     if (!team_gram<T, PP>(tm, ctl, pr, bar, sh, X, Y, carry ? Pb[(rs.k - 1) & 1] : nullptr, G2, carry ? W : nullptr,
                           dl, v, 0, 0)) {
       rs.carry = 0;
@@ -940,6 +942,7 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
       __syncthreads();
       return 5;
     }
+    clk.mark(GSI_PASS_GRAM);
     for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) C[e] = 0.5 * (G2[e] + G2[(e % PP) * PP + e / PP]);
     pass_barrier();
     clk.mark(GSI_PASS_REFRESH);
@@ -1089,7 +1092,9 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
       if (tm.t > 1 && !team_sync(tm, ctl, bar, sh)) { stop = 5; break; }
       with_48_16(shp.ch, [&](auto C) { b_spmm<T, PP, decltype(C)::value>(tm.r0, tm.r1, pr.rowptr, pr.colind, vals, X, Y); });
       pass_barrier();
+      clk.mark(GSI_PASS_REFRESH);
       if (!team_gram<T, PP>(tm, ctl, pr, bar, sh, X, Y, nullptr, G3, nullptr, dl, v, 0, 0)) { stop = 5; break; }
+      clk.mark(GSI_PASS_GRAM);
       for (int e = threadIdx.x; e < PP * PP; e += blockDim.x) C[e] = 0.5 * (G3[e] + G3[(e % PP) * PP + e / PP]);
       pass_barrier();
       clk.mark(GSI_PASS_REFRESH);
@@ -1404,21 +1409,24 @@ gsi_status fetch(gsi_batch* b, std::vector<BatchProblem>& res) {
   return GSI_OK;
 }
 
+// Estimated time of an iteration of q by t workgroups, in units of a 64-row tile of 32 float64
+// columns (13.6 us; one of 16 columns takes 0.7 of it, whatever p is): the tiles over t, a fixed
+// part for the p x p work and one for a team's barriers.
+double iteration_cost(const BatchProblem& q, int t, bool mixed) {
+  const bool wide = q.PP > 16;
+  const double size = mixed ? 0.6 : 1.0;  // most iterations of a mixed solve are float32
+  return size * q.tiles * (wide ? 1.0 : 0.7) / t + (wide ? 16.0 : 5.0) + (t > 1 ? 5.0 : 0.0);
+}
+
 // Start teams. One workgroup streams a block at a rate of its own whatever the rest of the
 // device does, so the largest problems decide when a batch ends: of 256 problems of 1 to 25 thousand
-// rows the last ran 2.4 times as long as the mean workgroup. Estimated time of an iteration by t
-// workgroups, in units of a 64-row tile of 32 float64 columns (13.6 us; one of 16 columns takes 0.7
-// of it): the tiles over t, a fixed part for the p x p work and one for a team's barriers. For a T, every problem gets the
-// fewest members (at most one per TPM_DEF tiles) that bring it under T; the T is taken that ends
-// the batch first on `slots` workgroups. Sets team0; returns the members in all. Recruiting alone,
-// every 32 iterations, took 251 ms for those 256 problems and 60 iterations, 130 ms for 5 problems of
-// 3600 to 19600 rows and 83 ms for 17 of 1600 to 12100; with start teams 205, 25 and 25 ms.
+// rows the last ran 2.4 times as long as the mean workgroup. For a T, every problem gets the fewest
+// members (at most one per TPM_DEF tiles) that bring its iteration under T; the T is taken that
+// ends the batch first on `slots` workgroups. Sets team0; returns the members in all. Recruiting
+// alone, every 32 iterations, took 251 ms for those 256 problems and 60 iterations, 130 ms for 5
+// problems of 3600 to 19600 rows and 83 ms for 17 of 1600 to 12100; with start teams 205, 25 and 25 ms.
 int start_teams(std::vector<BatchProblem>& probs, int slots, bool mixed) {
-  const double size = mixed ? 0.6 : 1.0;  // most iterations of a mixed solve are float32
-  auto cost = [&](const BatchProblem& q, int t) {
-    const bool wide = q.PP > 16;
-    return size * q.tiles * (wide ? 1.0 : 0.7) / t + (wide ? 16.0 : 5.0) + (t > 1 ? 5.0 : 0.0);
-  };
+  auto cost = [&](const BatchProblem& q, int t) { return iteration_cost(q, t, mixed); };
   auto cap = [](const BatchProblem& q) { return std::max(1, std::min(q.tiles / TPM_DEF, q.tcap)); };
   auto members = [&](const BatchProblem& q, double T) {
     int t = 1;
@@ -1579,13 +1587,14 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
   if (e != hipSuccess) { b->err = std::string("kernel attributes: ") + hipGetErrorString(e); return GSI_EDEVICE; }
   const int slots = ncu * std::max(per_cu, 1);  // workgroups resident at once
   const int members = start_teams(b->hprobs, slots, b->mixed != 0);
-  // queue: largest n * p first (longest-processing-time order), the start teams before all
+  // queue: longest first by the estimate, the start teams before all. (By n p a problem of few
+  // columns, whose blocks are padded to 16, starts too late: one of 17424 x 4 ended a batch alone.)
   std::vector<int32_t> order(count);
   for (int i = 0; i < count; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
     const BatchProblem &pa = b->hprobs[a], &pc = b->hprobs[c];
     if ((pa.team0 > 1) != (pc.team0 > 1)) return pa.team0 > 1;
-    return pa.n * pa.p > pc.n * pc.p;
+    return iteration_cost(pa, 1, b->mixed != 0) > iteration_cost(pc, 1, b->mixed != 0);
   });
   std::vector<QEntry> start;
   for (int i : order)
