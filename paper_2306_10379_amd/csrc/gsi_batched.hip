@@ -68,8 +68,8 @@ struct BatchProblem {
 
 // Loop state handed by a problem's first member to the workgroups that join it.
 struct LoopState {
-  int32_t k, k_best, restart_next, v_valid, phase, team, base, xc;
-  double gg_old, rho_best;
+  int32_t k, k_best, restart_next, v_valid, phase, team, base, xc, have_grad, pad;
+  double gg_old, rho_best, gg, gdot;
 };
 
 struct QEntry {
@@ -255,7 +255,7 @@ struct GramAcc {
 // G = X C - Y over tiles [ta, tb), K = X^T G; sums of G^2 and G_old G, max absolute row sum. A
 // pass of its own for K read X and G once more from memory: the eight passes of an iteration moved
 // 22 blocks where these move 17, and with a workgroup on every CU the batch runs at the
-// memory's rate (5.1 TB/s): 217 -> 190 ms for 256 problems of 1 to 25 thousand rows.
+// memory's rate (5.1 TB/s): 217 -> 190 ms for 256 problems of 1 to 25 thousand rows (22 -> 17).
 template <typename T, int PP, int U>
 __device__ __noinline__ void b_grad(int64_t n, int64_t ta, int64_t tb, const T* X, const T* Y, const T* Gold, T* G,
                                     const T* sC, bool have_old, double* sums, double* red, double* kout) {
@@ -349,52 +349,105 @@ __device__ __noinline__ void b_dir(int64_t n, int64_t ta, int64_t tb, const T* X
   S.template flush<true>(red, sout);
 }
 
-// X <- (X - mu P) M, Y <- (Y - mu Z) M over tiles [ta, tb) (Y skipped when upd_y is false).
+// X <- (X - mu P) M over tiles [ta, tb): the retraction before A X is recomputed.
 template <typename T, int PP, int U>
-__device__ __noinline__ void b_update(int64_t n, int64_t ta, int64_t tb, T* X, T* Y, const T* P, const T* Z,
-                                      const T* sM, T mu, bool upd_y) {
+__device__ __noinline__ void b_update(int64_t n, int64_t ta, int64_t tb, T* X, const T* P, const T* sM, T mu) {
   const int w = threadIdx.x >> 6;
   sM = to_lds(sM);
   for (int64_t t = ta; t < tb; t += U) {
-    T a1[U][PP / 4], b1[U][PP / 4], a2[U][PP / 4], b2[U][PP / 4];
+    T a[U][PP / 4], d[U][PP / 4];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t row0 = (t + u) * TR + 16 * w, nv = t + u < tb ? n : 0;
-      load_al<T, PP>(X, row0, nv, a1[u]);
-      load_al<T, PP>(P, row0, nv, b1[u]);
-      if (upd_y) {
-        load_al<T, PP>(Y, row0, nv, a2[u]);
-        load_al<T, PP>(Z, row0, nv, b2[u]);
-      }
+      load_al<T, PP>(X, row0, nv, a[u]);
+      load_al<T, PP>(P, row0, nv, d[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t row0 = (t + u) * TR + 16 * w, nv = t + u < tb ? n : 0;
 #pragma unroll
-      for (int s = 0; s < PP / 4; ++s) a1[u][s] = a1[u][s] - mu * b1[u][s];
-      typename Vec4<T>::type xacc[PP / 16], yacc[PP / 16];
+      for (int s = 0; s < PP / 4; ++s) a[u][s] = a[u][s] - mu * d[u][s];
+      typename Vec4<T>::type acc[PP / 16];
+      zero_acc<T, PP>(acc);
+      product<T, PP>(a[u], sM, acc);
+      T xo[PP / 16][4];
+#pragma unroll
+      for (int cb = 0; cb < PP / 16; ++cb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xo[cb][r] = acc[cb][r];
+      // every wave reads and writes only its own rows, so in-place is safe
+      store_rl<T, PP>(X, row0, nv, xo);
+    }
+  }
+}
+
+// X <- (X - mu P) M, Y <- (Y - mu Z) M over tiles [ta, tb) and the next gradient from the same
+// operands: G = X C_new - Y = (X_old - mu P) MC - Y with MC = M C_new, K = X^T G, and the sums of
+// b_grad. The gradient then reads X and Y no more: 15 blocks an iteration instead of 17, 160 -> 152 ms
+// for 256 problems of 1 to 25 thousand rows.
+template <typename T, int PP, int U>
+__device__ __noinline__ void b_update_grad(int64_t n, int64_t ta, int64_t tb, T* X, T* Y, const T* P, const T* Z,
+                                           const T* Gold, T* G, const T* sM, const T* sMC, T mu, double* sums,
+                                           double* red, double* kout) {
+  const int w = threadIdx.x >> 6;
+  sM = to_lds(sM);
+  sMC = to_lds(sMC);
+  red = to_lds(red);
+  double gg = 0.0, gdot = 0.0, ginf = 0.0;
+  GramAcc<T, PP> K;
+  K.zero();
+  for (int64_t t = ta; t < tb; t += U) {
+    T a1[U][PP / 4], b1[U][PP / 4], a2[U][PP / 4], b2[U][PP / 4], go[U][PP / 16][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t row0 = (t + u) * TR + 16 * w, nv = t + u < tb ? n : 0;
+      load_al<T, PP>(X, row0, nv, a1[u]);
+      load_al<T, PP>(P, row0, nv, b1[u]);
+      load_al<T, PP>(Y, row0, nv, a2[u]);
+      load_al<T, PP>(Z, row0, nv, b2[u]);
+      load_rl<T, PP>(Gold, row0, nv, go[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t row0 = (t + u) * TR + 16 * w, nv = t + u < tb ? n : 0;
+#pragma unroll
+      for (int s = 0; s < PP / 4; ++s) {
+        a1[u][s] = a1[u][s] - mu * b1[u][s];
+        a2[u][s] = a2[u][s] - mu * b2[u][s];
+      }
+      typename Vec4<T>::type xacc[PP / 16], yacc[PP / 16], gacc[PP / 16];
       zero_acc<T, PP>(xacc);
       zero_acc<T, PP>(yacc);
-      if (upd_y) {
-#pragma unroll
-        for (int s = 0; s < PP / 4; ++s) a2[u][s] = a2[u][s] - mu * b2[u][s];
-        product2<T, PP>(a1[u], a2[u], sM, xacc, yacc);
-      } else {
-        product<T, PP>(a1[u], sM, xacc);
-      }
-      T xo[PP / 16][4], yo[PP / 16][4];
+      zero_acc<T, PP>(gacc);
+      product2<T, PP>(a1[u], a2[u], sM, xacc, yacc);
+      product<T, PP>(a1[u], sMC, gacc);
+      T xo[PP / 16][4], yo[PP / 16][4], g[PP / 16][4];
+      double rs[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int cb = 0; cb < PP / 16; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           xo[cb][r] = xacc[cb][r];
           yo[cb][r] = yacc[cb][r];
+          g[cb][r] = gacc[cb][r] - yacc[cb][r];
+          const double gv = (double)g[cb][r];
+          gg += gv * gv;
+          gdot += (double)go[u][cb][r] * gv;
+          rs[r] += fabs(gv);
         }
       // every wave reads and writes only its own rows, so in-place is safe
       store_rl<T, PP>(X, row0, nv, xo);
-      if (upd_y) store_rl<T, PP>(Y, row0, nv, yo);
+      store_rl<T, PP>(Y, row0, nv, yo);
+      store_rl<T, PP>(G, row0, nv, g);
+      K.add(xo, g);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ginf = fmax(ginf, group16_sum(rs[r]));
     }
   }
+  sums[0] = gg;
+  sums[1] = gdot;
+  sums[2] = ginf;
+  K.flush(red, kout);
 }
 
 // IN <- IN M in place over tiles [ta, tb).
@@ -719,7 +772,7 @@ __device__ __noinline__ int b_eig(double* small, int p, bool warm, double* lds) 
 template <int PP>
 __device__ __noinline__ void b_linesearch(const double* PZr, const double* PYr, double* small, int p, double* lds,
                                           Terms& terms, double* smu, int* sok, int* sevals, double* sbmax) {
-  linesearch_dev<PP>(PZr, PYr, small, p, to_lds(lds), terms, smu, sok, sevals, sbmax);
+  linesearch_dev<PP>(PZr, PYr, small, p, to_lds(lds), terms, smu, sok, sevals, sbmax, true);
 }
 
 // ---------------------------------------------------------------- one problem
@@ -891,6 +944,8 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
   double* PZ = small + S_PZ * PP * PP;
   double* PY = small + S_PY * PP * PP;
   double* M = small + S_M * PP * PP;
+  double* MC = small + S_MC * PP * PP;
+  T* sMC = reinterpret_cast<T*>(dl + 2 * PP * PP);  // clear of the Gram's reduction at dl
   double* G2 = small + S_T1 * PP * PP;
   double* G3 = small + S_T2 * PP * PP;
   const double sqrt_p = sqrt((double)p);
@@ -898,9 +953,12 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
   const Shape shp = Shape::of<T, PP>(pr.shape);
   int k, k_best, restarts = 0, nulls = 0, stop = 0;
   double gg_old, rho = 0.0, rho_best;
-  bool v_valid;
-  double v[4];
+  bool v_valid, have_grad = false;  // have_grad: the last retraction left G, K, gg and gdot of iteration k
+  double v[4], gg = 0.0, gdot = 0.0;
   if (join) {
+    have_grad = join->have_grad != 0;
+    gg = join->gg;
+    gdot = join->gdot;
     k = join->k;
     k_best = join->k_best;
     gg_old = join->gg_old;
@@ -984,6 +1042,9 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
           ls->team = tm.t + want;
           ls->base = tm.base + (tm.t > 1 ? (tm.gen + 1) * tm.t : 0);
           ls->xc = tm.xc;
+          ls->have_grad = have_grad ? 1 : 0;
+          ls->gg = gg;
+          ls->gdot = gdot;
           ls->gg_old = gg_old;
           ls->rho_best = rho_best;
           __threadfence();
@@ -1013,20 +1074,24 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
       }
     }
     const int par = k & 1;
-    // gradient pass and K = X^T G
-    b_load_matrix<T, PP>(sMat, C);
-    __syncthreads();
     double sums[3];
-    with_124(shp.u, [&](auto U) { b_grad<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Y, Gb[par ^ 1], Gb[par], sMat, k > 0, sums, dl, gram_slot<PP>(tm, pr, 0, K)); });
-    double gg = sums[0], gdot = sums[1], ginf = sums[2];
-    b_reduce3(gg, gdot, ginf, sh.red);
-    v[0] = gg;
-    v[1] = gdot;
-    v[2] = ginf;
-    if (!team_sums<PP>(tm, ctl, pr, bar, sh, 1, K, nullptr, v, 2, 1)) { stop = 5; break; }
-    gg = v[0];
-    gdot = v[1];
-    clk.mark(GSI_PASS_GRAD);
+    if (!have_grad) {  // gradient pass and K = X^T G
+      b_load_matrix<T, PP>(sMat, C);
+      __syncthreads();
+      with_124(shp.u, [&](auto U) {
+        b_grad<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Y, Gb[par ^ 1], Gb[par], sMat, k > 0, sums, dl,
+                                          gram_slot<PP>(tm, pr, 0, K));
+      });
+      b_reduce3(sums[0], sums[1], sums[2], sh.red);
+      v[0] = sums[0];
+      v[1] = sums[1];
+      v[2] = sums[2];
+      if (!team_sums<PP>(tm, ctl, pr, bar, sh, 1, K, nullptr, v, 2, 1)) { stop = 5; break; }
+      gg = v[0];
+      gdot = v[1];
+      clk.mark(GSI_PASS_GRAD);
+    }
+    have_grad = false;
     rho = sqrt(gg) / (sqrt_p * pr.nA);
     if (k == k_first || rho <= 0.5 * rho_best) { rho_best = rho; k_best = k; }
     if (!isfinite(gg)) stop = 3;
@@ -1082,11 +1147,28 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
     const double mu = sh.smu;
     const bool refresh = ctl->recompute_ax || mu * sqrt(sh.sbmax) <= 1e3 * EPS;
     restarts += restart ? 1 : 0;
-    // retraction
+    gg_old = gg;
+    // retraction, with the next gradient unless Y is about to be recomputed
     b_load_matrix<T, PP>(sMat, M);
+    if (!refresh) b_load_matrix<T, PP>(sMC, MC);
     __syncthreads();
-    with_12(shp.uu, [&](auto U) { b_update<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Y, Pb[par], Z, sMat, (T)mu, !refresh); });
-    pass_barrier();
+    if (!refresh) {
+      with_12(shp.uu, [&](auto U) {
+        b_update_grad<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Y, Pb[par], Z, Gb[par], Gb[par ^ 1], sMat, sMC, (T)mu,
+                                                 sums, dl, gram_slot<PP>(tm, pr, 0, K));
+      });
+      b_reduce3(sums[0], sums[1], sums[2], sh.red);
+      v[0] = sums[0];
+      v[1] = sums[1];
+      v[2] = sums[2];
+      if (!team_sums<PP>(tm, ctl, pr, bar, sh, 1, K, nullptr, v, 2, 1)) { stop = 5; break; }
+      gg = v[0];
+      gdot = v[1];
+      have_grad = true;
+    } else {
+      with_12(shp.uu, [&](auto U) { b_update<T, PP, decltype(U)::value>(n, tm.ta, tm.tb, X, Pb[par], sMat, (T)mu); });
+      pass_barrier();
+    }
     clk.mark(GSI_PASS_UPDATE);
     if (refresh) {
       if (tm.t > 1 && !team_sync(tm, ctl, bar, sh)) { stop = 5; break; }
@@ -1099,7 +1181,6 @@ __device__ __noinline__ int solve_phase(BatchProblem& pr, BatchCtl* ctl, int idx
       pass_barrier();
       clk.mark(GSI_PASS_REFRESH);
     }
-    gg_old = gg;
     if (threadIdx.x == 0) sh.restart_next = 0;
     __syncthreads();
     ++k;
