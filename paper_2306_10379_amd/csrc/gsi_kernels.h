@@ -48,10 +48,11 @@ struct Kernels {
   // the retraction fused with the next gradient (k_update_grad); partials as for grad
   static void update_grad(hipStream_t st, int nb, int64_t n, T* X, T* Y, const T* P0, const T* P1, const T* Z,
                           T* G0, T* G1, const double* small, const Scalars* sc, double* partials);
-  // plane_tiles > 0: banded tile order (see spmm_tile in gsi_kernels.hip); 0: one slab per XCD
+  // plane_tiles > 0: banded tile order (see spmm_tile in gsi_kernels.hip); 0: one slab per XCD;
+  // p: columns of the block in use (the others are zero)
   static void spmm(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const T* vals,
                    const T* W0, const T* W1, T* Z, const Scalars* sc, int mode, int64_t plane_tiles = 0,
-                   int batch = 8);
+                   int batch = 8, int p = PP);
   // A^T B1 (and A^T B2 when B2 != nullptr); mode as for spmm (mode 1 picks A0/A1 by parity)
   static void gram(hipStream_t st, int nb, int64_t n, const T* A0, const T* A1, const T* B1, const T* B2,
                    const Scalars* sc, int mode, double* partials);
@@ -59,15 +60,15 @@ struct Kernels {
   // Z = A W with bfloat16 values and W, float32 accumulation and output
   static void spmm16(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const uint16_t* vals,
                      const uint16_t* W, float* Z, const Scalars* sc, int mode, int64_t plane_tiles = 0,
-                     int batch = 8);
+                     int batch = 8, int p = PP);
   // Z = alpha (A W) + beta W + gamma V (V nullable), always runs
   static void spmm_axpy(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const T* vals,
                         const T* W, const T* V, T* Z, double alpha, double beta, double gamma,
-                        int64_t plane_tiles = 0, int batch = 8);
+                        int64_t plane_tiles = 0, int batch = 8, int p = PP);
   // Z (float64) = A W from float32 values and W, float64 products and accumulation
   static void spmm_fin(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const float* vals,
                        const float* W, double* Z, const Scalars* sc, int mode, int64_t plane_tiles = 0,
-                       int batch = 8);
+                       int batch = 8, int p = PP);
   static void colres(hipStream_t st, int nb, int64_t n, const T* X, const T* Y, const double* theta,
                      double* partials);
   // matrix-free stencil operator on the grid dims[0] x dims[1] x dims[2] (host array):

@@ -887,7 +887,7 @@ template <typename T, int PP, int U>
 __global__ __launch_bounds__(WG) void k_spmm(int64_t n, const int32_t* __restrict__ rowptr,
                                              const int32_t* __restrict__ colind, const T* __restrict__ vals,
                                              const T* __restrict__ W0, const T* __restrict__ W1, T* __restrict__ Z,
-                                             const Scalars* __restrict__ sc, int mode, int64_t plane_tiles) {
+                                             const Scalars* __restrict__ sc, int mode, int64_t plane_tiles, int cols) {
   if (spmm_skip(sc, mode)) return;
   const T* W = (mode == 1 && (sc->k & 1)) ? W1 : W0;
   constexpr int EPL = 16 / (int)sizeof(T);  // columns per lane: one 16-byte gather per nonzero
@@ -910,7 +910,7 @@ __global__ __launch_bounds__(WG) void k_spmm(int64_t n, const int32_t* __restric
     const int64_t row = r0 + lr;
     typedef typename std::conditional<sizeof(T) == 8, d2, f4>::type V16;
     V16 acc = {};
-    const int32_t j0 = s_rp[lr], j1 = s_rp[lr + 1];
+    const int32_t j0 = s_rp[lr], j1 = EPL * lane < cols ? s_rp[lr + 1] : j0;
     for (int32_t j = j0; j < j1; j += U) {
       int32_t col[U];
       T v[U];
@@ -947,7 +947,7 @@ template <int PP, int U>
 __global__ __launch_bounds__(WG) void k_spmm16(int64_t n, const int32_t* __restrict__ rowptr,
                                                const int32_t* __restrict__ colind, const uint16_t* __restrict__ vals,
                                                const uint16_t* __restrict__ W, float* __restrict__ Z,
-                                               const Scalars* __restrict__ sc, int mode, int64_t plane_tiles) {
+                                               const Scalars* __restrict__ sc, int mode, int64_t plane_tiles, int cols) {
   if (spmm_skip(sc, mode)) return;
   constexpr int EPL = 8;
   constexpr int LPR = PP / EPL;  // lanes per row
@@ -972,7 +972,7 @@ __global__ __launch_bounds__(WG) void k_spmm16(int64_t n, const int32_t* __restr
     float acc[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-    const int32_t j0 = s_rp[lr], j1 = s_rp[lr + 1];
+    const int32_t j0 = s_rp[lr], j1 = EPL * lane < cols ? s_rp[lr + 1] : j0;
     for (int32_t j = j0; j < j1; j += U) {
       int32_t col[U];
       float v[U];
@@ -1013,7 +1013,7 @@ template <int PP, int U>
 __global__ __launch_bounds__(WG) void k_spmm_fin(int64_t n, const int32_t* __restrict__ rowptr,
                                                  const int32_t* __restrict__ colind, const float* __restrict__ vals,
                                                  const float* __restrict__ W, double* __restrict__ Z,
-                                                 const Scalars* __restrict__ sc, int mode, int64_t plane_tiles) {
+                                                 const Scalars* __restrict__ sc, int mode, int64_t plane_tiles, int cols) {
   if (spmm_skip(sc, mode)) return;
   constexpr int EPL = 4;
   constexpr int LPR = PP / EPL;  // lanes per row
@@ -1035,7 +1035,7 @@ __global__ __launch_bounds__(WG) void k_spmm_fin(int64_t n, const int32_t* __res
     if (lr >= nrows) continue;
     const int64_t row = r0 + lr;
     double acc[EPL] = {0.0, 0.0, 0.0, 0.0};
-    const int32_t j0 = s_rp[lr], j1 = s_rp[lr + 1];
+    const int32_t j0 = s_rp[lr], j1 = EPL * lane < cols ? s_rp[lr + 1] : j0;
     for (int32_t j = j0; j < j1; j += U) {
       int32_t col[U];
       double v[U];
@@ -1071,7 +1071,7 @@ template <typename T, int PP, int U>
 __global__ __launch_bounds__(WG) void k_spmm_axpy(int64_t n, const int32_t* __restrict__ rowptr,
                                                   const int32_t* __restrict__ colind, const T* __restrict__ vals,
                                                   const T* __restrict__ W, const T* __restrict__ V, T* __restrict__ Z,
-                                                  double alpha, double beta, double gamma, int64_t plane_tiles) {
+                                                  double alpha, double beta, double gamma, int64_t plane_tiles, int cols) {
   typedef typename std::conditional<sizeof(T) == 8, d2, f4>::type V16;
   constexpr int EPL = 16 / (int)sizeof(T);  // one 16-byte gather per nonzero per lane
   constexpr int LPR = PP / EPL;
@@ -1092,7 +1092,7 @@ __global__ __launch_bounds__(WG) void k_spmm_axpy(int64_t n, const int32_t* __re
     if (lr >= nrows) continue;
     const int64_t row = r0 + lr;
     V16 acc = {};
-    const int32_t j0 = s_rp[lr], j1 = s_rp[lr + 1];
+    const int32_t j0 = s_rp[lr], j1 = EPL * lane < cols ? s_rp[lr + 1] : j0;
     for (int32_t j = j0; j < j1; j += U) {
       int32_t col[U];
       T v[U];
@@ -2037,17 +2037,23 @@ void Kernels<T, PP>::dir(hipStream_t st, int nb, int64_t n, const T* X, const T*
   else
     k_dir<T, PP><<<nb, WG, lds_bytes<T, PP>(Pass::Dir), st>>>(n, X, G0, G1, P0, P1, small, sc, partials, P16, P32);
 }
+// Columns of a block that the CSR products gather: p up to whole 16-column groups (a cache line in
+// float64). The padding columns past them are zero in W and are written as zeros; their lanes have
+// no nonzeros to go through. On random columns the gathers are the cost: 428 -> 335 us at n = 250007,
+// 17 nonzeros a row, p = 40.
+static int live_cols(int p) { return (p + 15) / 16 * 16; }
 template <typename T, int PP>
 void Kernels<T, PP>::spmm_axpy(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const T* vals,
                                const T* W, const T* V, T* Z, double alpha, double beta, double gamma,
-                               int64_t plane_tiles, int batch) {
+                               int64_t plane_tiles, int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
+  const int cols = live_cols(p);
   if (batch == 7)
     k_spmm_axpy<T, PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, V, Z, alpha, beta,
-                                                                    gamma, plane_tiles);
+                                                                    gamma, plane_tiles, cols);
   else
     k_spmm_axpy<T, PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, V, Z, alpha, beta,
-                                                                    gamma, plane_tiles);
+                                                                    gamma, plane_tiles, cols);
 }
 // Grids with at least SY rows in y march through their planes (k_spmm_march); lines use
 // the row-tile kernel.
@@ -2081,22 +2087,28 @@ void Kernels<T, PP>::spmm_stencil_axpy(hipStream_t st, int64_t n, const int32_t*
 template <typename T, int PP>
 void Kernels<T, PP>::spmm_fin(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind,
                               const float* vals, const float* W, double* Z, const Scalars* sc, int mode,
-                              int64_t plane_tiles, int batch) {
+                              int64_t plane_tiles, int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
+  const int cols = live_cols(p);
   if (batch == 7)
-    k_spmm_fin<PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles);
+    k_spmm_fin<PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
+                                                                 cols);
   else
-    k_spmm_fin<PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles);
+    k_spmm_fin<PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
+                                                                 cols);
 }
 template <typename T, int PP>
 void Kernels<T, PP>::spmm16(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind,
                             const uint16_t* vals, const uint16_t* W, float* Z, const Scalars* sc, int mode,
-                            int64_t plane_tiles, int batch) {
+                            int64_t plane_tiles, int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
+  const int cols = live_cols(p);
   if (batch == 7)
-    k_spmm16<PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles);
+    k_spmm16<PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
+                                                               cols);
   else
-    k_spmm16<PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles);
+    k_spmm16<PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
+                                                               cols);
 }
 template <typename T, int PP>
 void Kernels<T, PP>::update(hipStream_t st, int nb, int64_t n, T* X, T* Y, const T* P0, const T* P1, const T* Z,
@@ -2114,14 +2126,15 @@ void Kernels<T, PP>::update(hipStream_t st, int nb, int64_t n, T* X, T* Y, const
 template <typename T, int PP>
 void Kernels<T, PP>::spmm(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const T* vals,
                           const T* W0, const T* W1, T* Z, const Scalars* sc, int mode, int64_t plane_tiles,
-                          int batch) {
+                          int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
+  const int cols = live_cols(p);
   if (batch == 7)
     k_spmm<T, PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W0, W1, Z, sc, mode,
-                                                               plane_tiles);
+                                                               plane_tiles, cols);
   else
     k_spmm<T, PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W0, W1, Z, sc, mode,
-                                                               plane_tiles);
+                                                               plane_tiles, cols);
 }
 template <typename T, int PP>
 void Kernels<T, PP>::gram(hipStream_t st, int nb, int64_t n, const T* A0, const T* A1, const T* B1, const T* B2,
