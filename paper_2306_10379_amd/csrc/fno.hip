@@ -7,8 +7,8 @@
 // n x p row-major, as callers hold them. A layer is three kernels: k_sine_fwd (S U S^T of every
 // channel, both contractions), k_mix_inv (mixes the channels mode by mode and applies S from one
 // side) and k_layer (S from the other side, the pointwise mixing, bias and activation in one pass
-// over the grid); the backward pass runs the same three with the weights transposed. Gram-like reductions over the whole grid (weight gradients, the
-// p x p Grams of the loss) split the grid over workgroups and add the partial results in a fixed
+// over the grid); the backward pass runs the same three with the weights transposed. Gram-like
+// reductions over the whole grid (weight gradients, the p x p Grams of the loss) split the grid over workgroups and add the partial results in a fixed
 // order (k_pqt_small, k_gram_rows, k_sum_parts). Contractions are float32 MFMA. The p x p loss
 // algebra (Cholesky of Y^T Y) runs in float64, one workgroup per sample.
 #include <hip/hip_runtime.h>
@@ -567,7 +567,8 @@ __global__ __launch_bounds__(WG) void k_loss_small(const double* G, const double
 
 // Partial G = Y^T Y and Bm = X^T Y of sample blockIdx.y over the split's rows, Y and X n x p
 // row-major: lane (g, c) holds rows 4 g .. 4 g + 3 of a step, column 16 cb + c, both operands'
-// layout (the rows of a step share their cache lines over q). Partials of G in part, of Bm after those of all samples.
+// layout (the rows of a step share their cache lines over q). Partials of G in part, of Bm after
+// those of all samples.
 __global__ __launch_bounds__(WG) void k_gram_rows(const float* __restrict__ Y, const float* __restrict__ X, int p,
                                                   int64_t n, int splits, float* __restrict__ part) {
   __shared__ float red[2 * 1024];

@@ -3,8 +3,8 @@
 // first) and runs the whole Riemannian CG iteration for one problem with workgroup barriers
 // (a problem of more than an even share of the work starts with a team of workgroups that
 // splits its rows, see start_teams; once the queue has drained, a running problem may recruit
-// idle workgroups, see k_batched): gradient, direction, eigendecomposition of P^T P, SpMM, Grams, line search and
-// retraction (the same steps and readings as the single-problem path, see gsi_kernels.hip
+// idle workgroups, see k_batched): gradient, direction, eigendecomposition of P^T P, SpMM, Grams,
+// line search and retraction (the same steps and readings as the single-problem path, see gsi_kernels.hip
 // and gsi_small.hip). The p x p state is float64. Blocks are float64, or float32 first and
 // float64 after: the float32 phase runs until rho <= switch_tol (or rho stops improving),
 // then the iterate, the previous gradient and the previous direction are widened and the
@@ -12,8 +12,8 @@
 //
 // One workgroup owns a problem, so it must keep many loads in flight by itself: the
 // streaming passes issue the loads of 2-4 tiles before using any of them, every wave takes
-// part in each Gram (partial sums combined across waves in a fixed order), and the SpMM
-// gathers the nonzeros of a row in batches of 8.
+// part in each Gram (partial sums combined across waves in a fixed order; an iteration's Grams
+// ride on its streaming passes), and the SpMM gathers the nonzeros of a row in batches of 8.
 //
 // Passes read rows that other waves of the same workgroup wrote in the previous pass; an
 // agent-scope fence (L1 invalidation) plus a barrier separates passes.
@@ -254,8 +254,9 @@ struct GramAcc {
 
 // G = X C - Y over tiles [ta, tb), K = X^T G; sums of G^2 and G_old G, max absolute row sum. A
 // pass of its own for K read X and G once more from memory: the eight passes of an iteration moved
-// 22 blocks where these move 17, and with a workgroup on every CU the batch runs at the
-// memory's rate (5.1 TB/s): 217 -> 190 ms for 256 problems of 1 to 25 thousand rows (22 -> 17).
+// 22 blocks, 17 with the Grams on the passes that have their operands, and with a workgroup on
+// every CU a batch runs at the memory's rate (5.1 TB/s): 217 -> 190 ms for 256 problems of 1 to 25
+// thousand rows.
 template <typename T, int PP, int U>
 __device__ __noinline__ void b_grad(int64_t n, int64_t ta, int64_t tb, const T* X, const T* Y, const T* Gold, T* G,
                                     const T* sC, bool have_old, double* sums, double* red, double* kout) {

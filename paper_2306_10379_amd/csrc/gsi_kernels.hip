@@ -2040,7 +2040,7 @@ void Kernels<T, PP>::dir(hipStream_t st, int nb, int64_t n, const T* X, const T*
 // Columns of a block that the CSR products gather: p up to whole 16-column groups (a cache line in
 // float64). The padding columns past them are zero in W and are written as zeros; their lanes have
 // no nonzeros to go through. On random columns the gathers are the cost: 428 -> 335 us at n = 250007,
-// 17 nonzeros a row, p = 40.
+// 25 nonzeros a row, p = 40.
 static int live_cols(int p) { return (p + 15) / 16 * 16; }
 template <typename T, int PP>
 void Kernels<T, PP>::spmm_axpy(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const T* vals,

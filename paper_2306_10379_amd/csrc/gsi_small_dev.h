@@ -351,8 +351,9 @@ __device__ __forceinline__ void quad_diag(int nb, const double* V, const double*
 // it. Matrices sit in LDS at the stride that keeps the operand loads free of bank conflicts
 // (with a stride of PP each load hit one bank 16 times), the Grams are read coalesced, blocks
 // below the diagonal of symmetric products and past p are left out: k_linesearch 108 -> 64 us at
-// p = 64, 30 -> 27 us at p = 32, 15.5 -> 14.5 us at p = 8, 1010 -> 293 us at p = 128. Above PP = 64 one matrix fits LDS (V, then M in its two stages) and
-// the others sit in the work area of the small buffer, always read by rows.
+// p = 64, 30 -> 27 us at p = 32, 15.5 -> 14.5 us at p = 8, 1010 -> 293 us at p = 128. Above PP = 64
+// one matrix fits LDS (V, then M in its two stages) and the others sit in the work area of the
+// small buffer, always read by rows.
 constexpr int linesearch_lds_doubles(int PP) { return (PP > PP_LDS_MAX ? 1 : 4) * PP * (PP + 2); }
 
 template <int PP>
