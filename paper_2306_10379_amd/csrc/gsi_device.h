@@ -82,6 +82,8 @@ __device__ __forceinline__ uint16_t bf16_round(float f) {
 __device__ __forceinline__ float bf16_widen(uint32_t b) { return __uint_as_float(b << 16); }
 
 // ---------------------------------------------------------------- tile I/O (per wave)
+//
+// W: leading columns that are read, written or multiplied (the others are zero and stay so).
 
 template <typename T, int PP>
 __device__ __forceinline__ void zero_rl(T (&v)[PP / 16][4]) {
@@ -91,8 +93,8 @@ __device__ __forceinline__ void zero_rl(T (&v)[PP / 16][4]) {
     for (int r = 0; r < 4; ++r) v[cb][r] = T(0);
 }
 
-template <typename T, int PP>
-__device__ __forceinline__ void load_rl(const T* __restrict__ B, int64_t row0, int64_t n, T (&v)[PP / 16][4]) {
+template <typename T, int PP, int W = PP>
+__device__ __forceinline__ void load_rl(const T* __restrict__ B, int64_t row0, int64_t n, T (&v)[W / 16][4]) {
   const int l = threadIdx.x & 63, g = l >> 4, c = l & 15;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -100,12 +102,12 @@ __device__ __forceinline__ void load_rl(const T* __restrict__ B, int64_t row0, i
     const bool ok = row < n;
     const T* p = B + (ok ? row : 0) * PP + c;
 #pragma unroll
-    for (int cb = 0; cb < PP / 16; ++cb) v[cb][r] = ok ? gld(p + 16 * cb) : T(0);
+    for (int cb = 0; cb < W / 16; ++cb) v[cb][r] = ok ? gld(p + 16 * cb) : T(0);
   }
 }
 
-template <typename T, int PP>
-__device__ __forceinline__ void store_rl(T* __restrict__ B, int64_t row0, int64_t n, const T (&v)[PP / 16][4]) {
+template <typename T, int PP, int W = PP>
+__device__ __forceinline__ void store_rl(T* __restrict__ B, int64_t row0, int64_t n, const T (&v)[W / 16][4]) {
   const int l = threadIdx.x & 63, g = l >> 4, c = l & 15;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -113,21 +115,21 @@ __device__ __forceinline__ void store_rl(T* __restrict__ B, int64_t row0, int64_
     if (row < n) {
       T* p = B + row * PP + c;
 #pragma unroll
-      for (int cb = 0; cb < PP / 16; ++cb) gst(p + 16 * cb, v[cb][r]);
+      for (int cb = 0; cb < W / 16; ++cb) gst(p + 16 * cb, v[cb][r]);
     }
   }
 }
 
 // A-operand layout: lane (g, c) holds row c; k-step s holds column kappa(s, g).
-template <typename T, int PP>
-__device__ __forceinline__ void load_al(const T* __restrict__ B, int64_t row0, int64_t n, T (&a)[PP / 4]) {
+template <typename T, int PP, int W = PP>
+__device__ __forceinline__ void load_al(const T* __restrict__ B, int64_t row0, int64_t n, T (&a)[W / 4]) {
   constexpr int E = AL<T>::E;
   const int l = threadIdx.x & 63, g = l >> 4, c = l & 15;
   const int64_t row = row0 + c;
   const bool ok = row < n;
   const T* p = B + (ok ? row : 0) * PP + E * g;
 #pragma unroll
-  for (int t = 0; t < PP / (4 * E); ++t) {
+  for (int t = 0; t < W / (4 * E); ++t) {
     if constexpr (E == 2) {
       const d2 q = ok ? gld(reinterpret_cast<const d2*>(p + 4 * E * t)) : d2{0.0, 0.0};
       a[E * t + 0] = q.x;
@@ -143,15 +145,15 @@ __device__ __forceinline__ void load_al(const T* __restrict__ B, int64_t row0, i
 }
 
 // acc[ncb] (RL, 16 x PP) += A (AL, 16 x PP) * M (PP x PP, row-major in LDS).
-template <typename T, int PP>
-__device__ __forceinline__ void product(const T (&a)[PP / 4], const T* __restrict__ M,
-                                        typename Vec4<T>::type (&acc)[PP / 16]) {
+template <typename T, int PP, int W = PP>
+__device__ __forceinline__ void product(const T (&a)[W / 4], const T* __restrict__ M,
+                                        typename Vec4<T>::type (&acc)[W / 16]) {
   const int l = threadIdx.x & 63, g = l >> 4, c = l & 15;
 #pragma unroll
-  for (int s = 0; s < PP / 4; ++s) {
+  for (int s = 0; s < W / 4; ++s) {
     const T* mrow = M + AL<T>::kappa(s, g) * PP + c;
 #pragma unroll
-    for (int ncb = 0; ncb < PP / 16; ++ncb) acc[ncb] = mfma(a[s], mrow[16 * ncb], acc[ncb]);
+    for (int ncb = 0; ncb < W / 16; ++ncb) acc[ncb] = mfma(a[s], mrow[16 * ncb], acc[ncb]);
     // at PP = 128 the unrolled loop holds 256 operand loads, which the scheduler would issue
     // all at once (spilling); one k-step at a time keeps 8 in flight
     if constexpr (PP > 64) __builtin_amdgcn_sched_barrier(0);
@@ -159,16 +161,16 @@ __device__ __forceinline__ void product(const T (&a)[PP / 4], const T* __restric
 }
 
 // Two products with the same right factor: acc1 += A1 * M, acc2 += A2 * M.
-template <typename T, int PP>
-__device__ __forceinline__ void product2(const T (&a1)[PP / 4], const T (&a2)[PP / 4], const T* __restrict__ M,
-                                         typename Vec4<T>::type (&acc1)[PP / 16],
-                                         typename Vec4<T>::type (&acc2)[PP / 16]) {
+template <typename T, int PP, int W = PP>
+__device__ __forceinline__ void product2(const T (&a1)[W / 4], const T (&a2)[W / 4], const T* __restrict__ M,
+                                         typename Vec4<T>::type (&acc1)[W / 16],
+                                         typename Vec4<T>::type (&acc2)[W / 16]) {
   const int l = threadIdx.x & 63, g = l >> 4, c = l & 15;
 #pragma unroll
-  for (int s = 0; s < PP / 4; ++s) {
+  for (int s = 0; s < W / 4; ++s) {
     const T* mrow = M + AL<T>::kappa(s, g) * PP + c;
 #pragma unroll
-    for (int ncb = 0; ncb < PP / 16; ++ncb) {
+    for (int ncb = 0; ncb < W / 16; ++ncb) {
       const T b = mrow[16 * ncb];
       acc1[ncb] = mfma(a1[s], b, acc1[ncb]);
       acc2[ncb] = mfma(a2[s], b, acc2[ncb]);

@@ -402,7 +402,8 @@ void launch_iteration(gsi_ctx* h, Engine<T>& e, double* hist, Sequence seq = SEQ
     }
     {
       PassTimer t(h, GSI_PASS_DIR);
-      Kernels<T, PP>::dir(h->st, e.nb, e.n, e.X, e.G0, e.G1, e.P0, e.P1, e.small, e.sc, h->partials, e.P16, e.P32);
+      Kernels<T, PP>::dir(h->st, e.nb, e.n, e.X, e.G0, e.G1, e.P0, e.P1, e.small, e.sc, h->partials, h->p, e.P16,
+                          e.P32);
     }
     {
       const Partials f = reduced(e.nb, P2 + 1, P2 + 1, 1);
@@ -452,7 +453,7 @@ void launch_iteration(gsi_ctx* h, Engine<T>& e, double* hist, Sequence seq = SEQ
       PassTimer t(h, GSI_PASS_UPDATE);
       if (fused)
         Kernels<T, PP>::update_grad(h->st, e.nb, e.n, e.X, e.Y, e.P0, e.P1, e.Z, e.G0, e.G1, e.small, e.sc,
-                                    h->partials);
+                                    h->partials, h->p);
       else
         Kernels<T, PP>::update(h->st, e.nb, e.n, e.X, e.Y, e.P0, e.P1, e.Z, e.small, e.sc, h->partials,
                                e.explicit_grams);

@@ -41,13 +41,13 @@ struct Kernels {
                    const Scalars* sc, double* partials, int cond = GRAD_ALWAYS);
   // P16 / P32 (nullable): bfloat16 / float32 copy of P written beside it
   static void dir(hipStream_t st, int nb, int64_t n, const T* X, const T* G0, const T* G1, T* P0, T* P1,
-                  const double* small, const Scalars* sc, double* partials, uint16_t* P16 = nullptr,
+                  const double* small, const Scalars* sc, double* partials, int p, uint16_t* P16 = nullptr,
                   float* P32 = nullptr);
   static void update(hipStream_t st, int nb, int64_t n, T* X, T* Y, const T* P0, const T* P1, const T* Z,
                      const double* small, const Scalars* sc, double* partials, bool grams);
   // the retraction fused with the next gradient (k_update_grad); partials as for grad
   static void update_grad(hipStream_t st, int nb, int64_t n, T* X, T* Y, const T* P0, const T* P1, const T* Z,
-                          T* G0, T* G1, const double* small, const Scalars* sc, double* partials);
+                          T* G0, T* G1, const double* small, const Scalars* sc, double* partials, int p);
   // plane_tiles > 0: banded tile order (see spmm_tile in gsi_kernels.hip); 0: one slab per XCD;
   // p: columns of the block in use (the others are zero)
   static void spmm(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const T* vals,

@@ -135,8 +135,8 @@ __global__ __launch_bounds__(WG) void k_grad(int64_t n, const T* __restrict__ X,
 // P = (I - X X^T)(G + beta P_old) = G + beta P_old - X (K + beta W)   (Sec. 5.1, eq. Pnew,
 // projected onto the tangent space as in Algorithm 4), fused with <G, P> and S = P^T P (its
 // upper blocks formed, the lower ones mirrored).
-// Partials: S (PP*PP), <G,P>.
-template <typename T, int PP>
+// Partials: S (PP*PP), <G,P>. W: columns in use (see k_update_grad).
+template <typename T, int PP, int W = PP>
 __global__ __launch_bounds__(WG) void k_dir(int64_t n, const T* __restrict__ X, const T* __restrict__ G0,
                                             const T* __restrict__ G1, T* __restrict__ P0, T* __restrict__ P1,
                                             const double* __restrict__ small, const Scalars* __restrict__ sc,
@@ -167,26 +167,26 @@ __global__ __launch_bounds__(WG) void k_dir(int64_t n, const T* __restrict__ X, 
   double gp = 0.0;
   for (int64_t t = t0; t < t1; ++t) {
     const int64_t row0 = t * TR + 16 * w;
-    T a[PP / 4];
-    load_al<T, PP>(X, row0, n, a);
-    typename Vec4<T>::type acc[PP / 16];
-    zero_acc<T, PP>(acc);
-    product<T, PP>(a, sK, acc);
-    T g[PP / 16][4], p[PP / 16][4];
-    load_rl<T, PP>(G, row0, n, g);
+    T a[W / 4];
+    load_al<T, PP, W>(X, row0, n, a);
+    typename Vec4<T>::type acc[W / 16];
+    zero_acc<T, W>(acc);
+    product<T, PP, W>(a, sK, acc);
+    T g[W / 16][4], p[W / 16][4];
+    load_rl<T, PP, W>(G, row0, n, g);
     if (use_old) {
-      load_rl<T, PP>(Pold, row0, n, p);
+      load_rl<T, PP, W>(Pold, row0, n, p);
 #pragma unroll
-      for (int cb = 0; cb < PP / 16; ++cb)
+      for (int cb = 0; cb < W / 16; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) p[cb][r] = g[cb][r] + beta * p[cb][r] - acc[cb][r];
     } else {
 #pragma unroll
-      for (int cb = 0; cb < PP / 16; ++cb)
+      for (int cb = 0; cb < W / 16; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) p[cb][r] = g[cb][r] - acc[cb][r];
     }
-    store_rl<T, PP>(P, row0, n, p);
+    store_rl<T, PP, W>(P, row0, n, p);
     if (P16) {
       // bfloat16 copy of P for the SpMM of the bfloat16 mode
       const int l = threadIdx.x & 63, g = l >> 4, c = l & 15;
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(WG) void k_dir(int64_t n, const T* __restrict__ X, 
         const int64_t row = row0 + rowof<T>(g, r);
         if (row < n)
 #pragma unroll
-          for (int cb = 0; cb < PP / 16; ++cb) gst(P16 + row * PP + 16 * cb + c, bf16_round((float)p[cb][r]));
+          for (int cb = 0; cb < W / 16; ++cb) gst(P16 + row * PP + 16 * cb + c, bf16_round((float)p[cb][r]));
       }
     }
     if (P32) {
@@ -206,14 +206,20 @@ __global__ __launch_bounds__(WG) void k_dir(int64_t n, const T* __restrict__ X, 
         const int64_t row = row0 + rowof<T>(g, r);
         if (row < n)
 #pragma unroll
-          for (int cb = 0; cb < PP / 16; ++cb) gst(P32 + row * PP + 16 * cb + c, (float)p[cb][r]);
+          for (int cb = 0; cb < W / 16; ++cb) gst(P32 + row * PP + 16 * cb + c, (float)p[cb][r]);
       }
     }
 #pragma unroll
-    for (int cb = 0; cb < PP / 16; ++cb)
+    for (int cb = 0; cb < W / 16; ++cb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) gp += (double)g[cb][r] * (double)p[cb][r];
-    rl_to_lds<T, PP>(sP, p);
+    T pf[PP / 16][4];  // whole rows for the Gram
+    zero_rl<T, PP>(pf);
+#pragma unroll
+    for (int cb = 0; cb < W / 16; ++cb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pf[cb][r] = p[cb][r];
+    rl_to_lds<T, PP>(sP, pf);
     __syncthreads();
     gram_tile_sym<T, PP>(sP, sacc);
     __syncthreads();
@@ -679,7 +685,12 @@ __global__ __launch_bounds__(WG) void k_update(int64_t n, T* __restrict__ X, T* 
 // gradient pass runs after the product; a void step or a finished solve returns at once. X and
 // Y come out bit for bit as from k_update; G differs from the separate pass's X_new C - Y_new
 // by rounding only (the product with C is taken before the rounding of X_new).
-template <typename T, int PP>
+//
+// W: columns in use, whole 16-column blocks. A block of 33 to 48 columns is stored 64 wide; its
+// last 16 columns are zero from the allocation on, are not read or written here nor in the
+// direction pass, and have no products (p = 40, n = 250007: 251 -> 163 us, direction 99 -> 82).
+// Only this width has a block of 16 to leave out: 17 to 32 and 49 to 64 columns use all of theirs.
+template <typename T, int PP, int W = PP>
 __global__ __launch_bounds__(WG) void k_update_grad(int64_t n, T* __restrict__ X, T* __restrict__ Y,
                                                     const T* __restrict__ P0, const T* __restrict__ P1,
                                                     const T* __restrict__ Z, T* __restrict__ G0, T* __restrict__ G1,
@@ -704,7 +715,7 @@ __global__ __launch_bounds__(WG) void k_update_grad(int64_t n, T* __restrict__ X
   const int64_t ntiles = (n + TR - 1) / TR;
   int64_t t0, t1;
   tile_range(ntiles, t0, t1);
-  constexpr int NB = PP / 16;
+  constexpr int NB = W / 16;
   typedef typename Vec4<T>::type V4;
   V4 kacc[NB * NB];
 #pragma unroll
@@ -712,27 +723,27 @@ __global__ __launch_bounds__(WG) void k_update_grad(int64_t n, T* __restrict__ X
   double gg = 0.0, gdot = 0.0, ginf = 0.0;
   for (int64_t t = t0; t < t1; ++t) {
     const int64_t row0 = t * TR + 16 * w;
-    T a1[PP / 4], a2[PP / 4], b[PP / 4];
-    load_al<T, PP>(X, row0, n, a1);
-    load_al<T, PP>(P, row0, n, b);
+    T a1[W / 4], a2[W / 4], b[W / 4];
+    load_al<T, PP, W>(X, row0, n, a1);
+    load_al<T, PP, W>(P, row0, n, b);
 #pragma unroll
-    for (int s = 0; s < PP / 4; ++s) a1[s] = a1[s] - mu * b[s];
+    for (int s = 0; s < W / 4; ++s) a1[s] = a1[s] - mu * b[s];
     V4 xacc[NB];
-    zero_acc<T, PP>(xacc);
+    zero_acc<T, W>(xacc);
     if (full) {
       // G_old with the other operands: one wait per tile (a load issued after the stores
       // would wait for them too)
       T go[NB][4];
-      load_rl<T, PP>(Gold, row0, n, go);
-      load_al<T, PP>(Y, row0, n, a2);
-      load_al<T, PP>(Z, row0, n, b);
+      load_rl<T, PP, W>(Gold, row0, n, go);
+      load_al<T, PP, W>(Y, row0, n, a2);
+      load_al<T, PP, W>(Z, row0, n, b);
 #pragma unroll
-      for (int s = 0; s < PP / 4; ++s) a2[s] = a2[s] - mu * b[s];
+      for (int s = 0; s < W / 4; ++s) a2[s] = a2[s] - mu * b[s];
       V4 yacc[NB], gacc[NB];
-      zero_acc<T, PP>(yacc);
-      zero_acc<T, PP>(gacc);
-      product2<T, PP>(a1, a2, sM, xacc, yacc);
-      product<T, PP>(a1, sMC, gacc);
+      zero_acc<T, W>(yacc);
+      zero_acc<T, W>(gacc);
+      product2<T, PP, W>(a1, a2, sM, xacc, yacc);
+      product<T, PP, W>(a1, sMC, gacc);
       T xo[NB][4], yo[NB][4], g[NB][4];
 #pragma unroll
       for (int cb = 0; cb < NB; ++cb)
@@ -742,9 +753,9 @@ __global__ __launch_bounds__(WG) void k_update_grad(int64_t n, T* __restrict__ X
           yo[cb][r] = yacc[cb][r];
           g[cb][r] = gacc[cb][r] - yacc[cb][r];
         }
-      store_rl<T, PP>(X, row0, n, xo);
-      store_rl<T, PP>(Y, row0, n, yo);
-      store_rl<T, PP>(G, row0, n, g);
+      store_rl<T, PP, W>(X, row0, n, xo);
+      store_rl<T, PP, W>(Y, row0, n, yo);
+      store_rl<T, PP, W>(G, row0, n, g);
       double rs[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int cb = 0; cb < NB; ++cb)
@@ -764,13 +775,13 @@ __global__ __launch_bounds__(WG) void k_update_grad(int64_t n, T* __restrict__ X
 #pragma unroll
           for (int cb2 = 0; cb2 < NB; ++cb2) kacc[cb * NB + cb2] = mfma(xo[cb][r], g[cb2][r], kacc[cb * NB + cb2]);
     } else {
-      product<T, PP>(a1, sM, xacc);
+      product<T, PP, W>(a1, sM, xacc);
       T xo[NB][4];
 #pragma unroll
       for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) xo[cb][r] = xacc[cb][r];
-      store_rl<T, PP>(X, row0, n, xo);
+      store_rl<T, PP, W>(X, row0, n, xo);
     }
   }
   if (!full) return;
@@ -779,6 +790,10 @@ __global__ __launch_bounds__(WG) void k_update_grad(int64_t n, T* __restrict__ X
   double* sK = reinterpret_cast<double*>(lds_raw);
   const int l = threadIdx.x & 63, lg = l >> 4, lc = l & 15;
   __syncthreads();
+  if constexpr (W < PP) {
+    for (int e = threadIdx.x; e < PP * PP; e += WG) sK[e] = 0.0;
+    __syncthreads();
+  }
   for (int ww = 0; ww < 4; ++ww) {
     if (w == ww) {
 #pragma unroll
@@ -1994,6 +2009,7 @@ hipError_t set_lds_limits() {
   } else {
     GSI_SET((k_grad<T, PP>), Pass::Grad)
     GSI_SET((k_dir<T, PP>), Pass::Dir)
+    if constexpr (PP == 64) { GSI_SET((k_dir<T, PP, 48>), Pass::Dir) }
   }
   GSI_SET((k_update<T, PP, false>), Pass::Update)
   // the retraction with Gram epilogue and the fused retraction-gradient pass are not used above
@@ -2001,6 +2017,7 @@ hipError_t set_lds_limits() {
   if constexpr (PP <= PP_LDS_MAX) {
     GSI_SET((k_update<T, PP, true>), Pass::UpdateGrams)
     GSI_SET((k_update_grad<T, PP>), Pass::UpdateGrad)
+    if constexpr (PP == 64) { GSI_SET((k_update_grad<T, PP, 48>), Pass::UpdateGrad) }
   }
   GSI_SET((k_product<T, PP>), Pass::Product)
   if constexpr (PP == 64) {
@@ -2023,19 +2040,31 @@ void Kernels<T, PP>::grad(hipStream_t st, int nb, int64_t n, const T* X, const T
 template <typename T, int PP>
 void Kernels<T, PP>::update_grad(hipStream_t st, int nb, int64_t n, T* X, T* Y, const T* P0, const T* P1,
                                  const T* Z, T* G0, T* G1, const double* small, const Scalars* sc,
-                                 double* partials) {
-  if constexpr (PP <= PP_LDS_MAX)  // not used above (the host keeps the separate passes there)
-    k_update_grad<T, PP><<<nb, WG, lds_bytes<T, PP>(Pass::UpdateGrad), st>>>(n, X, Y, P0, P1, Z, G0, G1, small, sc,
-                                                                            partials);
+                                 double* partials, int p) {
+  auto go = [&](auto* k) {
+    k<<<nb, WG, lds_bytes<T, PP>(Pass::UpdateGrad), st>>>(n, X, Y, P0, P1, Z, G0, G1, small, sc, partials);
+  };
+  if constexpr (PP == 64) {
+    if (p <= 48) return go(k_update_grad<T, PP, 48>);
+  }
+  if constexpr (PP <= PP_LDS_MAX) go(k_update_grad<T, PP>);  // not used above (the host keeps the separate passes there)
 }
 template <typename T, int PP>
 void Kernels<T, PP>::dir(hipStream_t st, int nb, int64_t n, const T* X, const T* G0, const T* G1, T* P0, T* P1,
-                         const double* small, const Scalars* sc, double* partials, uint16_t* P16, float* P32) {
-  if constexpr (factor_wide<T, PP>())
+                         const double* small, const Scalars* sc, double* partials, int p, uint16_t* P16,
+                         float* P32) {
+  auto go = [&](auto* k) {
+    k<<<nb, WG, lds_bytes<T, PP>(Pass::Dir), st>>>(n, X, G0, G1, P0, P1, small, sc, partials, P16, P32);
+  };
+  if constexpr (factor_wide<T, PP>()) {
     k_dir_wide<T, PP><<<nb, WGW, lds_bytes<T, PP>(Pass::Dir), st>>>(n, X, G0, G1, P0, P1, small, sc, partials, P16,
                                                                     P32);
-  else
-    k_dir<T, PP><<<nb, WG, lds_bytes<T, PP>(Pass::Dir), st>>>(n, X, G0, G1, P0, P1, small, sc, partials, P16, P32);
+  } else {
+    if constexpr (PP == 64) {
+      if (p <= 48) return go(k_dir<T, PP, 48>);
+    }
+    go(k_dir<T, PP>);
+  }
 }
 // Columns of a block that the CSR products gather: p up to whole 16-column groups (a cache line in
 // float64). The padding columns past them are zero in W and are written as zeros; their lanes have
