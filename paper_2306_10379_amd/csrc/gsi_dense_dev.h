@@ -345,37 +345,45 @@ struct ColPairs {
     a = v[0];
     b = v[1];
   }
-  // Rotates every pair whose cosine is above the threshold, by the angle of at most 45 degrees
-  // with tan 2 theta = 2 c / d, c = x.y, d = |y|^2 - |x|^2: tan theta = 2 c / (d +- sqrt(d^2 + 4 c^2)).
-  // The tangent is taken in float32 (short latencies; a rotation then leaves 1e-7 of the
-  // cosine it meets instead of nothing, which the next sweep or the stop rule accounts for);
-  // the rotation by it is orthogonal to the last bit of float64. The norms are updated, and
-  // formed again once per block of pairings.
+  // Rotates every pair whose cosine is above the threshold, by the angle theta of at most 45 degrees
+  // with tan 2 theta = 2 c / d, c = x.y, d = |y|^2 - |x|^2. The angle enters as h = tan(theta / 2),
+  //   s = 2 h / (1 + h^2),  x <- x - s (y + h x),  y <- y + s (x - h y)
+  // (Rutishauser 1966), whose cosine is 1 - s h: rounding h changes the angle only, rounding s
+  // the columns' norms by s h of it. With a rounded cosine and sine the norms, whose squares are
+  // the eigenvalues, grew by 2e-17 a rotation, all in one direction: 9e-15 at p = 64, and as much
+  // in the step lengths; in this form 2e-16. h is taken in float32 (short latencies; a rotation
+  // then leaves 1e-7 of the cosine it meets instead of nothing, which the next sweep or the stop
+  // rule accounts for; the eigenvalues' error against 64 bits is the same with a float64 angle).
+  // The norms are updated, and formed again once per block of pairings.
   __device__ __forceinline__ void rotate() {
     double v[1] = {0.0};
 #pragma unroll
     for (int r = 0; r < R; ++r) v[0] = fma(x[r], y[r], v[0]);
-    const float fa = (float)a, fb = (float)b, fd = (float)(b - a);
+    const double d = b - a;
+    const float fa = (float)a, fb = (float)b, fd = (float)d;
     const float s = __builtin_amdgcn_rcpf(fa + fb), g = __builtin_amdgcn_rsqf(fa * fb);
     const float vd = fabsf(fd * s), big = fmaxf(fa, fb) * g;
     sum_rows8(v);
     const float fc = (float)v[0];
-    const float u = fc * s, w = fmaf(vd, vd, 4.f * u * u);
+    const float u = 2.f * fc * s, ri = __builtin_amdgcn_rsqf(fmaf(vd, vd, u * u));
     const float co = fabsf(fc) * g;
-    float t = 2.f * u * __builtin_amdgcn_rcpf(vd + w * __builtin_amdgcn_rsqf(w));
-    t = fd < 0.f ? -t : t;
+    const float k = fmaf(0.5f, vd * ri, 0.5f), rk = __builtin_amdgcn_rsqf(k);  // cos^2 theta, 1 / cos theta
+    float h = u * ri * (0.5f * rk) * __builtin_amdgcn_rcpf(fmaf(k, rk, 1.f));
+    h = fd < 0.f ? -h : h;
     const bool rot = co > tol;  // false for zero columns (not a number)
-    t = rot ? t : 0.f;
+    h = rot ? h : 0.f;
     cm = fmaxf(cm, rot ? co : 0.f);
-    em = fmaxf(em, rot ? fabsf(t) * big : 0.f);
-    const double td = t, cs = rsq_nr(fma(td, td, 1.0)), sn = td * cs, tc = td * v[0];
-    a -= tc;
-    b += tc;
+    // |tan theta| = 2 |h| / (1 - h^2), at most 2 |h| (1 + 1.2072 h^2) up to 45 degrees
+    em = fmaxf(em, rot ? fabsf(h) * fmaf(2.4145f * h, h, 2.f) * big : 0.f);
+    const double hd = h, sn = div_nr(hd + hd, fma(hd, hd, 1.0));
+    const double e = sn * fma(sn, d, -2.0 * fma(-sn, hd, 1.0) * v[0]);
+    a += e;
+    b -= e;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const double xr = x[r], yr = y[r];
-      x[r] = fma(cs, xr, -sn * yr);
-      y[r] = fma(sn, xr, cs * yr);
+      x[r] = fma(-sn, fma(hd, xr, yr), xr);
+      y[r] = fma(sn, fma(-hd, yr, xr), yr);
     }
   }
   // y from lane ^ M

@@ -1,0 +1,27 @@
+"""Accuracy of the p x p eigensolver in units of the last place."""
+import numpy as np
+import pytest
+
+from oracle import gsi_oracle as O
+from paper_2306_10379_amd import inputs
+
+pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+EPS = np.finfo(float).eps
+
+
+@pytest.mark.parametrize("p", [8, 16, 32, 48, 64, 80, 128])
+def test_first_step_length(p):
+    """The first step length follows from the eigenvalues of P^T P. It is well conditioned here (a
+    relative error of the terms grows by 4 to 9), so eigenvalues good to an ulp or two put it within
+    10 eps of the oracle's; norms that drift with the number of rotations do not."""
+    from paper_2306_10379_amd import gsi
+    A = inputs.spiked_sparse(1500, 6, p, seed=1)
+    X0 = np.random.default_rng(1).standard_normal((1500, p))
+    with gsi.Solver(A, X0, p, tol=0.0, max_iter=10) as s:
+        s.step(1)
+        mu = s.history()["mu"][0]
+    ref = O.rcg(A, X0, tol=0.0, max_iter=1).mu[0]
+    assert abs(mu - ref) <= 10 * EPS * ref
