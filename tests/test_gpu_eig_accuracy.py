@@ -25,3 +25,20 @@ def test_first_step_length(p):
         mu = s.history()["mu"][0]
     ref = O.rcg(A, X0, tol=0.0, max_iter=1).mu[0]
     assert abs(mu - ref) <= 10 * EPS * ref
+
+
+@pytest.mark.parametrize("p", [16, 31, 64, 80, 128])
+def test_ritz_vectors_are_orthogonal(p):
+    """Columns of the eigensolver are left as they are up to a cosine of eps; the cosine's own
+    rounding, that of the product X U and of the start block add as much again each, and the
+    largest of the p^2 entries is some standard deviations out: 6 eps."""
+    from paper_2306_10379_amd import gsi
+    A = inputs.spiked_sparse(1500, 6, p, seed=1)
+    X0 = np.random.default_rng(1).standard_normal((1500, p))
+    with gsi.Solver(A, X0, p, tol=0.0, max_iter=10) as s:
+        s.step(1)
+        s.residuals()
+        U = s.get_x().cpu().numpy().astype(np.longdouble)
+    off = U.T @ U
+    np.fill_diagonal(off, 0.0)
+    assert np.max(np.abs(off)) <= 6 * EPS
