@@ -1220,15 +1220,19 @@ __device__ __noinline__ void final_ritz(BatchProblem& pr, unsigned char* lds, Ba
     A[i * LD + j] = i < p && j < p ? C[ord[i] * PP + ord[j]] : 0.0;
   }
   __syncthreads();
-  // C is indefinite: its largest absolute row sum makes it positive semidefinite
+  // C is indefinite: its lowest Gershgorin bound, where negative, makes it positive semidefinite;
+  // the Ritz values are Rayleigh quotients with C itself (see k_ritz)
   double shift = 0.0;
   for (int i = 0; i < p; ++i) {
     double r = 0.0;
-    for (int j = threadIdx.x & 63; j < p; j += 64) r += fabs(A[i * LD + j]);
+    for (int j = threadIdx.x & 63; j < p; j += 64) r += j == i ? -A[i * LD + j] : fabs(A[i * LD + j]);
     shift = fmax(shift, wave_sum(r));
   }
   __syncthreads();
   eig_lds<PP>(p, A, ord, shift, lam);
+  __syncthreads();
+  const double* const B[1] = {C};
+  quad_diag<PP>((p + 15) >> 4, A, B, [&](int, int i, double v) { lam[i] = v; });
   __syncthreads();
   for (int i = threadIdx.x; i < p; i += blockDim.x) pr.ritz[rank_desc(lam, p, i)] = lam[i];
   __syncthreads();

@@ -300,8 +300,10 @@ __global__ __launch_bounds__(WG) void k_transform_cw(double* __restrict__ small,
 }
 
 // Rayleigh-Ritz: eig of sym(red) (p x p): eigenvalues descending into vals[0..p),
-// eigenvectors as the columns of small[S_M] (stride PP, padding zero). sym(red) is indefinite;
-// its largest absolute row sum bounds the spectrum and makes it a positive one.
+// eigenvectors as the columns of small[S_M] (stride PP, padding zero). sym(red) is indefinite:
+// it is shifted by its lowest Gershgorin bound where that is negative, and the eigenvalues are the
+// Rayleigh quotients of the vectors with the matrix as it came (the shifted ones less the shift
+// are wrong by eps times it: small values beside large ones were lost).
 template <int PP>
 __global__ __launch_bounds__(dense_threads(PP)) void k_ritz(int p, const double* __restrict__ red,
                                                             double* __restrict__ small, double* __restrict__ vals) {
@@ -318,14 +320,17 @@ __global__ __launch_bounds__(dense_threads(PP)) void k_ritz(int p, const double*
           i < p && j < p ? 0.5 * (red[order[i] * PP + order[j]] + red[order[j] * PP + order[i]]) : 0.0;
   __syncthreads();
   for (int i = threadIdx.x; i < p; i += blockDim.x) {
-    double s = 0.0;
-    for (int j = 0; j < p; ++j) s += fabs(A[i * LD + j]);
+    double s = -A[i * LD + i];
+    for (int j = 0; j < p; ++j) s += j == i ? 0.0 : fabs(A[i * LD + j]);
     row[i] = s;
   }
   __syncthreads();
   double shift = 0.0;
   for (int i = 0; i < p; ++i) shift = fmax(shift, row[i]);
   eig_lds<PP>(p, A, order, shift, lam);
+  __syncthreads();
+  const double* const B[1] = {red};
+  quad_diag<PP>(m / 16, A, B, [&](int, int i, double v) { lam[i] = v; });
   __syncthreads();
   for (int i = threadIdx.x; i < p; i += blockDim.x) order[rank_desc(lam, p, i)] = i;
   __syncthreads();

@@ -271,14 +271,13 @@ __device__ inline int eig_dev(double* small, int p, bool warm, double* lds) {
 
 // ---------------------------------------------------------------- line search and retraction factor
 
-// a_i = v_i^T C v_i, g_i = v_i^T Z v_i, z_i = -v_i^T Y v_i for the leading 16 nb columns v_i of V
-// (LDS, stride DLD<PP>) and the matrices C, Z, Y (global, stride PP): the line-search
-// diagonals. A wave takes 16 columns, whose operand stays in registers for all three matrices;
-// a matrix is read by rows as the transposed left operand (coalesced; v^T B v = v^T B^T v) and
-// the product's blocks go into the dot products from the matrix unit's registers.
-template <int PP>
-__device__ __forceinline__ void quad_diag(int nb, const double* V, const double* C, const double* Z, const double* Y,
-                                          Terms& terms) {
+// v_i^T B_q v_i for the leading 16 nb columns v_i of V (LDS, stride DLD<PP>) and the matrices B_q
+// (global, stride PP), put(q, i, value): the line-search diagonals, Rayleigh quotients. A wave
+// takes 16 columns, whose operand stays in registers for all matrices; a matrix is read by rows
+// as the transposed left operand (coalesced; v^T B v = v^T B^T v) and the product's blocks go into
+// the dot products from the matrix unit's registers.
+template <int PP, int NQ, typename F>
+__device__ __forceinline__ void quad_diag(int nb, const double* V, const double* const (&B)[NQ], F put) {
   constexpr int LD = DLD<PP>, NB = PP / 16;
   const int nw = blockDim.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
   for (int jb = threadIdx.x >> 6; jb < nb; jb += nw) {
@@ -289,23 +288,24 @@ __device__ __forceinline__ void quad_diag(int nb, const double* V, const double*
       for (int s = 0; s < 4; ++s) v[k][s] = k < nb ? V[(16 * k + 4 * s + g) * LD + 16 * jb + c] : 0.0;
     // the blocks (matrix, ib) one after the other, the next one's rows loaded before this one's
     // products
-    double sum[3] = {0.0, 0.0, 0.0};
     double x[NB][4], y[NB][4];
-    auto load = [&](const double* B, int ib, double (&to)[NB][4]) {
+    auto load = [&](const double* M, int ib, double (&to)[NB][4]) {
 #pragma unroll
       for (int k = 0; k < NB; ++k)
         if (k < nb)
 #pragma unroll
-          for (int s = 0; s < 4; ++s) to[k][s] = B[(16 * k + 4 * s + g) * PP + 16 * ib + c];
+          for (int s = 0; s < 4; ++s) to[k][s] = M[(16 * k + 4 * s + g) * PP + 16 * ib + c];
     };
-    if constexpr (NB <= 4) load(C, 0, x);
-    auto matrix = [&](const double* B, const double* next, double& acc) {
+    if constexpr (NB <= 4) load(B[0], 0, x);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      double acc = 0.0;
       for (int ib = 0; ib < nb; ++ib) {
         if constexpr (NB > 4) {
-          load(B, ib, x);  // two waves per SIMD cover each other's loads
+          load(B[q], ib, x);  // two waves per SIMD cover each other's loads
         } else {
-          if (ib + 1 < nb) load(B, ib + 1, y);
-          else if (next) load(next, 0, y);
+          if (ib + 1 < nb) load(B[q], ib + 1, y);
+          else if (q + 1 < NQ) load(B[q + 1 < NQ ? q + 1 : q], 0, y);
         }
         d4 t = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -321,20 +321,9 @@ __device__ __forceinline__ void quad_diag(int nb, const double* V, const double*
 #pragma unroll
             for (int s = 0; s < 4; ++s) x[k][s] = y[k][s];
       }
-    };
-    matrix(C, Z, sum[0]);
-    matrix(Z, Y, sum[1]);
-    matrix(Y, nullptr, sum[2]);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      sum[q] += __shfl_xor(sum[q], 16, 64);
-      sum[q] += __shfl_xor(sum[q], 32, 64);
-    }
-    const double a = sum[0], gm = sum[1], z = sum[2];
-    if (g == 0) {
-      terms.a[16 * jb + c] = a;
-      terms.g[16 * jb + c] = gm;
-      terms.z[16 * jb + c] = -z;
+      acc += __shfl_xor(acc, 16, 64);
+      acc += __shfl_xor(acc, 32, 64);
+      if (g == 0) put(q, 16 * jb + c, acc);
     }
   }
 }
@@ -395,7 +384,11 @@ __device__ inline void linesearch_dev(const double* PZr, const double* PYr, doub
   __syncthreads();
   // line-search diagonals (Sec. 5.2, eq. CG_linesearch_D) in the basis V; the diagonal of
   // V^T B V only needs the symmetric part of B, so the raw Grams are used
-  quad_diag<PP>(nb, U, C, PZr, PYr, terms);
+  {
+    const double* const B[3] = {C, PZr, PYr};
+    double* const to[3] = {terms.a, terms.g, terms.z};
+    quad_diag<PP>(nb, U, B, [&](int q, int i, double v) { to[q][i] = q == 2 ? -v : v; });
+  }
   __syncthreads();
   if (threadIdx.x < 64) {
     int evals = 0;

@@ -42,3 +42,34 @@ def test_ritz_vectors_are_orthogonal(p):
     off = U.T @ U
     np.fill_diagonal(off, 0.0)
     assert np.max(np.abs(off)) <= 6 * EPS
+
+
+def _graded(n, p, sign=1.0):
+    """Diagonal matrix whose first p entries fall over 12 decades, these entries in descending
+    order, and their eigenvectors."""
+    d = np.concatenate([sign * np.logspace(0, -12, p), -np.linspace(1.0, 0.5, n - p)])
+    A = inputs.CSR(n=n, rowptr=np.arange(n + 1, dtype=np.int32), colind=np.arange(n, dtype=np.int32), vals=d)
+    return A, np.sort(d[:p])[::-1], np.eye(n)[:, :p].copy()
+
+
+@pytest.mark.parametrize("p", [3, 16, 20, 64, 100])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_small_ritz_values_beside_large_ones(p, sign):
+    """The projected matrix of exact eigenvectors is diagonal: each Ritz value is right to the
+    rounding of its own vector's normalization (8 eps), however small it is. sign = -1 makes the
+    projected matrix negative."""
+    from paper_2306_10379_amd import gsi
+    A, w, X0 = _graded(300, p, sign)
+    with gsi.Solver(A, X0, p) as s:
+        ritz = s.residuals()[0]
+    np.testing.assert_allclose(ritz, w, rtol=8 * EPS)
+
+
+def test_small_ritz_values_of_a_batch():
+    from paper_2306_10379_amd import gsi
+    sizes = [(300, 3), (200, 16), (400, 20), (100, 32)]
+    mats, ws, xs = zip(*[_graded(n, p) for n, p in sizes])
+    b = gsi.BatchedSolver(list(mats), list(xs), [p for _, p in sizes], which=1, precision="fp64", max_iter=5)
+    b.solve()
+    for i in range(len(sizes)):
+        np.testing.assert_allclose(b.results(i)[0], ws[i], rtol=8 * EPS)
