@@ -359,26 +359,25 @@ struct ColPairs {
     double v[1] = {0.0};
 #pragma unroll
     for (int r = 0; r < R; ++r) v[0] = fma(x[r], y[r], v[0]);
-    const double d = b - a;
-    const float fa = (float)a, fb = (float)b, fd = (float)d;
-    const float s = __builtin_amdgcn_rcpf(fa + fb), g = __builtin_amdgcn_rsqf(fa * fb);
-    const float vd = fabsf(fd * s), big = fmaxf(fa, fb) * g;
+    const float fa = (float)a, fb = (float)b, fd = (float)(b - a);
+    // zero columns: finite (fa + fb is 1e-15 or more otherwise, see eig_lds)
+    const float s = __builtin_amdgcn_rcpf(fmaxf(fa + fb, 1e-30f)), g = __builtin_amdgcn_rsqf(fa * fb);
+    const float vd = fabsf(fd * s), vd2 = vd * vd, big = fmaxf(fa, fb) * g, s2 = copysignf(2.f * s, fd);
     sum_rows8(v);
     const float fc = (float)v[0];
-    const float u = 2.f * fc * s, ri = __builtin_amdgcn_rsqf(fmaf(vd, vd, u * u));
-    const float co = fabsf(fc) * g;
-    const float k = fmaf(0.5f, vd * ri, 0.5f), rk = __builtin_amdgcn_rsqf(k);  // cos^2 theta, 1 / cos theta
-    float h = u * ri * (0.5f * rk) * __builtin_amdgcn_rcpf(fmaf(k, rk, 1.f));
-    h = fd < 0.f ? -h : h;
+    const float u = fc * s2, co = fabsf(fc) * g;
     const bool rot = co > tol;  // false for zero columns (not a number)
-    h = rot ? h : 0.f;
+    const float ri = rot ? __builtin_amdgcn_rsqf(fmaf(u, u, vd2)) : 0.f;  // 0: h and tan theta are 0
+    const float k = fmaf(0.5f, vd * ri, 0.5f), rk = __builtin_amdgcn_rsqf(k);  // cos^2 theta, 1 / cos theta
+    const float st = u * ri * (0.5f * rk), c1 = fmaf(k, rk, 1.f);              // sin theta, 1 + cos theta
+    const float h = st * __builtin_amdgcn_rcpf(c1), t = st * rk;
     cm = fmaxf(cm, rot ? co : 0.f);
-    // |tan theta| = 2 |h| / (1 - h^2), at most 2 |h| (1 + 1.2072 h^2) up to 45 degrees
-    em = fmaxf(em, rot ? fabsf(h) * fmaf(2.4145f * h, h, 2.f) * big : 0.f);
-    const double hd = h, sn = div_nr(hd + hd, fma(hd, hd, 1.0));
-    const double e = sn * fma(sn, d, -2.0 * fma(-sn, hd, 1.0) * v[0]);
-    a += e;
-    b -= e;
+    em = fmaxf(em, fabsf(t) * big);
+    // s = 2 h / (1 + h^2) from 1 / (1 + h^2) = (1 + cos theta) / 2 to float32, one third-order step
+    const double hd = h, cd = c1, er = fma(fma(hd, hd, 1.0), -0.5 * cd, 1.0), m = hd * cd;
+    const double sn = fma(m, fma(er, er, er), m), tc = (double)(t * fc);
+    a -= tc;
+    b += tc;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const double xr = x[r], yr = y[r];
