@@ -1229,7 +1229,7 @@ __device__ __noinline__ void final_ritz(BatchProblem& pr, unsigned char* lds, Ba
     shift = fmax(shift, wave_sum(r));
   }
   __syncthreads();
-  eig_lds<PP>(p, A, ord, shift, lam);
+  eig_lds<PP>(p, A, ord, shift);
   __syncthreads();
   const double* const B[1] = {C};
   quad_diag<PP>((p + 15) >> 4, A, B, [&](int, int i, double v) { lam[i] = v; });

@@ -349,11 +349,11 @@ struct ColPairs {
   // with tan 2 theta = 2 c / d, c = x.y, d = |y|^2 - |x|^2. The angle enters as h = tan(theta / 2),
   //   s = 2 h / (1 + h^2),  x <- x - s (y + h x),  y <- y + s (x - h y)
   // (Rutishauser 1966), whose cosine is 1 - s h: rounding h changes the angle only, rounding s
-  // the columns' norms by s h of it. With a rounded cosine and sine the norms, whose squares are
-  // the eigenvalues, grew by 2e-17 a rotation, all in one direction: 9e-15 at p = 64, and as much
-  // in the step lengths; in this form 2e-16. h is taken in float32 (short latencies; a rotation
-  // then leaves 1e-7 of the cosine it meets instead of nothing, which the next sweep or the stop
-  // rule accounts for; the eigenvalues' error against 64 bits is the same with a float64 angle).
+  // the columns' norms by s h of it. With a rounded cosine and sine the norms grew by 2e-17 a
+  // rotation, all in one direction (9e-15 of their squares at p = 64), and the vectors were off by
+  // up to 6e-15 at p = 128; in this form 2e-16 and 2e-15. h is taken in float32 (short latencies; a
+  // rotation then leaves 1e-7 of the cosine it meets instead of nothing, which the next sweep or
+  // the stop rule accounts for; the errors against 64 bits are the same with a float64 angle).
   // The norms are updated, and formed again once per block of pairings.
   __device__ __forceinline__ void rotate() {
     double v[1] = {0.0};
@@ -465,15 +465,16 @@ __device__ __forceinline__ void diag_order(int p, int* ord, double* key, F d) {
 // both triangles, rows and columns p .. 16 ceil(p/16) zero) holds B with its rows and columns
 // in the order ord (LDS, from diag_order): A[i][j] = B[ord[i]][ord[j]]. It is replaced by U,
 // column j the eigenvector that the rotations grew out of column ord[j] of B (columns p .. are
-// unit vectors); lam (LDS or global) gets 16 ceil(p/16) values, zero from p on. B + shift I must
+// unit vectors); the eigenvalues are its Rayleigh quotients with B (quad_diag). B + shift I must
 // be positive semidefinite up to rounding: shift = 0 for a Gram matrix. Returns the number of
 // sweeps. Whole workgroup, dense_threads(PP) threads; the caller puts a barrier before and after.
 //
 // A + (shift + delta) I = L L^T (delta a few ulps of the largest diagonal entry, the floor of
 // the pivots too, so that a rank-deficient Gram has a factor), then rotations from the right
 // make the columns of L orthogonal (one-sided Jacobi on the Cholesky factor, Veselic and Hari
-// 1989): L J = U Sigma, so the columns' norms give the eigenvalues and their directions the
-// eigenvectors, with no second matrix to rotate and no row updates.
+// 1989): L J = U Sigma, so the columns' directions are the eigenvectors, with no second matrix to
+// rotate and no row updates. Their squared norms are the eigenvalues plus shift + delta, to eps of
+// the largest: they keep nothing of an eigenvalue below that.
 //
 // What bounds it is latency: a chain of ~p rounds per sweep, each the three dot products of a
 // column pair, one rotation and its application. Wave w holds 16 columns in registers, pair q
@@ -494,7 +495,7 @@ __device__ __forceinline__ void diag_order(int p, int* ord, double* key, F d) {
 // (|tan| times the ratio of the columns' norms) is below eps: what that sweep leaves is then
 // below the threshold, and no confirming sweep is run.
 template <int PP>
-__device__ __forceinline__ int eig_lds(int p, double* A, const int* ord, double shift, double* lam) {
+__device__ __forceinline__ int eig_lds(int p, double* A, const int* ord, double shift) {
   constexpr int LD = DLD<PP>, R = PP / 8, NW = PP / 16;
   __shared__ int ids[2 * NW][8];
   __shared__ float stat[NW][2];
@@ -508,9 +509,7 @@ __device__ __forceinline__ int eig_lds(int p, double* A, const int* ord, double 
   __syncthreads();
   (void)chol_lds<PP, true>(p, A, delta);
   // columns scaled by a power of two so that squared norms and their products stay in range
-  int ex = 0;
-  if (dmax > 0.0) ex = ilogb(dmax) / 2;
-  const double scale = ldexp(1.0, -ex);
+  const double scale = ldexp(1.0, dmax > 0.0 ? -ilogb(dmax) / 2 : 0);
   const bool on = w < nw;
   ColPairs<R> u;
   u.ix = 16 * w + q;
@@ -575,7 +574,7 @@ __device__ __forceinline__ int eig_lds(int p, double* A, const int* ord, double 
     __syncthreads();
     if (!(cm * (em + 4e-7f) > (float)EPS)) break;
   }
-  // column norms: lam + shift + delta, directions: U
+  // the columns' directions: U
   if (on) {
     u.norms();
     const double a = u.a, b = u.b;
@@ -588,11 +587,6 @@ __device__ __forceinline__ int eig_lds(int p, double* A, const int* ord, double 
         A[to + u.ix] = a > 0.0 ? u.x[r] * ra : (row == u.ix ? 1.0 : 0.0);
         A[to + u.iy] = b > 0.0 ? u.y[r] * rb : (row == u.iy ? 1.0 : 0.0);
       }
-    }
-    if (g == 0) {
-      const double s2 = ldexp(1.0, 2 * ex);
-      lam[u.ix] = u.ix < p ? a * s2 - shift - delta : 0.0;
-      lam[u.iy] = u.iy < p ? b * s2 - shift - delta : 0.0;
     }
   }
   return sweep + 1;

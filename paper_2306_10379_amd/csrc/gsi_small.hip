@@ -327,7 +327,7 @@ __global__ __launch_bounds__(dense_threads(PP)) void k_ritz(int p, const double*
   __syncthreads();
   double shift = 0.0;
   for (int i = 0; i < p; ++i) shift = fmax(shift, row[i]);
-  eig_lds<PP>(p, A, order, shift, lam);
+  eig_lds<PP>(p, A, order, shift);
   __syncthreads();
   const double* const B[1] = {red};
   quad_diag<PP>(m / 16, A, B, [&](int, int i, double v) { lam[i] = v; });

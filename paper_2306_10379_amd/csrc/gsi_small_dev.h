@@ -79,9 +79,9 @@ __device__ inline double get_mu(Terms& T, int p, int preal, int* evals, double* 
   if (!(bmax > 0.0)) { *evals = 0; return -1.0; }
   const bool act = l < p && bl > preal * EPS * bmax;
   const bool act2 = l2 < p && bl2 > preal * EPS * bmax;
-  // inactive terms become zero ones, so that the sums below need no test
-  if (l < p && !act) T.a[l] = T.b[l] = T.g[l] = T.z[l] = 0.0;
-  if (l2 < p && !act2) T.a[l2] = T.b[l2] = T.g[l2] = T.z[l2] = 0.0;
+  // inactive terms become zero ones, so that the sums below need no test (b stays, for M)
+  if (l < p && !act) T.a[l] = T.g[l] = T.z[l] = 0.0;
+  if (l2 < p && !act2) T.a[l2] = T.g[l2] = T.z[l2] = 0.0;
   wave_sync();
   const bool conv = act && zl > 0.0;
   const bool conv2 = act2 && zl2 > 0.0;
@@ -197,8 +197,8 @@ __device__ inline double get_mu(Terms& T, int p, int preal, int* evals, double* 
 
 // ---------------------------------------------------------------- eigendecomposition of P^T P
 
-// P^T P = V diag(b) V^T (Sec. 5.2) for S = small[S_S]: writes V (small[S_V]) and b
-// (small[S_VEC ...]); returns the sweep count. Warm start (warm = true): the previous V, made
+// P^T P = V diag(b) V^T (Sec. 5.2) for S = small[S_S]: writes V (small[S_V]; the line search
+// forms b); returns the sweep count. Warm start (warm = true): the previous V, made
 // orthonormal again by one Newton-Schulz step V <- V (3 I - V^T V) / 2, turns S into a nearly
 // diagonal V^T S V when the directions change little from step to step.
 // lds: eig_lds_doubles(PP) doubles; above PP = 64 only the matrix that is decomposed fits
@@ -218,7 +218,6 @@ __device__ inline int eig_dev(double* small, int p, bool warm, double* lds) {
   double* T = V1 + PP * LD;
   const double* S = small + S_S * PP * PP;
   double* Vg = small + S_V * PP * PP;
-  double* b = small + S_VEC * PP * PP;
   auto to = [](double* dst) { return [dst](int i, int j, double v) { dst[i * LD + j] = v; }; };
   auto to_sym = [](double* dst) { return [dst](int i, int j, double v) { dst[i * LD + j] = dst[j * LD + i] = v; }; };
   if (warm) {
@@ -258,13 +257,12 @@ __device__ inline int eig_dev(double* small, int p, bool warm, double* lds) {
     fill_dense(m, A, LD, [&](int i, int j) { return S[ord[i] * PP + ord[j]]; });
   }
   __syncthreads();
-  const int sweeps = eig_lds<PP>(p, A, ord, 0.0, b);
+  const int sweeps = eig_lds<PP>(p, A, ord, 0.0);
   __syncthreads();
   if (warm)
     mm_dense<PP / 16, LD, false, LD, false>(nb, V1, A, [&](int i, int j, double v) { Vg[i * PP + j] = v; });
   else
     fill_dense(m, Vg, PP, [&](int i, int j) { return A[i * LD + j]; });
-  for (int i = threadIdx.x; i < PP; i += blockDim.x) b[i] = i < p ? fmax(b[i], 0.0) : 0.0;
   __syncthreads();
   return sweeps;
 }
@@ -297,6 +295,7 @@ __device__ __forceinline__ void quad_diag(int nb, const double* V, const double*
           for (int s = 0; s < 4; ++s) to[k][s] = M[(16 * k + 4 * s + g) * PP + 16 * ib + c];
     };
     if constexpr (NB <= 4) load(B[0], 0, x);
+    double sum[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       double acc = 0.0;
@@ -321,14 +320,18 @@ __device__ __forceinline__ void quad_diag(int nb, const double* V, const double*
 #pragma unroll
             for (int s = 0; s < 4; ++s) x[k][s] = y[k][s];
       }
-      acc += __shfl_xor(acc, 16, 64);
-      acc += __shfl_xor(acc, 32, 64);
-      if (g == 0) put(q, 16 * jb + c, acc);
+      sum[q] = acc;
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      sum[q] += __shfl_xor(sum[q], 16, 64);
+      sum[q] += __shfl_xor(sum[q], 32, 64);
+      if (g == 0) put(q, 16 * jb + c, sum[q]);
     }
   }
 }
 
-// Exact line search (Sec. 5.2, Algorithm 3, Sec. 6.1) from V, b (eig_dev), C = small[S_C],
+// Exact line search (Sec. 5.2, Algorithm 3, Sec. 6.1) from V (eig_dev), C = small[S_C],
 // S = small[S_S] and the Grams P^T A P (PZr) and P^T A X (PYr). On success (*sok = 1) it
 // writes mu (*smu), M = small[S_M], the next C and W (small[S_C], small[S_W]) and the largest
 // b (*sbmax), and with want_mc also M C_next = small[S_MC] (the right factor of the next
@@ -360,7 +363,6 @@ __device__ inline void linesearch_dev(const double* PZr, const double* PYr, doub
   double* M = small + S_M * PP * PP;
   double* W = small + S_W * PP * PP;
   double* MC = small + S_MC * PP * PP;
-  const double* bvec = small + S_VEC * PP * PP;
   const double* Vg = small + S_V * PP * PP;
   // a matrix that the following products read from LDS
   auto settle = [&](double* src) {
@@ -377,17 +379,17 @@ __device__ inline void linesearch_dev(const double* PZr, const double* PYr, doub
     fill_dense(m, b3, LD, [&](int i, int j) { return S[i * PP + j]; });
     Sm = b3;
   }
-  for (int i = threadIdx.x; i < TMAXP; i += blockDim.x) {
-    terms.b[i] = i < PP ? bvec[i] : 0.0;
-    if (i >= m) terms.a[i] = terms.g[i] = terms.z[i] = 0.0;
-  }
+  for (int i = m + threadIdx.x; i < TMAXP; i += blockDim.x) terms.a[i] = terms.b[i] = terms.g[i] = terms.z[i] = 0.0;
   __syncthreads();
   // line-search diagonals (Sec. 5.2, eq. CG_linesearch_D) in the basis V; the diagonal of
-  // V^T B V only needs the symmetric part of B, so the raw Grams are used
+  // V^T B V only needs the symmetric part of B, so the raw Grams are used. b too is a Rayleigh
+  // quotient: M below needs a small b to its own last bits, also beside one 1e16 times as large
+  // (a step of mu^2 b = 1e10 in one direction left X orthonormal to 1e-7 with a b to eps of the
+  // largest, to 1e-3 at 1e12)
   {
-    const double* const B[3] = {C, PZr, PYr};
-    double* const to[3] = {terms.a, terms.g, terms.z};
-    quad_diag<PP>(nb, U, B, [&](int q, int i, double v) { to[q][i] = q == 2 ? -v : v; });
+    const double* const B[4] = {C, PZr, PYr, S};
+    double* const to[4] = {terms.a, terms.g, terms.z, terms.b};
+    quad_diag<PP>(nb, U, B, [&](int q, int i, double v) { to[q][i] = q == 2 ? -v : (q == 3 ? fmax(v, 0.0) : v); });
   }
   __syncthreads();
   if (threadIdx.x < 64) {

@@ -57,7 +57,6 @@ enum {
   S_MC,      // M C_next: the right factor of the next gradient in the fused retraction pass
   S_T1,      // temporaries
   S_T2,
-  S_VEC,     // vectors of length PP: b (eigenvalues of P^T P), then scratch
   S_COUNT
 };
 

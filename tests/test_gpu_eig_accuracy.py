@@ -73,3 +73,25 @@ def test_small_ritz_values_of_a_batch():
     b.solve()
     for i in range(len(sizes)):
         np.testing.assert_allclose(b.results(i)[0], ws[i], rtol=8 * EPS)
+
+
+@pytest.mark.parametrize("p", [2, 18])
+@pytest.mark.parametrize("e1", [1e-4, 1e-5, 1e-6])
+def test_long_step_keeps_the_block_orthonormal(p, e1):
+    """A start column nearly orthogonal to the eigenvector it moves to takes a step with mu^2 b up to
+    1e12, beside columns whose b are 1e-16 of the largest: each column is scaled by its own
+    (1 + mu^2 b)^-1/2. Column norms and cosines carry the rounding of some products: 8 eps."""
+    from paper_2306_10379_amd import gsi
+    n = 80
+    d = np.concatenate([[3.0], np.linspace(2.5, 1.5, p - 1), np.linspace(0.5, -1.0, n - p)])
+    A = inputs.CSR(n=n, rowptr=np.arange(n + 1, dtype=np.int32), colind=np.arange(n, dtype=np.int32), vals=d)
+    X0 = np.zeros((n, p))
+    X0[p, 0], X0[0, 0] = 1.0, e1
+    for j in range(1, p):
+        X0[j, j], X0[p + 10 + j, j] = 1.0, 3e-8 * e1
+    with gsi.Solver(A, X0, p, tol=0.0, max_iter=10) as s:
+        s.step(1)
+        X = s.get_x().cpu().numpy()
+        mu = s.history()["mu"][0]
+    assert mu * mu * (e1 * (d[0] - d[p])) ** 2 > 1e6, "no longer a long step"
+    assert np.max(np.abs(X.T @ X - np.eye(p))) <= 8 * EPS
