@@ -22,6 +22,7 @@
 
 #include "../../include/gsi.h"
 #include "gsi_kernels.h"
+#include "gsi_launch_plan.h"
 
 using namespace gsi;
 
@@ -70,10 +71,6 @@ struct Dev {
     ptrs.clear();
   }
 };
-
-// Launch sequences of an iteration (launch_iteration): the full one; the short one; the full one
-// before a short one, which stops the launches after it when the short one could not follow.
-enum Sequence { SEQ_FULL, SEQ_LEAN, SEQ_FULL_LEAD, SEQUENCES };
 
 // Tall blocks, matrix values and per-solve state for one block precision.
 template <typename T>
@@ -375,7 +372,7 @@ void launch_refresh(gsi_ctx* h, Engine<T>& e, bool hold) {
 // SEQ_LEAN (fused only): the short sequence, without the kernels at the top and for the explicit A X
 // that return at once in almost every iteration: seven launches of 4 to 5 us each, gaps included
 // (a quarter of an iteration at n = 1024, p = 8). When one of them would have had work to do, the
-// bookkeeping at the end sets DONE_HOLD and run_until_done launches a full sequence.
+// bookkeeping at the end sets DONE_HOLD and run_until_done goes on with full ones (LaunchPlan).
 template <typename T>
 void launch_iteration(gsi_ctx* h, Engine<T>& e, double* hist, Sequence seq = SEQ_FULL) {
   const bool lean = seq == SEQ_LEAN;
@@ -563,24 +560,20 @@ gsi_status run_until_done(gsi_ctx* h, Engine<T>& e, double* hist, Scalars* out, 
   const int every = h->timing ? 1 : (h->opt.check_every > 0 ? h->opt.check_every : 25);
   // the short sequence after a full one from any state (per-pass timing and RCG(+), whose every
   // iteration forms A X, keep to the full one)
-  const bool lean = e.fused && !h->rax && !h->timing;
-  bool full_first = true;
+  LaunchPlan plan(every, e.fused && !h->rax && !h->timing);
   GSI_TRY(read_scalars(h, e.sc, out));
   for (;;) {
     // no more launches than the iteration cap leaves (and one for the stop test of an engine
     // that makes it at the top of an iteration): those past it would return at once
-    const int left = h->opt.max_iter - out->k + (e.fused ? 0 : 1);
-    const int count = every < left ? every : (left > 1 ? left : 1);
-    GSI_TRY(lean ? enqueue_iterations(h, e, hist, count, full_first ? SEQ_FULL_LEAD : SEQ_LEAN, SEQ_LEAN)
-                 : enqueue_iterations(h, e, hist, count));
+    const Batch b = plan.next(h->opt.max_iter - out->k + (e.fused ? 0 : 1));
+    GSI_TRY(enqueue_iterations(h, e, hist, b.count, b.first, b.rest));
     GSI_TRY(hip_check(h, hipMemcpyAsync(out, e.sc, sizeof(Scalars), hipMemcpyDeviceToHost, h->st), "poll"));
     GSI_TRY(hip_check(h, hipStreamSynchronize(h->st), "iterate"));
     if (h->timing) collect_times(h);
-    full_first = false;
+    plan.ran(b, out->done == DONE_HOLD);
     if (out->done == DONE_HOLD) {
       // an explicit A X or the gradient's own pass is due
       out->done = 0;
-      full_first = true;
       GSI_TRY(hip_check(h, hipMemcpyAsync(&e.sc->done, &out->done, sizeof(int32_t), hipMemcpyHostToDevice, h->st),
                         "resume"));
       dispatch_pp<T>(e.PP, [&](auto PPc) { launch_refresh<T, decltype(PPc)::value>(h, e, false); });
@@ -604,7 +597,7 @@ gsi_status run_until_done(gsi_ctx* h, Engine<T>& e, double* hist, Scalars* out, 
       out->stall_window = 0;
       out->restart_next = 1;
       out->grad_ready = 0;  // the gradient of the new A X is formed at the top of the next iteration
-      full_first = true;
+      plan.restart();
       GSI_TRY(hip_check(h, hipMemcpyAsync(e.sc, out, sizeof(Scalars), hipMemcpyHostToDevice, h->st), "resume"));
       continue;
     }
@@ -621,7 +614,7 @@ gsi_status run_until_done(gsi_ctx* h, Engine<T>& e, double* hist, Scalars* out, 
       });
       out->done = 0;
       out->grad_ready = 0;
-      full_first = true;
+      plan.restart();
       GSI_TRY(hip_check(h, hipMemcpyAsync(e.sc, out, sizeof(Scalars), hipMemcpyHostToDevice, h->st), "resume"));
       continue;
     }
