@@ -328,11 +328,12 @@ const char* gsi_last_error(gsi_handle h);
  * switch_tol, stall_window. GSI_FP64: float64 blocks throughout. GSI_MIXED_FP32: float32
  * blocks with float64 p x p solves until rho <= max(switch_tol, tol) or until rho has not
  * halved for stall_window iterations, then the iterate, previous gradient and previous direction are widened to
- * float64 and the iteration continues to tol without a restart. 1 <= p[i] <= 32, p[i] < n.
+ * float64 and the iteration continues to tol without a restart. 1 <= p[i] <= 32, p[i] < n, and
+ * no row of more than 7 nonzeros.
  * Arrays A, p, X0 are host arrays of count entries; the CSR arrays (float64 values) and
  * X0[i] (n x p float64, row-major) are device pointers owned by the caller and copied.
- * Errors: GSI_EINVAL (bad sizes, invalid CSR, non-finite values, problem index reported by
- * gsi_batched_last_error), GSI_ENOMEM, GSI_EDEVICE. The handle is returned even on failure
+ * Errors: GSI_EINVAL (bad sizes, invalid CSR, a longer row, non-finite values, problem index
+ * reported by gsi_batched_last_error), GSI_ENOMEM, GSI_EDEVICE. The handle is returned even on failure
  * (for the message) and must be destroyed. */
 typedef struct gsi_batch* gsi_batch_handle;
 gsi_status gsi_create_batched(gsi_batch_handle* h, int32_t count, const gsi_csr* A, const int32_t* p,

@@ -39,7 +39,6 @@ namespace gsi {
 constexpr int NBLK = 7;      // X, Y, G0, G1, P0, P1, Z
 constexpr int TMAX = 16;     // largest team of workgroups on one problem
 constexpr int TPM_MIN = 4;   // fewest 64-row tiles per team member that storage is sized for
-constexpr int ROWNZ = 7;     // nonzeros of a row that the matrix product takes (checked at creation)
 // default team policy (gsi_batched_set_tuning changes it): fewest tiles per member,
 // workgroups recruited at one check, iterations between checks
 constexpr int TPM_DEF = 16, GROW_DEF = 4, ESC_DEF = 32;
@@ -1647,8 +1646,14 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
     (void)hipMemcpyAsync(&fl, flags, sizeof(int), hipMemcpyDeviceToHost, b->st);
     e = hipStreamSynchronize(b->st);
     if (e != hipSuccess) { b->err = std::string("validate: ") + hipGetErrorString(e); return GSI_EDEVICE; }
-    // any flag refuses the matrix, that of a row of more than ROWNZ nonzeros too
-    if (fl) { b->err = "problem " + std::to_string(i) + ": invalid CSR or non-finite values"; return GSI_EINVAL; }
+    if (fl & ~CSR_LONG_ROW) {
+      b->err = "problem " + std::to_string(i) + ": invalid CSR or non-finite values";
+      return GSI_EINVAL;
+    }
+    if (fl & CSR_LONG_ROW) {  // b_spmm_gram has no room for longer rows
+      b->err = "problem " + std::to_string(i) + ": a row of more than " + std::to_string(ROWNZ) + " nonzeros";
+      return GSI_EINVAL;
+    }
     double nA = 0.0;
     for (double v : pm) nA = v > nA ? v : nA;
     pr.nA = nA;

@@ -1044,7 +1044,7 @@ gsi_status create_impl(gsi_handle* out, const gsi_csr* A, const gsi_stencil* S, 
   if (fl[0] & 2) return bail(GSI_EINVAL, "column index out of range");
   if (fl[0] & 8) return bail(GSI_EINVAL, "column indices not sorted within a row");
   if (fl[0] & 4) return bail(GSI_BREAKDOWN, "non-finite matrix value");
-  h->spmm_batch = (A && !(fl[0] & 32)) ? 7 : 8;
+  h->spmm_batch = (A && !(fl[0] & CSR_LONG_ROW)) ? ROWNZ : 8;
   if (fl[1]) return bail(GSI_BREAKDOWN, "non-finite value in X0");
   if (A && opt->check_symmetric) {
     // the structure is valid (checked above), so the searches stay inside the arrays

@@ -8,6 +8,12 @@
 
 namespace gsi {
 
+// The check of a CSR matrix sets CSR_LONG_ROW, which is no error of the matrix, where a row holds more
+// than ROWNZ nonzeros (a 3D 7-point stencil). Up to that the matrix products gather a row's nonzeros
+// in one batch, and the batched solve, whose product keeps the nonzeros of 16 rows in a buffer of 128,
+// takes no longer rows.
+constexpr int ROWNZ = 7, CSR_LONG_ROW = 32;
+
 enum class Pass { Grad, Dir, Update, UpdateGrams, UpdateGrad, Spmm, SpmmPlain, Gram, Product };
 
 // When a gradient pass, its reduction and its bookkeeping (after_grad) run. ALWAYS: every

@@ -1918,7 +1918,7 @@ __global__ void k_to_bf16(int64_t count, const double* __restrict__ src, uint16_
 
 // CSR checks and ||A||_inf: partial max of absolute row sums per workgroup, error flags:
 // bit 0 rowptr not monotone / out of range, bit 1 column index out of range, bit 2
-// non-finite value, bit 3 columns not sorted within a row.
+// non-finite value, bit 3 columns not sorted within a row; CSR_LONG_ROW.
 __global__ void k_csr_check(int64_t n, int64_t nnz, const int32_t* __restrict__ rowptr,
                             const int32_t* __restrict__ colind, const double* __restrict__ vals,
                             double* __restrict__ partial_max, int* __restrict__ flags,
@@ -1931,7 +1931,7 @@ __global__ void k_csr_check(int64_t n, int64_t nnz, const int32_t* __restrict__ 
   for (int64_t row = (int64_t)blockIdx.x * WG + threadIdx.x; row < n; row += (int64_t)gridDim.x * WG) {
     const int64_t j0 = rowptr[row], j1 = rowptr[row + 1];
     if (j1 < j0 || j0 < 0 || j1 > nnz) { f |= 1; continue; }
-    if (j1 - j0 > 7) f |= 32;  // not an error: the SpMM's batch of gathers stays at 8
+    if (j1 - j0 > ROWNZ) f |= CSR_LONG_ROW;
     double s = 0.0;
     int32_t prev = -1;
     for (int64_t j = j0; j < j1; ++j) {
@@ -2077,8 +2077,8 @@ void Kernels<T, PP>::spmm_axpy(hipStream_t st, int64_t n, const int32_t* rowptr,
                                int64_t plane_tiles, int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
   const int cols = live_cols(p);
-  if (batch == 7)
-    k_spmm_axpy<T, PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, V, Z, alpha, beta,
+  if (batch == ROWNZ)
+    k_spmm_axpy<T, PP, ROWNZ><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, V, Z, alpha, beta,
                                                                     gamma, plane_tiles, cols);
   else
     k_spmm_axpy<T, PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, V, Z, alpha, beta,
@@ -2119,8 +2119,8 @@ void Kernels<T, PP>::spmm_fin(hipStream_t st, int64_t n, const int32_t* rowptr, 
                               int64_t plane_tiles, int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
   const int cols = live_cols(p);
-  if (batch == 7)
-    k_spmm_fin<PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
+  if (batch == ROWNZ)
+    k_spmm_fin<PP, ROWNZ><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
                                                                  cols);
   else
     k_spmm_fin<PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
@@ -2132,8 +2132,8 @@ void Kernels<T, PP>::spmm16(hipStream_t st, int64_t n, const int32_t* rowptr, co
                             int64_t plane_tiles, int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
   const int cols = live_cols(p);
-  if (batch == 7)
-    k_spmm16<PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
+  if (batch == ROWNZ)
+    k_spmm16<PP, ROWNZ><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
                                                                cols);
   else
     k_spmm16<PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W, Z, sc, mode, plane_tiles,
@@ -2158,8 +2158,8 @@ void Kernels<T, PP>::spmm(hipStream_t st, int64_t n, const int32_t* rowptr, cons
                           int batch, int p) {
   const int64_t grid = spmm_grid((n + TR - 1) / TR, plane_tiles);
   const int cols = live_cols(p);
-  if (batch == 7)
-    k_spmm<T, PP, 7><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W0, W1, Z, sc, mode,
+  if (batch == ROWNZ)
+    k_spmm<T, PP, ROWNZ><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W0, W1, Z, sc, mode,
                                                                plane_tiles, cols);
   else
     k_spmm<T, PP, 8><<<dim3((unsigned)grid), dim3(WG), 0, st>>>(n, rowptr, colind, vals, W0, W1, Z, sc, mode,

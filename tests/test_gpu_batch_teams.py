@@ -91,3 +91,22 @@ def test_row_lengths_of_the_matrix_product(n, p):
         ritz, _ = _solve(b)
     w = np.linalg.eigvalsh(a)[::-1][:p]
     assert np.max(np.abs(ritz[0] - w)) <= 1e-10 * np.max(np.abs(w))
+
+
+def test_longer_rows_are_refused_by_name():
+    """A valid matrix with one row of eight nonzeros among shorter ones: refused, as it has no room
+    in the product's buffer, and the message says so. The same matrix solves on its own."""
+    from paper_2306_10379_amd import gsi
+    n, p = 200, 4
+    a = np.diag(np.linspace(1.0, 5.0, n))
+    a[100, 20:27] = a[20:27, 100] = 0.1
+    A = I.dense_to_csr(a)
+    assert np.diff(A.rowptr).max() == 8
+    X0 = I.start_block(n, p, 5)
+    with pytest.raises(gsi.GsiError, match="problem 1: a row of more than 7 nonzeros") as e:
+        gsi.BatchedSolver([I.dense_to_csr(np.diag(np.linspace(1.0, 5.0, n))), A], [X0, X0], [p, p], which=1)
+    assert e.value.status == gsi.GSI_EINVAL
+    with gsi.Solver(A, X0, p, tol=1e-10) as s:
+        ritz = s.run().ritz
+    w = np.linalg.eigvalsh(a)[::-1][:p]
+    assert np.max(np.abs(ritz - w)) <= 1e-10 * np.max(np.abs(w))
