@@ -359,7 +359,7 @@ gsi_status gsi_batched_get_x(gsi_batch_handle h, int32_t i, double* X_out);
  * count, each nullable. Syncs.
  *
  * Teams: a problem that would outlast the others starts with a team of workgroups (sized at
- * creation from all problems' n and p), and once every problem has started, a running problem
+ * creation from all problems' n and p, and again by gsi_batched_set_tuning), and once every problem has started, a running problem
  * recruits idle workgroups by the team policy of gsi_batched_set_tuning (by default every 32
  * iterations, up to 4 at a time), up to 16 members with at least 16 row tiles of 64 rows each.
  * The members split the tiles, add their partial Grams and sums in member order and repeat
@@ -370,8 +370,8 @@ gsi_status gsi_batched_timeline(gsi_batch_handle h, double* begin_us, double* sw
                                 int32_t* iters_low, int32_t* team);
 /* Team policy of the following solves (defaults 16, 4, 32): a problem recruits idle
  * workgroups every check_every iterations, at most recruit_step at a time, up to one member
- * per tiles_per_member row tiles of 64 rows (and at most 16 members); the limit on members
- * holds for the team that a problem starts with, too. tiles_per_member >= 4,
+ * per tiles_per_member row tiles of 64 rows (and at most 16 members); the teams that the problems
+ * start with are sized anew under that limit. tiles_per_member >= 4,
  * 1 <= recruit_step <= 15, check_every >= 1, else GSI_EINVAL. The values are what
  * paper_2306_10379_amd/tuning.py measures and picks per batch shape. Syncs. */
 gsi_status gsi_batched_set_tuning(gsi_batch_handle h, int32_t tiles_per_member, int32_t recruit_step,

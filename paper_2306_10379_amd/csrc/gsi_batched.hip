@@ -57,7 +57,7 @@ struct BatchProblem {
   double* ritz;             // p outputs (Ritz values of the operator solved)
   int32_t tmax, team;       // largest team allowed this solve / team size reached
   int32_t tcap, tiles;      // member storage allocated; row tiles
-  int32_t team0, pad0;      // workgroups that the problem starts with (at most tmax are taken)
+  int32_t team0, pad0;      // workgroups that the problem starts with (at most tmax)
   int32_t iters, iters_low, status, restarts, null_steps;
   int32_t shape;            // tile shape of the passes (see Shape); 0 = the defaults of Unroll
   double rho;
@@ -1303,12 +1303,6 @@ __device__ __noinline__ void solve_problem(BatchProblem& pr, BatchCtl* ctl, int 
   clk.mark(GSI_PASS_SMALL);
 }
 
-// Workgroups of problem pr's start team under the tiles-per-member limit in force.
-__device__ __forceinline__ int start_team(const BatchProblem& pr, int tpm) {
-  const int cap = max(1, min(pr.tiles / tpm, pr.tcap));
-  return min(pr.team0, cap);
-}
-
 // The first member of problem idx closes its start team: with all `want` members, or after
 // gather_ticks with those that have arrived (a device shared with other work may not hold all
 // workgroups of the launch at once; late members take the next entry). Returns the team size.
@@ -1347,11 +1341,11 @@ __global__ __launch_bounds__(WG) void k_batched(BatchProblem* __restrict__ probs
         const int q = atomicAdd(&ctl->headA, 1);
         if (q >= ctl->nstart) break;
         const QEntry en = ctl->start[q];
-        const int want = start_team(probs[en.prob], ctl->tpm);
+        const int want = probs[en.prob].team0;
         if (en.rank == 0) {
           job = en.prob;
           team = want > 1 ? gather_team(ctl, en.prob, want) : 1;
-        } else if (en.rank < want && (rank = join_start(ctl, en.prob, team)) > 0) {
+        } else if ((rank = join_start(ctl, en.prob, team)) > 0) {
           job = en.prob;
         }
       }
@@ -1467,12 +1461,14 @@ struct gsi_batch {
   std::vector<void*> allocs;
   BatchProblem* dprobs = nullptr;
   BatchCtl* dctl = nullptr;
+  QEntry* dstart = nullptr;  // start queue, room for teams of tcap
   std::vector<BatchProblem> hprobs;
   double* ritz = nullptr;
   std::vector<int64_t> ritz_off;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   int grid = 0;
+  int slots = 0;  // workgroups resident at once
   std::string err;
 };
 
@@ -1506,13 +1502,13 @@ double iteration_cost(const BatchProblem& q, int t, bool mixed) {
 // Start teams. One workgroup streams a block at a rate of its own whatever the rest of the
 // device does, so the largest problems decide when a batch ends: of 256 problems of 1 to 25 thousand
 // rows the last ran 2.4 times as long as the mean workgroup. For a T, every problem gets the fewest
-// members (at most one per TPM_DEF tiles) that bring its iteration under T; the T is taken that
+// members (at most one per tpm tiles) that bring its iteration under T; the T is taken that
 // ends the batch first on `slots` workgroups. Sets team0; returns the members in all. Recruiting
 // alone, every 32 iterations, took 251 ms for those 256 problems and 60 iterations, 130 ms for 5
 // problems of 3600 to 19600 rows and 83 ms for 17 of 1600 to 12100; with start teams 205, 25 and 25 ms.
-int start_teams(std::vector<BatchProblem>& probs, int slots, bool mixed) {
+int start_teams(std::vector<BatchProblem>& probs, int slots, bool mixed, int tpm) {
   auto cost = [&](const BatchProblem& q, int t) { return iteration_cost(q, t, mixed); };
-  auto cap = [](const BatchProblem& q) { return std::max(1, std::min(q.tiles / TPM_DEF, q.tcap)); };
+  auto cap = [tpm](const BatchProblem& q) { return std::max(1, std::min(q.tiles / tpm, q.tcap)); };
   auto members = [&](const BatchProblem& q, double T) {
     int t = 1;
     while (t < cap(q) && cost(q, t) > T) ++t;
@@ -1560,6 +1556,42 @@ int start_teams(std::vector<BatchProblem>& probs, int slots, bool mixed) {
     all += q.team0;
   }
   return (int)std::min<int64_t>(all, slots);
+}
+
+// Start teams and start queue for at least tpm tiles a member: team0 and the queue to the device,
+// nstart and tpm to ctl (which the caller uploads), and the grid, whose launch is captured anew if it
+// changes.
+hipError_t plan_start(gsi_batch* b, int tpm, BatchCtl& ctl) {
+  const int count = b->count;
+  const int members = start_teams(b->hprobs, b->slots, b->mixed != 0, tpm);
+  // queue: longest first by the estimate, the start teams before all. (By n p a problem of few
+  // columns, whose blocks are padded to 16, starts too late: one of 17424 x 4 ended a batch alone.)
+  std::vector<int32_t> order(count);
+  for (int i = 0; i < count; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
+    const BatchProblem &pa = b->hprobs[a], &pc = b->hprobs[c];
+    if ((pa.team0 > 1) != (pc.team0 > 1)) return pa.team0 > 1;
+    return iteration_cost(pa, 1, b->mixed != 0) > iteration_cost(pc, 1, b->mixed != 0);
+  });
+  std::vector<QEntry> start;
+  for (int i : order)
+    for (int r = 0; r < b->hprobs[i].team0; ++r) start.push_back(QEntry{i, r});
+  ctl.nstart = (int32_t)start.size();
+  ctl.tpm = tpm;
+  // persistent grid: enough workgroups to fill the device, never more than there is work for
+  const int grid = std::max(1, std::min(std::max(count, members), b->slots));
+  if (grid != b->grid) {
+    if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
+    if (b->graph) (void)hipGraphDestroy(b->graph);
+    b->gexec = nullptr;
+    b->graph = nullptr;
+    b->grid = grid;
+  }
+  hipError_t e = hipMemcpy(b->dstart, start.data(), sizeof(QEntry) * start.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess)
+    e = hipMemcpy2D(&b->dprobs->team0, sizeof(BatchProblem), &b->hprobs[0].team0, sizeof(BatchProblem),
+                    sizeof(int32_t), count, hipMemcpyHostToDevice);
+  return e;
 }
 
 double tick_us() {
@@ -1676,21 +1708,10 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
   (void)hipGetDevice(&dev);
   if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0) ncu = prop.multiProcessorCount;
   if (e != hipSuccess) { b->err = std::string("kernel attributes: ") + hipGetErrorString(e); return GSI_EDEVICE; }
-  const int slots = ncu * std::max(per_cu, 1);  // workgroups resident at once
-  const int members = start_teams(b->hprobs, slots, b->mixed != 0);
-  // queue: longest first by the estimate, the start teams before all. (By n p a problem of few
-  // columns, whose blocks are padded to 16, starts too late: one of 17424 x 4 ended a batch alone.)
-  std::vector<int32_t> order(count);
-  for (int i = 0; i < count; ++i) order[i] = i;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
-    const BatchProblem &pa = b->hprobs[a], &pc = b->hprobs[c];
-    if ((pa.team0 > 1) != (pc.team0 > 1)) return pa.team0 > 1;
-    return iteration_cost(pa, 1, b->mixed != 0) > iteration_cost(pc, 1, b->mixed != 0);
-  });
-  std::vector<QEntry> start;
-  for (int i : order)
-    for (int r = 0; r < b->hprobs[i].team0; ++r) start.push_back(QEntry{i, r});
-  QEntry* dstart = balloc<QEntry>(b, start.size(), e);
+  b->slots = ncu * std::max(per_cu, 1);
+  size_t room = 0;
+  for (const BatchProblem& q : b->hprobs) room += q.tcap;
+  b->dstart = balloc<QEntry>(b, room, e);
   int32_t* arrive = balloc<int32_t>(b, count, e);
   int32_t* gathered = balloc<int32_t>(b, count, e);
   b->dprobs = balloc<BatchProblem>(b, count, e);
@@ -1712,11 +1733,9 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
   ctl.mixed = b->mixed;
   ctl.tol = opt->tol;
   ctl.switch_tol = opt->switch_tol;
-  ctl.tpm = TPM_DEF;
   ctl.grow_step = GROW_DEF;
   ctl.esc_every = ESC_DEF;
-  ctl.nstart = (int32_t)start.size();
-  ctl.start = dstart;
+  ctl.start = b->dstart;
   ctl.arrive = arrive;
   ctl.gathered = gathered;
   ctl.qB = qB;
@@ -1733,14 +1752,11 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
     ctl.timeout_ticks = (int64_t)khz * 1000 * 30;
     ctl.gather_ticks = (int64_t)khz * 2;
   }
-  e = hipMemcpyAsync(dstart, start.data(), sizeof(QEntry) * start.size(), hipMemcpyHostToDevice, b->st);
-  if (e == hipSuccess) e = hipMemcpyAsync(b->dctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice, b->st);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b->dprobs, b->hprobs.data(), sizeof(BatchProblem) * count, hipMemcpyHostToDevice, b->st);
+  e = hipMemcpyAsync(b->dprobs, b->hprobs.data(), sizeof(BatchProblem) * count, hipMemcpyHostToDevice, b->st);
   if (e == hipSuccess) e = hipStreamSynchronize(b->st);
+  if (e == hipSuccess) e = plan_start(b, TPM_DEF, ctl);
+  if (e == hipSuccess) e = hipMemcpy(b->dctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice);
   if (e != hipSuccess) { b->err = std::string("upload: ") + hipGetErrorString(e); return GSI_EDEVICE; }
-  // persistent grid: enough workgroups to fill the device, never more than there is work for
-  b->grid = std::max(1, std::min(std::max(count, members), slots));
   return GSI_OK;
 }
 
@@ -1805,9 +1821,9 @@ gsi_status gsi_batched_set_tuning(gsi_batch_handle b, int32_t tiles_per_member, 
   }
   BatchCtl ctl;
   hipError_t e = hipMemcpy(&ctl, b->dctl, sizeof(ctl), hipMemcpyDeviceToHost);
-  ctl.tpm = tiles_per_member;
   ctl.grow_step = recruit_step;
   ctl.esc_every = check_every;
+  if (e == hipSuccess) e = plan_start(b, tiles_per_member, ctl);
   if (e == hipSuccess) e = hipMemcpy(b->dctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice);
   if (e != hipSuccess) { b->err = std::string("tuning: ") + hipGetErrorString(e); return GSI_EDEVICE; }
   return GSI_OK;

@@ -51,6 +51,18 @@ def test_start_teams_match_one_workgroup(sides, ps, precision):
             assert np.max(np.abs(x - y) / np.abs(y)) <= 1e-10
 
 
+def test_start_teams_follow_the_tiles_per_member():
+    """A changed limit sizes the start teams anew, up and down (32 tiles: one member per limit)."""
+    with _solver([45], [5]) as b:
+        ref, team = _solve(b)
+        assert team[0] == 2
+        for limit, want in ((4, 8), (8, 4), (32, 1), (16, 2)):
+            b.set_tuning(limit, 1, 1 << 20)  # no recruiting
+            got, team = _solve(b)
+            assert team[0] == want, (limit, team)
+            assert np.max(np.abs(got[0] - ref[0]) / np.abs(ref[0])) <= 1e-10
+
+
 def test_start_teams_of_two_solvers_at_once():
     """Two launches share the device; each closes its teams with whoever arrives."""
     with _solver([96, 90, 20], [12, 20, 4]) as a, _solver([80, 100], [18, 9]) as b:
