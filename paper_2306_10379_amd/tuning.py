@@ -84,8 +84,10 @@ def apply_cached(solver, path: str, key: str) -> bool:
 #
 # The batched passes' tile shapes are runtime choices per problem (gsi_batched_set_shapes):
 # u row tiles whose loads are issued together in the gradient, direction and product passes,
-# uu in the retraction pass, ug in the Gram passes, and ch nonzeros gathered together in the
-# SpMM. The best choice depends on the problem's size (how many tiles one workgroup sweeps),
+# uu in the retraction pass (with the next gradient), ug in the Gram passes of the start block and of
+# refreshes, and ch nonzeros gathered together in the SpMM. The gradient and Gram passes by
+# themselves run a few times a solve, so that u follows the direction pass and ug hardly counts; the
+# costs are a problem's clocks all the same. The best choice depends on the problem's size (how many tiles one workgroup sweeps),
 # its block width and the precision, so the tuner picks one shape per group
 # (power-of-two band of n, block width 16 or 32, precision): coordinate descent over the
 # four fields, where every candidate value is measured for all groups by one solve of the
