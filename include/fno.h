@@ -37,8 +37,10 @@
  *
  * Limits: N a multiple of 16, N <= 1024; 1 <= m <= 32, m <= N; 1 <= w <= 32; 1 <= p <= 32;
  * L >= 0; batch 1 .. max_batch; bf16_weights 0 or 1. All pointers to data are device pointers owned by the
- * caller; calls are ordered on the stream given at creation; no call allocates after
- * fno_create. Errors: GSI_EINVAL for sizes or null pointers, GSI_ENOMEM, GSI_EDEVICE
+ * caller; calls are ordered on the stream given at creation (NULL: a blocking stream of the
+ * handle's own, ordered with the default stream but not with other handles' streams, so memory
+ * that a call reads or writes must not go to another handle before it has run; fno_stream is the
+ * stream to wait on); no call allocates after fno_create. Errors: GSI_EINVAL for sizes or null pointers, GSI_ENOMEM, GSI_EDEVICE
  * (HIP error, or a singular Gram Y^T Y in the loss: message in fno_last_error). */
 #ifndef FNO_H
 #define FNO_H
@@ -70,6 +72,8 @@ int64_t fno_param_count(const fno_config* cfg);
  * that the untrained network returns the prior) and Adam moments at zero. *h is set even
  * on failure (for the message) and must be destroyed. */
 gsi_status fno_create(fno_handle* h, const fno_config* cfg, uint64_t seed, void* hip_stream);
+/* The stream that the handle's calls run on. */
+void* fno_stream(fno_handle h);
 
 /* Copy parameters in from / out to a device array of fno_param_count floats. */
 gsi_status fno_set_params(fno_handle h, const float* params);

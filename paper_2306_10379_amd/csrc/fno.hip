@@ -1009,6 +1009,8 @@ gsi_status fno_create(fno_handle* out, const fno_config* cfg, uint64_t seed, voi
   return hip_status(h, e, "create");
 }
 
+void* fno_stream(fno_handle h) { return h ? h->st : nullptr; }
+
 gsi_status fno_set_params(fno_handle h, const float* params) {
   if (!h || !params) return GSI_EINVAL;
   hipError_t e = hipMemcpyAsync(h->params, params, h->count * 4, hipMemcpyDeviceToDevice, h->st);

@@ -5,13 +5,14 @@ kernels of libgsi.so (csrc/fno.hip); PyTorch provides device memory and the stre
 """
 from __future__ import annotations
 
+import collections
 import ctypes
 
 import numpy as np
 
 from . import gsi
 
-EXPORTS = ["fno_param_count", "fno_create", "fno_set_params", "fno_get_params", "fno_forward", "fno_loss_grad",
+EXPORTS = ["fno_param_count", "fno_create", "fno_stream", "fno_set_params", "fno_get_params", "fno_forward", "fno_loss_grad",
            "fno_adam", "fno_last_error", "fno_destroy"]
 
 
@@ -33,6 +34,8 @@ def load():
         L.fno_param_count.restype = ctypes.c_int64
         L.fno_create.argtypes = [P(vp), P(FnoConfig), ctypes.c_uint64, vp]
         L.fno_create.restype = ctypes.c_int
+        L.fno_stream.argtypes = [vp]
+        L.fno_stream.restype = vp
         L.fno_set_params.argtypes = [vp, vp]
         L.fno_set_params.restype = ctypes.c_int
         L.fno_get_params.argtypes = [vp, vp]
@@ -68,6 +71,8 @@ class Net:
     handle's device; V is (B, N*N), targets (B, N*N, p). bf16_weights: the passes read a
     bfloat16 copy of the float32 parameters (which Adam updates)."""
 
+    _AHEAD = 4  # calls in flight: enough for the device never to wait for the host
+
     def __init__(self, N=256, modes=24, width=20, layers=4, p=32, max_batch=16, seed=0, stream=None,
                  bf16_weights=False):
         import torch
@@ -81,6 +86,26 @@ class Net:
         s = self.L.fno_create(ctypes.byref(self.h), ctypes.byref(self.cfg), int(seed), ctypes.c_void_p(st))
         self._check(s)
         self.N, self.p, self.n = N, p, N * N
+        self._own = not st
+        self._stream = torch.cuda.ExternalStream(self.L.fno_stream(self.h))
+        self._running = collections.deque()  # (event, tensors) of calls that may still run
+
+    def _hold(self, *tensors):
+        """Keeps the tensors of an asynchronous call alive until it has run. A handle created on the
+        default stream has a stream of its own, which torch's allocator does not know: memory given
+        back while the call runs could become another network's output, on a stream that nothing
+        orders with this one. The tensors of the last _AHEAD calls stay held until later calls or
+        close(); the host waits for the call before those."""
+        import torch
+        if not self._own and torch.cuda.current_stream().cuda_stream == self._stream.cuda_stream:
+            return
+        if len(self._running) < self._AHEAD:
+            ev = torch.cuda.Event()
+        else:
+            ev = self._running.popleft()[0]
+            ev.synchronize()
+        ev.record(self._stream)
+        self._running.append((ev, tensors))
 
     def _check(self, s):
         if s != gsi.GSI_OK:
@@ -96,6 +121,7 @@ class Net:
     def set_params(self, t):
         _need(t, "params", (self.count,))
         self._check(self.L.fno_set_params(self.h, _p(t)))
+        self._hold(t)
 
     def forward(self, V, f64=False):
         import torch
@@ -103,6 +129,7 @@ class Net:
         _need(V, "V", (B, self.n))
         out = torch.empty((B, self.n, self.p), dtype=torch.float64 if f64 else torch.float32, device=V.device)
         self._check(self.L.fno_forward(self.h, _p(V), B, None if f64 else _p(out), _p(out) if f64 else None))
+        self._hold(V, out)
         return out
 
     def loss_grad(self, V, Xs, want_grad=True):
@@ -120,8 +147,9 @@ class Net:
 
     def close(self):
         if getattr(self, "h", None) is not None and self.h.value:
-            self.L.fno_destroy(self.h)
+            self.L.fno_destroy(self.h)  # waits for the stream
         self.h = None
+        self._running = ()
 
     def __del__(self):
         try:

@@ -170,3 +170,28 @@ def test_bf16_adam_updates_the_float32_master():
     Yref = F.predict(F.round_bf16(w), V32, cfg)
     assert np.max(np.abs(Y - Yref)) <= 2e-5 * np.max(np.abs(Yref))
     net.close()
+
+
+def test_outputs_of_two_networks_do_not_meet_in_memory():
+    """The output of a dropped forward pass goes back to torch's allocator while the pass still
+    runs, and another network's next output takes its place: all calls of handles created on one
+    stream are ordered, so the second is written last. No synchronization between the passes."""
+    cfg, B = F.Config(N=64, m=12, w=9, L=1, p=7), 4
+    nets, ref = [], []
+    V = _dev(_case(cfg, B, 1)[1])
+    for seed in (3, 4):
+        net = _net(cfg, B, seed)
+        net.set_params(_dev(_case(cfg, B, seed)[0]))
+        ref.append(net.forward(V).clone())
+        nets.append(net)
+    torch.cuda.synchronize()
+    assert not torch.equal(ref[0], ref[1])
+    for k in range(40):
+        a, b = nets[k % 2], nets[1 - k % 2]
+        r = a.forward(V)
+        for _ in range(4):
+            b.forward(V)  # dropped at once
+        r = a.forward(V)
+        assert torch.equal(r, ref[k % 2]), k
+    for net in nets:
+        net.close()
