@@ -57,7 +57,6 @@ struct BatchProblem {
   double* ritz;             // p outputs (Ritz values of the operator solved)
   int32_t tmax, team;       // largest team allowed this solve / team size reached
   int32_t tcap, tiles;      // member storage allocated; row tiles
-  int32_t team0, pad0;      // workgroups that the problem starts with (at most tmax)
   int32_t iters, iters_low, status, restarts, null_steps;
   int32_t shape;            // tile shape of the passes (see Shape); 0 = the defaults of Unroll
   double rho;
@@ -71,8 +70,9 @@ struct LoopState {
   double gg_old, rho_best, gg, gdot;
 };
 
+// Entry of a queue: member `rank` of problem `prob`; team: size of the start team (start queue).
 struct QEntry {
-  int32_t prob, rank;
+  int32_t prob, rank, team, pad;
 };
 
 struct BatchCtl {
@@ -1316,12 +1316,23 @@ __device__ int gather_team(BatchCtl* ctl, int idx, int want) {
 }
 
 // A workgroup arrives for the start team of problem idx: its rank and the team size in
-// `team`, or rank 0 if the team was closed without it. Thread 0.
+// `team`, or rank 0 if the team was closed without it. Thread 0. The first member took its entry
+// before this one did, with a team of more than one in it, and closes the team within gather_ticks;
+// the wait ends as the other ones do if that should fail.
 __device__ int join_start(BatchCtl* ctl, int idx, int& team) {
   const int a = atomicAdd(ctl->arrive + idx, 1);
   if (a & GATHERED) return 0;
-  // the first member took its entry before this one did and closes the team within gather_ticks
-  while ((team = ld_acq(ctl->gathered + idx)) == 0) __builtin_amdgcn_s_sleep(1);
+  const int64_t t0 = wall_clock64();
+  int t;
+  while ((t = ld_acq(ctl->gathered + idx)) == 0) {
+    if (ld_acq(&ctl->abort)) return 0;
+    if (wall_clock64() - t0 > ctl->timeout_ticks + ctl->gather_ticks) {
+      st_rel(&ctl->abort, 1);
+      return 0;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  team = t;
   return a + 1;
 }
 
@@ -1341,10 +1352,9 @@ __global__ __launch_bounds__(WG) void k_batched(BatchProblem* __restrict__ probs
         const int q = atomicAdd(&ctl->headA, 1);
         if (q >= ctl->nstart) break;
         const QEntry en = ctl->start[q];
-        const int want = probs[en.prob].team0;
         if (en.rank == 0) {
           job = en.prob;
-          team = want > 1 ? gather_team(ctl, en.prob, want) : 1;
+          team = en.team > 1 ? gather_team(ctl, en.prob, en.team) : 1;
         } else if ((rank = join_start(ctl, en.prob, team)) > 0) {
           job = en.prob;
         }
@@ -1462,7 +1472,9 @@ struct gsi_batch {
   BatchProblem* dprobs = nullptr;
   BatchCtl* dctl = nullptr;
   QEntry* dstart = nullptr;  // start queue, room for teams of tcap
+  BatchCtl hctl{};           // *dctl as uploaded (the kernels change its queue heads and counters only)
   std::vector<BatchProblem> hprobs;
+  std::vector<int32_t> team0;  // workgroups that each problem starts with
   double* ritz = nullptr;
   std::vector<int64_t> ritz_off;
   hipGraph_t graph = nullptr;
@@ -1481,6 +1493,13 @@ U* balloc(gsi_batch* b, size_t count, hipError_t& e) {
   if (e != hipSuccess) return nullptr;
   b->allocs.push_back(p);
   return reinterpret_cast<U*>(p);
+}
+
+// Host data to the device, on the handle's stream and complete on return: the launches that read it
+// are on that stream, which a copy on the default stream need not precede.
+hipError_t upload(gsi_batch* b, void* dst, const void* src, size_t bytes) {
+  const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, b->st);
+  return e == hipSuccess ? hipStreamSynchronize(b->st) : e;
 }
 
 gsi_status fetch(gsi_batch* b, std::vector<BatchProblem>& res) {
@@ -1506,7 +1525,7 @@ double iteration_cost(const BatchProblem& q, int t, bool mixed) {
 // ends the batch first on `slots` workgroups. Sets team0; returns the members in all. Recruiting
 // alone, every 32 iterations, took 251 ms for those 256 problems and 60 iterations, 130 ms for 5
 // problems of 3600 to 19600 rows and 83 ms for 17 of 1600 to 12100; with start teams 205, 25 and 25 ms.
-int start_teams(std::vector<BatchProblem>& probs, int slots, bool mixed, int tpm) {
+int start_teams(const std::vector<BatchProblem>& probs, int slots, bool mixed, int tpm, std::vector<int32_t>& team0) {
   auto cost = [&](const BatchProblem& q, int t) { return iteration_cost(q, t, mixed); };
   auto cap = [tpm](const BatchProblem& q) { return std::max(1, std::min(q.tiles / tpm, q.tcap)); };
   auto members = [&](const BatchProblem& q, double T) {
@@ -1551,33 +1570,32 @@ int start_teams(std::vector<BatchProblem>& probs, int slots, bool mixed, int tpm
     if (m < 0.999 * end) { end = m; best = T; }
   }
   int64_t all = 0;
-  for (BatchProblem& q : probs) {
-    q.team0 = members(q, best);
-    all += q.team0;
+  team0.clear();
+  for (const BatchProblem& q : probs) {
+    team0.push_back(members(q, best));
+    all += team0.back();
   }
   return (int)std::min<int64_t>(all, slots);
 }
 
-// Start teams and start queue for at least tpm tiles a member: team0 and the queue to the device,
-// nstart and tpm to ctl (which the caller uploads), and the grid, whose launch is captured anew if it
-// changes.
-hipError_t plan_start(gsi_batch* b, int tpm, BatchCtl& ctl) {
+// Start teams and start queue for at least tpm tiles a member, and the grid, whose launch is captured
+// anew if it changes. Uploads the queue and the control block, whose other fields are set.
+hipError_t plan_start(gsi_batch* b, int tpm) {
   const int count = b->count;
-  const int members = start_teams(b->hprobs, b->slots, b->mixed != 0, tpm);
+  const int members = start_teams(b->hprobs, b->slots, b->mixed != 0, tpm, b->team0);
   // queue: longest first by the estimate, the start teams before all. (By n p a problem of few
   // columns, whose blocks are padded to 16, starts too late: one of 17424 x 4 ended a batch alone.)
   std::vector<int32_t> order(count);
   for (int i = 0; i < count; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
-    const BatchProblem &pa = b->hprobs[a], &pc = b->hprobs[c];
-    if ((pa.team0 > 1) != (pc.team0 > 1)) return pa.team0 > 1;
-    return iteration_cost(pa, 1, b->mixed != 0) > iteration_cost(pc, 1, b->mixed != 0);
+    if ((b->team0[a] > 1) != (b->team0[c] > 1)) return b->team0[a] > 1;
+    return iteration_cost(b->hprobs[a], 1, b->mixed != 0) > iteration_cost(b->hprobs[c], 1, b->mixed != 0);
   });
   std::vector<QEntry> start;
   for (int i : order)
-    for (int r = 0; r < b->hprobs[i].team0; ++r) start.push_back(QEntry{i, r});
-  ctl.nstart = (int32_t)start.size();
-  ctl.tpm = tpm;
+    for (int r = 0; r < b->team0[i]; ++r) start.push_back(QEntry{i, r, b->team0[i], 0});
+  b->hctl.nstart = (int32_t)start.size();
+  b->hctl.tpm = tpm;
   // persistent grid: enough workgroups to fill the device, never more than there is work for
   const int grid = std::max(1, std::min(std::max(count, members), b->slots));
   if (grid != b->grid) {
@@ -1587,11 +1605,8 @@ hipError_t plan_start(gsi_batch* b, int tpm, BatchCtl& ctl) {
     b->graph = nullptr;
     b->grid = grid;
   }
-  hipError_t e = hipMemcpy(b->dstart, start.data(), sizeof(QEntry) * start.size(), hipMemcpyHostToDevice);
-  if (e == hipSuccess)
-    e = hipMemcpy2D(&b->dprobs->team0, sizeof(BatchProblem), &b->hprobs[0].team0, sizeof(BatchProblem),
-                    sizeof(int32_t), count, hipMemcpyHostToDevice);
-  return e;
+  const hipError_t e = upload(b, b->dstart, start.data(), sizeof(QEntry) * start.size());
+  return e == hipSuccess ? upload(b, b->dctl, &b->hctl, sizeof(BatchCtl)) : e;
 }
 
 double tick_us() {
@@ -1722,8 +1737,7 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
   int32_t* grow = balloc<int32_t>(b, count, e);
   LoopState* ls = balloc<LoopState>(b, count, e);
   if (e != hipSuccess) { b->err = "allocation failed"; return GSI_ENOMEM; }
-  BatchCtl ctl;
-  memset(&ctl, 0, sizeof(ctl));
+  BatchCtl& ctl = b->hctl;
   ctl.count = count;
   ctl.method = opt->method;
   ctl.k_restart = opt->k_restart;
@@ -1752,10 +1766,8 @@ gsi_status gsi_create_batched(gsi_batch_handle* out, int32_t count, const gsi_cs
     ctl.timeout_ticks = (int64_t)khz * 1000 * 30;
     ctl.gather_ticks = (int64_t)khz * 2;
   }
-  e = hipMemcpyAsync(b->dprobs, b->hprobs.data(), sizeof(BatchProblem) * count, hipMemcpyHostToDevice, b->st);
-  if (e == hipSuccess) e = hipStreamSynchronize(b->st);
-  if (e == hipSuccess) e = plan_start(b, TPM_DEF, ctl);
-  if (e == hipSuccess) e = hipMemcpy(b->dctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice);
+  e = upload(b, b->dprobs, b->hprobs.data(), sizeof(BatchProblem) * count);
+  if (e == hipSuccess) e = plan_start(b, TPM_DEF);
   if (e != hipSuccess) { b->err = std::string("upload: ") + hipGetErrorString(e); return GSI_EDEVICE; }
   return GSI_OK;
 }
@@ -1819,12 +1831,10 @@ gsi_status gsi_batched_set_tuning(gsi_batch_handle b, int32_t tiles_per_member, 
     if (b) b->err = "tuning: tiles_per_member >= 4, 1 <= recruit_step <= 15, check_every >= 1";
     return GSI_EINVAL;
   }
-  BatchCtl ctl;
-  hipError_t e = hipMemcpy(&ctl, b->dctl, sizeof(ctl), hipMemcpyDeviceToHost);
-  ctl.grow_step = recruit_step;
-  ctl.esc_every = check_every;
-  if (e == hipSuccess) e = plan_start(b, tiles_per_member, ctl);
-  if (e == hipSuccess) e = hipMemcpy(b->dctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice);
+  if (!b->dctl) { b->err = "tuning: the handle was not created"; return GSI_EDEVICE; }
+  b->hctl.grow_step = recruit_step;
+  b->hctl.esc_every = check_every;
+  const hipError_t e = plan_start(b, tiles_per_member);
   if (e != hipSuccess) { b->err = std::string("tuning: ") + hipGetErrorString(e); return GSI_EDEVICE; }
   return GSI_OK;
 }
@@ -1846,12 +1856,13 @@ gsi_status gsi_batched_set_shapes(gsi_batch_handle b, const int32_t* shapes) {
     }
   }
   std::vector<BatchProblem> cur(b->count);
-  hipError_t e = hipMemcpy(cur.data(), b->dprobs, sizeof(BatchProblem) * b->count, hipMemcpyDeviceToHost);
+  hipError_t e = hipMemcpyAsync(cur.data(), b->dprobs, sizeof(BatchProblem) * b->count, hipMemcpyDeviceToHost, b->st);
+  if (e == hipSuccess) e = hipStreamSynchronize(b->st);
   for (int i = 0; i < b->count; ++i) {
     cur[i].shape = shapes[i];
     b->hprobs[i].shape = shapes[i];
   }
-  if (e == hipSuccess) e = hipMemcpy(b->dprobs, cur.data(), sizeof(BatchProblem) * b->count, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = upload(b, b->dprobs, cur.data(), sizeof(BatchProblem) * b->count);
   if (e != hipSuccess) { b->err = std::string("shapes: ") + hipGetErrorString(e); return GSI_EDEVICE; }
   return GSI_OK;
 }
@@ -1863,10 +1874,9 @@ gsi_status gsi_batched_set_wait_limit(gsi_batch_handle b, double seconds) {
   }
   const double us = tick_us();
   if (!(us > 0.0)) { b->err = "wait limit: wall clock rate unavailable"; return GSI_EDEVICE; }
-  BatchCtl ctl;
-  hipError_t e = hipMemcpy(&ctl, b->dctl, sizeof(ctl), hipMemcpyDeviceToHost);
-  ctl.timeout_ticks = (int64_t)(seconds * 1e6 / us) > 0 ? (int64_t)(seconds * 1e6 / us) : 1;
-  if (e == hipSuccess) e = hipMemcpy(b->dctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice);
+  if (!b->dctl) { b->err = "wait limit: the handle was not created"; return GSI_EDEVICE; }
+  b->hctl.timeout_ticks = (int64_t)(seconds * 1e6 / us) > 0 ? (int64_t)(seconds * 1e6 / us) : 1;
+  const hipError_t e = upload(b, b->dctl, &b->hctl, sizeof(BatchCtl));
   if (e != hipSuccess) { b->err = std::string("wait limit: ") + hipGetErrorString(e); return GSI_EDEVICE; }
   return GSI_OK;
 }

@@ -63,6 +63,30 @@ def test_start_teams_follow_the_tiles_per_member():
             assert np.max(np.abs(got[0] - ref[0]) / np.abs(ref[0])) <= 1e-10
 
 
+def test_every_solve_follows_the_limit_set_before_it():
+    """Limits set and solves launched one after the other on a stream that the default stream does
+    not wait for: queue, teams and control block belong together in every one of them."""
+    from paper_2306_10379_amd import gsi
+    sides, ps = [45, 64, 20, 33], [5, 9, 4, 20]
+    tiles = [(N * N + 63) // 64 for N in sides]
+    mats = [I.schrodinger_2d(N, I.random_wells(900 + N, count=(4, 6))) for N in sides]
+    X0s = [I.start_block(A.n, p, 901) for A, p in zip(mats, ps)]
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        b = gsi.BatchedSolver(mats, X0s, ps, which=-1, precision="fp64", max_iter=3)
+        for k in range(40):
+            limit = (4, 8, 16, 32, 1 << 20)[k % 5]
+            b.set_tuning(limit, 1, 1 << 20)
+            _, iters, status = b.solve()
+            *_, team = b.timeline()
+            assert np.all(iters == 3) and np.all(status == 2)
+            assert all(t <= max(1, min(16, n // limit)) for t, n in zip(team, tiles)), (limit, team)
+            if limit == 1 << 20:
+                assert np.all(team == 1)
+        torch.cuda.synchronize()
+
+
 def test_start_teams_of_two_solvers_at_once():
     """Two launches share the device; each closes its teams with whoever arrives."""
     with _solver([96, 90, 20], [12, 20, 4]) as a, _solver([80, 100], [18, 9]) as b:
