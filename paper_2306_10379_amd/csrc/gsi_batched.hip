@@ -135,9 +135,12 @@ __device__ __forceinline__ void pass_barrier() {
   __syncthreads();
 }
 
-// Tiles whose loads are issued together in the streaming passes (the defaults, sized so that
-// no pass spills registers): U for the passes reading three blocks, UU for the retraction
-// (four blocks), UG for the Grams; CH nonzeros gathered per batch in the SpMM.
+// Tiles whose loads are issued together in the streaming passes (the defaults): U for the passes
+// reading three blocks, UU for the retraction (five blocks), UG for the Grams of the start and of
+// refreshes; CH nonzeros gathered per batch in the SpMM. Sized for the 256 + 256 registers of a wave
+// that has its SIMD to itself: the whole kernel spills 10 of them (its scratch, 1660 bytes a lane,
+// is mostly the frames of the pass functions), which the retraction's three products and its Gram
+// need at 32 float64 columns.
 template <typename T, int PP>
 struct Unroll {
   static constexpr int U = sizeof(T) * PP >= 256 ? 2 : 4;

@@ -483,10 +483,10 @@ __device__ __forceinline__ void diag_order(int p, int* ord, double* key, F d) {
 // column (lane xor 1, 2, 7 walk through all 8 pairings): no LDS and no barrier. The blocks of 8
 // columns go round the waves (circle tournament) through LDS once every 8 rounds. The
 // two-sided Jacobi with the matrix and V in LDS that this replaces moved both every round:
-// k_eig 526 -> 168 us at p = 64 (35 x 40 x 25 Laplacian, 25 iterations from a random block),
-// 113 -> 63 us at p = 32, 28 -> 26 us at p = 8, 22 -> 1.6 ms at p = 128 (where half the
-// matrix's traffic went to memory). A round takes 500 clocks at p <= 16 and 750 at p = 64, a
-// sweep p - 1 of them.
+// k_eig 526 -> 171 us at p = 64 (35 x 40 x 25 Laplacian, 25 iterations from a random block),
+// 113 -> 63 us at p = 32, 28 -> 26 us at p = 8, 22 -> 1.2 ms at p = 128 (where half the
+// matrix's traffic went to memory). A round takes 510 clocks at p <= 16 and 760 at p = 64, a
+// sweep p - 1 of them (some 10 of it for the half angle, against a cosine and sine).
 //
 // A pair is rotated when |x.y| > eps |x| |y|. A larger bound saves nothing, since every pairing is
 // computed whether it rotates or not; with sqrt(PP) eps the vectors were orthogonal to 1.8e-15 at p =

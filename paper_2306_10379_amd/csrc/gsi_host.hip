@@ -956,9 +956,11 @@ gsi_status create_impl(gsi_handle* out, const gsi_csr* A, const gsi_stencil* S, 
   (void)hipGetDevice(&dev);
   int ncu = 256;
   if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0) ncu = prop.multiProcessorCount;
-  // two workgroups per CU for the streaming passes (the register-limited residency of the
-  // float64 passes at p = 64): more workgroups did not move the passes and only enlarge the
-  // per-workgroup partial sums the reductions read (measured at n = 128^3, p = 64)
+  // two workgroups per CU for the streaming passes: more workgroups did not move the passes and only
+  // enlarge the per-workgroup partial sums the reductions read (measured at n = 128^3, p = 64). It
+  // is the residency that registers leave the float64 Gram pass and the fused retraction of 33 to
+  // 48 columns; the direction pass could have three, the fused retraction of 49 to 64 columns
+  // (256 + 92 registers) has one, and runs its second half as a second round.
   // no more of them than give the same largest share of the tiles: 274 instead of 512 for the
   // 547 tiles of the 35 x 40 x 25 grid, two tiles each either way and half the partial sums
   auto spread = [&](int64_t most) {

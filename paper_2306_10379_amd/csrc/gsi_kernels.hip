@@ -687,8 +687,11 @@ __global__ __launch_bounds__(WG) void k_update(int64_t n, T* __restrict__ X, T* 
 // by rounding only (the product with C is taken before the rounding of X_new).
 //
 // W: columns in use, whole 16-column blocks. A block of 33 to 48 columns is stored 64 wide; its
-// last 16 columns are zero from the allocation on, are not read or written here nor in the
-// direction pass, and have no products (p = 40, n = 250007: 251 -> 163 us, direction 99 -> 82).
+// last 16 columns are not read or written here nor in the direction pass, and have no products (p =
+// 40, n = 250007: 251 -> 163 us, direction 99 -> 82). In X, Y, Z and P they are zero: from the
+// allocation, from the pack of a start block, and from every pass that writes whole rows (products
+// with factors whose padding is zero, A times such a block). Those of a G may hold what
+// gsi_set_values unpacked there; nothing reads them but the separate gradient pass, beside zeros.
 // Only this width has a block of 16 to leave out: 17 to 32 and 49 to 64 columns use all of theirs.
 template <typename T, int PP, int W = PP>
 __global__ __launch_bounds__(WG) void k_update_grad(int64_t n, T* __restrict__ X, T* __restrict__ Y,
@@ -2069,7 +2072,7 @@ void Kernels<T, PP>::dir(hipStream_t st, int nb, int64_t n, const T* X, const T*
 // Columns of a block that the CSR products gather: p up to whole 16-column groups (a cache line in
 // float64). The padding columns past them are zero in W and are written as zeros; their lanes have
 // no nonzeros to go through. On random columns the gathers are the cost: 428 -> 335 us at n = 250007,
-// 25 nonzeros a row, p = 40.
+// 24 nonzeros a row, p = 40.
 static int live_cols(int p) { return (p + 15) / 16 * 16; }
 template <typename T, int PP>
 void Kernels<T, PP>::spmm_axpy(hipStream_t st, int64_t n, const int32_t* rowptr, const int32_t* colind, const T* vals,

@@ -339,13 +339,13 @@ __device__ __forceinline__ void quad_diag(int nb, const double* V, const double*
 // linesearch_lds_doubles(PP); terms, smu, sok, sevals, sbmax in shared memory. Whole workgroup
 // of dense_threads(PP).
 //
-// Twelve p x p products one after the other, and Get_Mu (5 us at p = 8, 7 us at p = 64), bound
-// it. Matrices sit in LDS at the stride that keeps the operand loads free of bank conflicts
+// Four quadratic diagonals, Get_Mu (5 us at p = 8, 7 us at p = 64) and eight p x p products, one
+// after the other, bound it. Matrices sit in LDS at the stride that keeps the operand loads free of bank conflicts
 // (with a stride of PP each load hit one bank 16 times), the Grams are read coalesced, blocks
-// below the diagonal of symmetric products and past p are left out: k_linesearch 108 -> 64 us at
-// p = 64, 30 -> 27 us at p = 32, 15.5 -> 14.5 us at p = 8, 1010 -> 293 us at p = 128. Above PP = 64
-// one matrix fits LDS (V, then M in its two stages) and the others sit in the work area of the
-// small buffer, always read by rows.
+// below the diagonal of symmetric products and past p are left out: k_linesearch 108 -> 68 us at
+// p = 64 (3 of them for b, the fourth diagonal), 30 -> 29 us at p = 32, 15.5 -> 15 us at p = 8, 1010
+// -> 287 us at p = 128. Above PP = 64 one matrix fits LDS (V, then M in its two stages) and the
+// others sit in the work area of the small buffer, always read by rows.
 constexpr int linesearch_lds_doubles(int PP) { return (PP > PP_LDS_MAX ? 1 : 4) * PP * (PP + 2); }
 
 template <int PP>
