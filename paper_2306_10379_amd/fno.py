@@ -95,8 +95,11 @@ class Net:
         default stream has a stream of its own, which torch's allocator does not know: memory given
         back while the call runs could become another network's output, on a stream that nothing
         orders with this one. The tensors of the last _AHEAD calls stay held until later calls or
-        close(); the host waits for the call before those."""
+        close(); the host waits for the call before those. A call recorded into a graph is not held: its
+        memory is the graph's, and an event recorded with it cannot be waited for."""
         import torch
+        if torch.cuda.is_current_stream_capturing():
+            return
         if not self._own and torch.cuda.current_stream().cuda_stream == self._stream.cuda_stream:
             return
         if len(self._running) < self._AHEAD:

@@ -174,8 +174,8 @@ def test_bf16_adam_updates_the_float32_master():
 
 def test_outputs_of_two_networks_do_not_meet_in_memory():
     """The output of a dropped forward pass goes back to torch's allocator while the pass still
-    runs, and another network's next output takes its place: all calls of handles created on one
-    stream are ordered, so the second is written last. No synchronization between the passes."""
+    runs, and another network's next output would take its place, written by a stream that nothing
+    orders with the first: the network holds it. No synchronization between the passes."""
     cfg, B = F.Config(N=64, m=12, w=9, L=1, p=7), 4
     nets, ref = [], []
     V = _dev(_case(cfg, B, 1)[1])
@@ -195,3 +195,36 @@ def test_outputs_of_two_networks_do_not_meet_in_memory():
         assert torch.equal(r, ref[k % 2]), k
     for net in nets:
         net.close()
+
+
+def test_forward_on_a_stream_forked_from_a_capture():
+    """A network on a side stream, recorded into a graph of another stream: more passes than a
+    network keeps tensors for, replayed with eager passes between the replays."""
+    cfg, B = F.Config(N=64, m=12, w=9, L=1, p=7), 2
+    flat, V = _case(cfg, B, 5)[:2]
+    V = _dev(V)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        net = _net(cfg, B, 5)
+    net.set_params(_dev(flat))
+    ref = net.forward(V)
+    torch.cuda.synchronize()
+    ref = ref.clone()
+    n = 2 * net._AHEAD
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        cur = torch.cuda.current_stream()
+        side.wait_stream(cur)
+        outs = [net.forward(V) for _ in range(n)]
+        cur.wait_stream(side)
+    for k in range(3):
+        for o in outs:
+            o.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for o in outs:
+            assert torch.equal(o, ref), k
+        r = net.forward(V)
+        torch.cuda.synchronize()
+        assert torch.equal(r, ref), k
+    net.close()
